@@ -61,6 +61,10 @@ inline thread_local bool in_capture = false;
 // LDS windows allow, for latency hiding.
 #define MGCD_ROWS_OCCUPANCY(K) __attribute__((amdgpu_waves_per_eu((K) >= 16 ? 4 : 1, 8)))
 
+// Inlined always: as a call, arrays held in registers would go to scratch memory.
+#define MGCD_INLINE __attribute__((always_inline)) inline
+#define MGCD_LAMBDA __attribute__((always_inline))
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Sets the calling thread's message returned by mgcd_last_error().

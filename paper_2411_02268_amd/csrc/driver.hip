@@ -148,10 +148,16 @@ struct Counts {
 };
 
 static Counts read_counts(const unsigned long long *ctr, hipStream_t st) {
-  unsigned long long h[3];
-  MGCD_HIP(hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, st));
+  std::vector<unsigned long long> h(CTR_WORDS);
+  MGCD_HIP(hipMemcpyAsync(h.data(), ctr, CTR_WORDS * sizeof(h[0]), hipMemcpyDeviceToHost, st));
   MGCD_HIP(hipStreamSynchronize(st));
-  return Counts{h[0], h[1], h[2]};
+  Counts c{0, 0, 0};
+  for (int x = 0; x < SPREAD; ++x) {
+    c.moved += h[(size_t)x * CTR_STRIDE];
+    c.prop += h[(size_t)x * CTR_STRIDE + 1];
+    c.sumG += h[(size_t)x * CTR_STRIDE + 2];
+  }
+  return c;
 }
 
 // grow: a segment that ends with the level still moving is followed by one twice as
@@ -191,7 +197,7 @@ static void run_lpa(const mgcd_csr *gin, const mgcd_params *p, int32_t *out, Are
   uint32_t *K = a.take<uint32_t>(n);
   prepare(g, p, K, a, st);
   int32_t *Ca = a.take<int32_t>(n), *Cb = a.take<int32_t>(n);
-  unsigned long long *ctr = a.take<unsigned long long>(4);
+  unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
   launch_iota(Ca, n, st);
   // sweeps on the degree-ordered copy (labels by position, values the communities'
   // own ids), or on the input
@@ -214,7 +220,7 @@ static void run_lpa(const mgcd_csr *gin, const mgcd_params *p, int32_t *out, Are
   mgcd_stats s{};
   ClassTimer ct;
   lm.start();
-  launch_zero_u64(ctr, 4, st);
+  launch_zero_u64(ctr, CTR_WORDS, st);
   launch_zero_state(ls, st);
   if (n > 0) {
     LevelState h = run_sweeps(p->max_iterations, ls, st, &ct, s, false, [&](int it, int j) {
@@ -263,7 +269,7 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
   int32_t *prop = leiden ? a.take<int32_t>(n) : nullptr;
   int32_t *nprop = leiden ? a.take<int32_t>(n) : nullptr;
   int32_t *from = leiden ? a.take<int32_t>(n) : nullptr;
-  unsigned long long *ctr = a.take<unsigned long long>(4);
+  unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
   LevelState *ls = a.take<LevelState>(1);
   struct Slot {
     int64_t *off;
@@ -310,7 +316,7 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
     // rows without entries are in no sweep: both label buffers start equal
     if (nl > 0) MGCD_HIP(hipMemcpyAsync(Cb, Ca, (size_t)nl * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     launch_community_totals(Ca, Km, Sig, nl, st);
-    launch_zero_u64(ctr, 4, st);
+    launch_zero_u64(ctr, CTR_WORDS, st);
     launch_zero_state(ls, st);
     LevelState h = run_sweeps(p->max_iterations, ls, st, pass == 0 ? &ct : nullptr, s,
                               pass > 0 && nl <= GROW_MAX_N, [&](int it, int j) {
@@ -343,7 +349,7 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
       tm.start();
       SweepArgs r{cur, nullptr, Ca, K, K, W, 0, prop, nullptr, ctr};
       launch_iota(prop, nl, st);  // a row without entries proposes itself
-      launch_zero_u64(ctr, 4, st);
+      launch_zero_u64(ctr, CTR_WORDS, st);
       launch_sweep(r, sch, ALGO_REFINE, p->mode, p->k, p->chunk_len, st);
       launch_refine_accept(prop, nprop, from, Cb, nl, st);  // Cb <- refined R
       ms_ref += tm.stop();
@@ -647,11 +653,11 @@ int mgcd_move_sweep(const mgcd_csr *gin, const mgcd_params *p, int32_t algo, con
     uint32_t *K = a.take<uint32_t>(g.n);
     uint64_t W = prepare(g, p, K, a, st);
     uint32_t *Sig = a.take<uint32_t>(g.n);
-    unsigned long long *ctr = a.take<unsigned long long>(4);
+    unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
     launch_community_totals(C, K, Sig, g.n, st);
     Schedule sch;
     build_schedule(g, sched_params(p), sch, a, st);
-    launch_zero_u64(ctr, 4, st);
+    launch_zero_u64(ctr, CTR_WORDS, st);
     // rows without entries are in no sweep: they keep their community and gain 0
     if (g.n > 0) MGCD_HIP(hipMemcpyAsync(C_new, C, (size_t)g.n * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     if (gain) launch_zero_u64(reinterpret_cast<unsigned long long *>(gain), g.n, st);
@@ -681,10 +687,10 @@ int mgcd_refine(const mgcd_csr *gin, const mgcd_params *p, const int32_t *bound,
     uint32_t *K = a.take<uint32_t>(g.n);
     uint64_t W = prepare(g, p, K, a, st);
     int32_t *prop = a.take<int32_t>(g.n), *nprop = a.take<int32_t>(g.n), *from = a.take<int32_t>(g.n);
-    unsigned long long *ctr = a.take<unsigned long long>(4);
+    unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
     Schedule sch;
     build_schedule(g, sched_params(p), sch, a, st);
-    launch_zero_u64(ctr, 4, st);
+    launch_zero_u64(ctr, CTR_WORDS, st);
     launch_iota(prop, g.n, st);  // a row without entries proposes itself
     SweepArgs r{g, nullptr, bound, K, K, W, 0, prop, nullptr, ctr};
     launch_sweep(r, sch, ALGO_REFINE, p->mode, p->k, p->chunk_len, st);

@@ -13,15 +13,15 @@
 //           G = W (K_ic - K_id) - K_i (K_i + Sigma_c - Sigma_d) (Eq. 2 times W^2/2),
 //           c != d, G > 0, lowest c on ties; applied only in the sweep's direction.
 //
-// Mapping on CDNA: every chunk is one lane's stream with the sketch in VGPRs.  A
-// row of at most 64 chunks occupies 2^b adjacent lanes of one wave (b = 0 for a
-// row of one chunk; rows of one chunk ordered heavy-first so a wave's lanes have
-// similar trip counts); its chunk sketches are merged with cross-lane shuffles and
-// the same lanes run pass 2.  Rows of more than 64 chunks write chunk sketches to
-// scratch and one workgroup per row merges them in LDS and runs pass 2 with
-// block-strided (coalesced) reads.
+// Mapping on CDNA: every chunk is the stream of four lanes with the sketch's slots in
+// their VGPRs, 64 chunks per workgroup, the chunks' entries staged in LDS.  A row of at
+// most 64 chunks takes 2^b quads of a workgroup (b = 0 for a row of one chunk); its chunk
+// sketches are merged in LDS and the same lanes run pass 2 from LDS.  Rows of
+// more than 64 chunks write one merged sketch per 64 chunks to scratch, and one
+// workgroup per row merges those in LDS.
 #include "move.hpp"
 #include "primitives.hpp"
+#include "quad_sketch.hpp"
 #include "sketch.hpp"
 #include "staging.hpp"
 #include "wave_sketch.hpp"
@@ -57,6 +57,13 @@ __device__ inline bool frozen(const SweepArgs &a, int32_t i) {
 // Wave-uniform (written before the kernel started).
 __device__ inline bool level_over(const SweepArgs &a) { return a.live && *a.live == 0; }
 
+// A product of two values that fit 32 signed bits, exact in 64: one multiply-add, where a
+// 64-bit product takes several quarter-rate multiplies.  Every factor of the gain fits: W
+// and all weights and totals are below 2^31, so are differences of two of them, and
+// K_i + Sigma_c - Sigma_d lies within 31 bits of 0 since vertex i's own K_i is part of
+// Sigma_d (refinement: Sigma_d = K_i).
+__device__ inline int64_t mul32(int64_t x, int64_t y) { return (int64_t)(int32_t)x * (int32_t)y; }
+
 // Evaluate candidate c (present: it exists) with exact linking weight kc and
 // community total sc; keep the best.  Branch-free, so gathers feeding sc are issued
 // together rather than each inside a branch of its own.
@@ -69,7 +76,7 @@ __device__ inline void consider_v(int64_t W, int32_t d, int64_t Ki, int64_t Sd, 
     G = (int64_t)kc;
     ok = present;
   } else {
-    G = W * ((int64_t)kc - (int64_t)kd) - Ki * (Ki + (int64_t)sc - Sd);
+    G = mul32(W, (int64_t)kc - (int64_t)kd) - mul32(Ki, Ki + (int64_t)sc - Sd);
     ok = present && c != d && G > 0;
   }
   const bool better = ok && (best < 0 || G > bestG || (G == bestG && c < best));
@@ -94,7 +101,7 @@ __device__ inline void consider(const SweepArgs &a, int64_t W, int32_t d, int64_
 // could neither win nor tie: the result equals scoring every slot.  Returns the number
 // of candidates' totals read.
 template <int K, int ALGO>
-__device__ inline int consider_slots(const SweepArgs &a, int64_t W, int32_t d, int64_t Ki, int64_t Sd,
+__device__ MGCD_INLINE int consider_slots(const SweepArgs &a, int64_t W, int32_t d, int64_t Ki, int64_t Sd,
                                      uint32_t kd, const uint32_t (&key)[K], const uint32_t (&ex)[K],
                                      int32_t &best, int64_t &bestG) {
   if constexpr (ALGO == ALGO_LPA) {
@@ -113,12 +120,12 @@ __device__ inline int consider_slots(const SweepArgs &a, int64_t W, int32_t d, i
     }
     const uint32_t s0 = a.Sig[c0 != EMPTY ? (int32_t)c0 : d];
     consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)c0, x0, s0, c0 != EMPTY, best, bestG);
-    const int64_t rest = Sd - Ki;  // Sigma_d without i: U(c) = W (k_c - k_d) + K_i (Sigma_d - K_i)
+    const int64_t own = mul32(Ki, Sd - Ki);  // U(c) = W (k_c - k_d) + K_i (Sigma_d - K_i)
     bool live[K];
     uint32_t sc[K];
 #pragma unroll
     for (int p = 0; p < K; ++p) {
-      const int64_t U = W * ((int64_t)ex[p] - (int64_t)kd) + Ki * rest;
+      const int64_t U = mul32(W, (int64_t)ex[p] - (int64_t)kd) + own;
       const int32_t c = (int32_t)key[p];
       live[p] = key[p] != EMPTY && key[p] != ud && key[p] != c0 && U > 0 &&
                 (best < 0 || U > bestG || (U == bestG && c < best));
@@ -153,41 +160,97 @@ __device__ inline void finish(const SweepArgs &a, int32_t i, int32_t d, int32_t 
   if (a.gctr) ct.g = a.gid[i];  // batched: added to the graph's counters when flushed
 }
 
-// Batched runs (all lanes of the wave): the lanes' counts go to their graphs'
-// counters, one atomic per graph and counter for the whole wave (lanes grouped by
-// graph, each group summed across the wave), then the counts restart.
-__device__ inline void flush_graph_counters(const SweepArgs &a, Counters &ct) {
+// Batched runs: counts of one graph's rows, kept by a whole wave (wave-uniform) until
+// rows of another graph come or the wave ends.  Every atomic on a graph's counters
+// queues behind those of the other waves at work on that graph (with one flush per 16
+// rows, a sweep over 192 graphs spent more than half its time waiting there).
+struct GraphCounts {
+  int32_t g;  // -1: none
+  uint32_t moved, prop;
+  uint64_t sumG;
+};
+
+__device__ inline void commit_graph_counts(const SweepArgs &a, const GraphCounts &gc) {  // one lane
+  if (gc.g < 0) return;
+  unsigned long long *c = a.gctr + 3 * (int64_t)gc.g;
+  if (gc.moved) atomicAdd(&c[0], (unsigned long long)gc.moved);
+  if (gc.prop) atomicAdd(&c[1], (unsigned long long)gc.prop);
+  if (gc.sumG) atomicAdd(&c[2], (unsigned long long)gc.sumG);
+}
+
+// Adds the lanes' counts (of at most one row each) to gc, graph by graph; they restart.
+__device__ inline void gather_graph_counts(const SweepArgs &a, Counters &ct, GraphCounts &gc) {
   const int lane = lane_id();
   uint64_t todo = __ballot(ct.moved != 0 || ct.prop != 0);  // a gain comes with a proposal
   while (todo) {  // wave-uniform
-    const int leader = __builtin_ctzll(todo);
-    const int32_t g = __shfl(ct.g, leader);
+    const int32_t g = uniform(__shfl(ct.g, __builtin_ctzll(todo)));
     const bool mine = ((todo >> lane) & 1ull) != 0 && ct.g == g;
-    const unsigned long long m = wave_sum((unsigned long long)(mine ? ct.moved : 0u));
-    const unsigned long long p = wave_sum((unsigned long long)(mine ? ct.prop : 0u));
-    const unsigned long long sg = wave_sum((unsigned long long)(mine ? ct.sumG : 0ull));
-    if (lane == leader) {
-      unsigned long long *c = a.gctr + 3 * (int64_t)g;
-      if (m) atomicAdd(&c[0], m);
-      if (p) atomicAdd(&c[1], p);
-      if (sg) atomicAdd(&c[2], sg);
+    if (gc.g != g) {
+      if (lane == 0) commit_graph_counts(a, gc);
+      gc = GraphCounts{g, 0, 0, 0};
     }
+    gc.moved += __popcll(__ballot(mine && ct.moved != 0));
+    const uint32_t p = __popcll(__ballot(mine && ct.prop != 0));
+    gc.prop += p;
+    if (p) gc.sumG += wave_sum((unsigned long long)(mine ? ct.sumG : 0ull));
     todo &= ~__ballot(mine);
   }
   ct = Counters{};
 }
 
+// This workgroup's copy of the sweep's counters (the reader adds up the copies).
+__device__ inline unsigned long long *sweep_counters(const SweepArgs &a) {
+  return a.ctr + (int64_t)spread_copy() * CTR_STRIDE;
+}
+
 // One thread's counts of one row, to its graph's counters (batched) or the sweep's.
 __device__ inline void commit_counters(const SweepArgs &a, const Counters &ct) {
-  unsigned long long *c = a.gctr ? a.gctr + 3 * (int64_t)ct.g : a.ctr;
+  unsigned long long *c = a.gctr ? a.gctr + 3 * (int64_t)ct.g : sweep_counters(a);
   if (ct.moved) atomicAdd(&c[0], (unsigned long long)ct.moved);
   if (ct.prop) atomicAdd(&c[1], (unsigned long long)ct.prop);
   if (ct.sumG) atomicAdd(&c[2], (unsigned long long)ct.sumG);
 }
 
+// One wave's counts of at most one row per lane.
+__device__ inline void flush_wave_counters(const SweepArgs &a, Counters &ct) {
+  if (a.gctr) {
+    GraphCounts gc{-1, 0, 0, 0};
+    gather_graph_counts(a, ct, gc);
+    if (lane_id() == 0) commit_graph_counts(a, gc);
+    return;
+  }
+  const uint32_t m = __popcll(__ballot(ct.moved != 0)), p = __popcll(__ballot(ct.prop != 0));
+  const uint32_t cands = wave_sum(ct.cand);
+  const unsigned long long g = wave_sum((unsigned long long)ct.sumG);
+  const int l = lane_id();
+  const unsigned long long x = l == 0 ? m : l == 1 ? p : l == 2 ? g : cands;
+  if (l < 4 && x) atomicAdd(&sweep_counters(a)[l], x);
+}
+
+// A workgroup's counts of at most one row per lane.
 __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
-  if (a.gctr) {  // batched (kernel-uniform): per graph, per wave
-    flush_graph_counters(a, ct);
+  const int w = threadIdx.x / WAVE;
+  if (a.gctr) {  // batched (kernel-uniform): the waves' last graphs together
+    __shared__ GraphCounts last[BLOCK / WAVE];
+    GraphCounts gc{-1, 0, 0, 0};
+    gather_graph_counts(a, ct, gc);
+    if (lane_id() == 0) last[w] = gc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int q = 1; q < BLOCK / WAVE; ++q) {
+        const GraphCounts x = last[q];
+        if (x.g < 0) continue;
+        if (x.g != gc.g) {
+          commit_graph_counts(a, gc);
+          gc = x;
+        } else {
+          gc.moved += x.moved;
+          gc.prop += x.prop;
+          gc.sumG += x.sumG;
+        }
+      }
+      commit_graph_counts(a, gc);
+    }
     return;
   }
   __shared__ unsigned long long red[4][4];
@@ -195,7 +258,6 @@ __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
   unsigned long long p = wave_sum((unsigned long long)ct.prop);
   unsigned long long g = wave_sum((unsigned long long)ct.sumG);
   unsigned long long c = wave_sum((unsigned long long)ct.cand);
-  int w = threadIdx.x / WAVE;
   if (lane_id() == 0) {
     red[0][w] = m;
     red[1][w] = p;
@@ -206,7 +268,7 @@ __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
   if (threadIdx.x < 4) {
     unsigned long long s = red[threadIdx.x][0] + red[threadIdx.x][1] + red[threadIdx.x][2] +
                            red[threadIdx.x][3];
-    if (s) atomicAdd(&a.ctr[threadIdx.x], s);
+    if (s) atomicAdd(&sweep_counters(a)[threadIdx.x], s);
   }
 }
 
@@ -239,125 +301,6 @@ __device__ inline void neighbour_keys(const SweepArgs &a, const int32_t (&j)[U],
 
 // ---- MG: long rows -----------------------------------------------------------------
 
-// Stage positions s0 .. s0+WIN-1 of every lane's chunk [clo, chi) of row i into the
-// wave's LDS window (staging.hpp).  GATHER: the keys are C[j] (with Algorithm 1's
-// skips), gathered with the loads of 8 rounds in flight, and are also written to the
-// key stream; otherwise they are read from the key stream.  FUSED: each round reads its
-// labels in its own step and ignores a.ident (the persistent batched kernel, whose
-// graphs never start a sweep from the identity: measured 6 % faster there); otherwise
-// the label reads of a group sit behind one branch on a.ident (the single-graph kernel,
-// where this form also needs fewer registers: four waves per SIMD at k = 8 instead of
-// three).
-template <int ALGO, bool GATHER, bool FUSED = false>
-__device__ inline void stage_window(const SweepArgs &a, uint32_t *win, int32_t i, int32_t bi,
-                                    int64_t clo, int64_t chi, int64_t s0, uint32_t *keybuf) {
-  if constexpr (!GATHER) {
-    stage_pairs(win, clo, chi, s0, keybuf, a.g.w);
-    return;
-  }
-  constexpr int G = WIN < 8 ? WIN : 8;  // rounds per group of loads in flight
-  const int lane = lane_id();
-#pragma unroll
-  for (int g0 = 0; g0 < WIN; g0 += G) {
-    uint32_t kk[G], ww[G];
-    uint32_t ok = 0;
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const int src = (g0 + r) * SPR + lane / WIN;
-      const int64_t e = __shfl(clo, src) + s0 + lane % WIN;
-      const bool v = e < __shfl(chi, src);
-      ok |= v ? 1u << r : 0u;
-      const int64_t es = v ? e : 0;
-      kk[r] = (uint32_t)__builtin_nontemporal_load(a.g.idx + es);
-      ww[r] = __builtin_nontemporal_load(a.g.w + es);
-    }
-    if constexpr (FUSED) {
-#pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const int src = (g0 + r) * SPR + lane / WIN;
-        const int32_t ii = __shfl(i, src);
-        const int32_t bb = __shfl(bi, src);
-        const bool v = (ok >> r) & 1u;
-        const int32_t j = v ? (int32_t)kk[r] : 0;
-        uint32_t c;
-        if (ALGO == ALGO_REFINE)
-          c = a.bound[j] == bb ? (uint32_t)j : EMPTY;
-        else
-          c = (uint32_t)a.C[j];
-        // self-loops are skipped.  The gathered value is used on every lane (OR with
-        // an all-ones mask instead of a select), so the compiler keeps the gathers of
-        // all rounds in flight instead of sinking each into a branch of its own.
-        kk[r] = c | ((v && j != ii) ? 0u : EMPTY);
-      }
-    } else {
-      int32_t jj[G], bb[G];
-      uint32_t c[G];
-#pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const int src = (g0 + r) * SPR + lane / WIN;
-        jj[r] = ((ok >> r) & 1u) ? (int32_t)kk[r] : 0;
-        bb[r] = ALGO == ALGO_REFINE ? __shfl(bi, src) : 0;
-      }
-      neighbour_keys<ALGO, G>(a, jj, bb, c);
-#pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const int src = (g0 + r) * SPR + lane / WIN;
-        const int32_t ii = __shfl(i, src);
-        const bool v = (ok >> r) & 1u;
-        kk[r] = c[r] | ((v && jj[r] != ii) ? 0u : EMPTY);  // self-loops are skipped
-      }
-    }
-    {
-#pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const int src = (g0 + r) * SPR + lane / WIN;
-        const int64_t e = __shfl(clo, src) + s0 + lane % WIN;
-        if ((ok >> r) & 1u) keybuf[e] = kk[r];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const bool v = (ok >> r) & 1u;
-      put_pair(win, (g0 + r) * SPR + lane / WIN, v ? kk[r] : EMPTY, v ? ww[r] : 0u);
-    }
-  }
-}
-
-// Pass 1 of Algorithm 1 over this lane's chunk [clo, chi) of row i: windows staged
-// by stage_window, then every lane folds its own 16 staged entries into its VGPR
-// sketch.  Every lane of the wave must call this; an idle lane passes an empty
-// chunk.
-template <int K, int ALGO, int MODE, bool GATHER = true, bool FUSED = false>
-__device__ inline void staged_sketch(const SweepArgs &a, RegSketch<K, MODE> &s, uint32_t *win,
-                                     int32_t i, int32_t bi, int64_t clo, int64_t chi,
-                                     uint32_t *keybuf) {
-  int64_t maxlen = chi - clo;
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    int64_t x = __shfl_xor(maxlen, o);
-    maxlen = x > maxlen ? x : maxlen;
-  }
-  for (int64_t s0 = 0; s0 < maxlen; s0 += WIN) {
-    stage_window<ALGO, GATHER, FUSED>(a, win, i, bi, clo, chi, s0, keybuf);
-    wave_sync();
-    uint32_t kk[WIN], ww[WIN];
-    read_window(win, kk, ww);
-    wave_sync();
-#pragma unroll
-    for (int t = 0; t < WIN; ++t)
-      if (kk[t] != EMPTY) s.update(kk[t], ww[t]);
-  }
-}
-
-// Rows of more than 64 chunks ("long rows"): the main sweep kernel sketches their
-// chunks, one wave per aligned group of 64 chunks (long_group), and merges each
-// group with the first six levels of the fixed tree; then
-//   k_long_merge   one workgroup per row: the rest of the fixed merge tree over its
-//                  group roots; a row whose sketch lost no weight is decided here;
-//   k_long_count   one wave per chunk of a lossy row: pass 2 against the row's
-//                  candidates, partial counts per chunk;
-//   k_long_decide  one workgroup per lossy row: sum the partial counts, decide.
-
 // Chunk q of a long row: its row, its bounds and whether it is active.
 struct LongChunk {
   int32_t m, i;
@@ -378,53 +321,6 @@ __device__ inline LongChunk long_chunk(const SweepArgs &a, const int32_t *multi,
   c.hi = c.lo + L < rhi ? c.lo + L : rhi;
   c.active = true;
   return c;
-}
-
-// Wave w takes the aligned group of 64 chunks gstart[m] .. of its long row m (lane
-// = chunk within the group): Algorithm 1 over the staged entries (keys gathered
-// and written to the key stream), then the first six levels of the fixed merge
-// tree with cross-lane shuffles; lane 0 writes the group's root.
-template <int K, int ALGO, int MODE, bool FUSED = false>
-__device__ __attribute__((always_inline)) inline void long_group(const SweepArgs &a, const Buckets &bk, int64_t L,
-                                  uint32_t *keybuf, uint32_t *win, int64_t w) {
-  const int lane = lane_id();
-  const int32_t m = bk.gowner[w];
-  const int32_t i = bk.multi[m];
-  const int64_t nc = bk.cstart[m + 1] - bk.cstart[m];
-  const int64_t q = (w - bk.gstart[m]) * WAVE + lane;  // chunk index within the row
-  const bool active = q < nc && !frozen(a, i);
-  int64_t lo = 0, hi = 0;
-  if (active) {
-    const int64_t rhi = a.g.off[i + 1];
-    lo = a.g.off[i] + q * L;
-    hi = lo + L < rhi ? lo + L : rhi;
-  }
-  const int32_t bi = (ALGO == ALGO_REFINE && active) ? a.bound[i] : 0;
-  RegSketch<K, MODE> s;
-  s.reset();
-  staged_sketch<K, ALGO, MODE, true, FUSED>(a, s, win, i, bi, lo, hi, keybuf);
-  s.finalize();
-  bool lossy = s.lossy;
-#pragma unroll 1
-  for (int l = 0; l < 6; ++l) {
-    const int stride = 1 << l;
-    uint32_t bk_[K], bv_[K];
-#pragma unroll
-    for (int p = 0; p < K; ++p) {
-      bk_[p] = __shfl_down(s.key[p], stride);
-      bv_[p] = __shfl_down(s.val[p], stride);
-    }
-    const int64_t c_l = (nc + stride - 1) >> l;  // nodes at level l
-    const bool left = (lane & ((2 << l) - 1)) == 0;
-    if (left && (q >> l) + 1 < c_l) lossy |= merge_sketch<K>(s.key, s.val, bk_, bv_);
-  }
-  const bool any = __ballot(lossy) != 0;
-  if (lane == 0) {
-#pragma unroll
-    for (int p = 0; p < K; ++p)
-      bk.sk[w * K + p] = Pair{s.val[p] > 0 ? s.key[p] : EMPTY, s.val[p]};
-    bk.skflag[w] = any ? 1u : 0u;
-  }
 }
 
 // Choose the best candidate of row i and record the move (one thread).
@@ -579,166 +475,696 @@ __global__ void __launch_bounds__(BLOCK)
   decide_long<K, ALGO>(a, i, community_of_self<ALGO>(a, i), key, ex, kd);
 }
 
-// ---- MG: every row of at most 64 chunks, one launch ---------------------------------
+// ---- MG: 64 chunks per workgroup, four lanes per chunk ---------------------------------
 
-// Rows are grouped in buckets by P = 2^b lanes per row (P >= the row's chunk count;
-// b = 0 for rows of one chunk), 64/P rows per wave, heaviest bucket first in the
-// grid.  Lane q of a row owns chunk q.
-//   pass 1: staged_sketch over the lane's chunk (keys also go to the key stream);
-//   merge:  chunk sketches merged by the fixed tree with cross-lane shuffles (node
-//           j of level l lives in lane j*2^l, its right partner 2^l lanes up);
-//   pass 2: only rows whose sketch lost weight: the same LDS windows over the key
-//           stream (no second gather) and the weights, each lane counting its own
-//           chunk, then xor-shuffles inside the row's aligned segment;
-//   lane 0 of the segment decides.
-template <int K, int ALGO, int MODE, bool FUSED = false>
-__device__ __attribute__((always_inline)) inline void row_work(const SweepArgs &a, const Buckets &bk, int64_t L, uint32_t *keybuf,
-                                uint32_t *win, int64_t wave, Counters &ct) {
-  const int lane = lane_id();
-  // buckets are laid out in the grid from b = 6 down to b = 0 (wave-uniform)
-  int b = 6;
-  while (b > 0 && wave >= bk.wave_end[b]) --b;
-  const int logp = b;
-  const int P = 1 << logp;
-  const int q = lane & (P - 1);
-  const int base_lane = lane & ~(P - 1);
-  const int64_t r = (wave - bk.wave_begin[b]) * (WAVE >> logp) + (lane >> logp);
-  const bool listed = wave < bk.wave_end[0] && r < bk.nrows[b];
-  const int32_t i = listed ? bk.rows[b][r] : 0;
-  const bool valid = listed && !frozen(a, i);
-  if (listed && !valid && q == 0) a.Cnew[i] = community_of_self<ALGO>(a, i);
-  const int64_t lo = valid ? a.g.off[i] : 0, hi = valid ? a.g.off[i + 1] : 0;
-  const int64_t nc = (hi - lo + L - 1) / L;
-  const int32_t bi = (ALGO == ALGO_REFINE && valid) ? a.bound[i] : 0;
-  // this lane's chunk [clo, chi)
-  const int64_t clo = lo + q * L;
-  const int64_t chi = q < nc ? (clo + L < hi ? clo + L : hi) : clo;
-  RegSketch<K, MODE> s;
-  s.reset();
-  staged_sketch<K, ALGO, MODE, true, FUSED>(a, s, win, i, bi, clo, chi, keybuf);
-  s.finalize();
-  bool lossy = s.lossy;
-  for (int l = 0; l < logp; ++l) {
-    const int stride = 1 << l;
-    uint32_t bk_[K], bv_[K];
-#pragma unroll
-    for (int p = 0; p < K; ++p) {
-      bk_[p] = __shfl_down(s.key[p], stride);
-      bv_[p] = __shfl_down(s.val[p], stride);
+// A workgroup takes 64 chunks, each a quad of lanes (quad_sketch.hpp): an aligned group
+// of 64 chunks of a long row (more than 64 chunks), or 64 / P rows of a bucket of P = 2^b
+// chunks each (P >= the row's chunk count; b = 0 for rows of one chunk).  The chunks go
+// to the quads in order of length, so that a wave's 16 quads end together.
+//   stage   windows of CAP entries per chunk: each wave loads those of its 16 chunks with
+//           128-bit loads, gathers the keys C[j] (with Algorithm 1's skips) and keeps keys
+//           and weights in LDS; the next window's loads are in flight during the fold;
+//   fold    every quad runs Algorithm 1 over its chunk from LDS;
+//   merge   the fixed tree over the chunk sketches of a row, in LDS, a quad per merge;
+//   pass 2  only rows whose sketch lost weight: every lane counts a quarter of its
+//           chunk's entries against the row's candidates, from LDS where the chunk had
+//           one window, else from the key stream that staging wrote;
+//   decide  lane r of the first wave decides row r.
+// Rows of more than 64 chunks continue after the sweep kernel:
+//   k_long_merge   one workgroup per row: the rest of the fixed merge tree over its
+//                  group roots; a row whose sketch lost no weight is decided here;
+//   k_long_count   one wave per chunk of a lossy row: pass 2 against the row's
+//                  candidates, partial counts per chunk;
+//   k_long_decide  one workgroup per lossy row: sum the partial counts, decide.
+//
+// Why this split.  With one lane per chunk (all slots in its registers) a level-0 sweep of
+// R-MAT 2^20 (31.4 M entries, k = 8) took 473 us, waves waiting most of the time: 16 waves
+// per CU, rows read twice over (a row's 64-byte pieces came back after its lines had left
+// the L2: 1.7 GB for 0.6), and on small levels one wave's serial chain was the launch (80 to
+// 170 us for a few hundred rows at k = 16).  A quad per chunk takes 312 us there, 438 us
+// against 564 for a Chung-Lu graph of 27 M entries at k = 16, and a Leiden run's sweeps
+// on Chung-Lu 2^22 18.5 ms against 38.8.  It is bound by VALU issue (77 % in a first sweep,
+// which reads no labels, 108 M wave instructions on R-MAT 2^20) and, in the other sweeps,
+// by the label gathers (about 100 us of them there).  Sorting the chunks by length inside
+// the workgroup and merging in LDS takes a quarter of the instructions out.  Measured and
+// not taken: CAP = 128 with pass 2 from LDS alone (two workgroups per CU: 350 + 63 us, the
+// light rows in a second launch), and whole chunks in registers (27 KB of unrolled fold:
+// 348 + 75 us, k = 16 spills).
+constexpr int WCH = 64;  // chunks per workgroup
+constexpr int CAP = 32;  // staged entries per chunk: six workgroups per CU (five at K = 16)
+
+template <int K>
+struct RowShare {
+  // rows of CAP + 4 words: the 16 quads of a wave read 128 bits each from distinct banks
+  __attribute__((aligned(16))) uint32_t key[WCH][CAP + 4];  // by quad: its chunk's staged
+  __attribute__((aligned(16))) uint32_t wt[WCH][CAP + 4];   // keys and weights
+  uint32_t sk[WCH][K + 1], sv[WCH][K + 1];   // by chunk: candidates and weights; [K]: K_{i->d}
+  int64_t lo[WCH], hi[WCH];                  // by quad: its chunk's entries,
+  int32_t row[WCH], bnd[WCH], chunk[WCH];    // its row, the row's bound, the chunk
+  int32_t nch[WCH], lead[WCH];               // by chunk: chunks of its row here, the row if
+                                             // this is its first chunk, else -1; of the row:
+  uint32_t own[WCH], ki[WCH], sd[WCH];       // its community, K_i, Sigma of its community,
+  uint32_t need[WCH], lossy[WCH];            // needs pass 2, lost weight
+  uint32_t any;                              // some row needs pass 2
+  int64_t item;                              // persistent: next work item
+};
+
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Entries e .. e + 3 of p (nnz entries; 0 past the end); nothing when off.
+__device__ inline v4u load4(const uint32_t *p, int64_t e, int64_t nnz, bool on) {
+  typedef uint32_t v4a __attribute__((ext_vector_type(4), aligned(4)));
+  v4u x = {0u, 0u, 0u, 0u};
+  if (on) {
+    if (e + 4 <= nnz) {
+      x = *reinterpret_cast<const v4a *>(p + e);
+    } else {
+      x.x = p[e];
+      x.y = e + 1 < nnz ? p[e + 1] : 0u;
+      x.z = e + 2 < nnz ? p[e + 2] : 0u;
     }
-    const int64_t c_l = (nc + stride - 1) >> l;  // nodes at level l
-    const bool left = (q & ((2 << l) - 1)) == 0;
-    if (left && (int64_t)(q >> l) + 1 < c_l) lossy |= merge_sketch<K>(s.key, s.val, bk_, bv_);
   }
-  uint32_t key[K], ex[K];
+  return x;
+}
+
+// A window: positions s0 .. s0 + CAP - 1 of this wave's 16 chunks, LPC lanes (four
+// entries each) per chunk, CPR chunks per round of loads.
+constexpr int LPC = CAP / 4, CPR = WAVE / LPC, ROUNDS = WCH / 4 / CPR;
+
+template <int K>
+__device__ MGCD_INLINE void load_window(const SweepArgs &a, const RowShare<K> &S, int64_t s0, v4u (&jj)[ROUNDS],
+                                        v4u (&ww)[ROUNDS]) {
+  const int lane = lane_id(), c0 = (threadIdx.x / WAVE) * (WCH / 4) + lane / LPC;
 #pragma unroll
-  for (int p = 0; p < K; ++p) {
-    uint32_t kk = __shfl(s.key[p], base_lane);
-    uint32_t vv = __shfl(s.val[p], base_lane);
-    key[p] = vv > 0 ? kk : EMPTY;
-    ex[p] = vv;
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int64_t e = S.lo[c0 + r * CPR] + s0 + 4 * (lane % LPC);
+    const bool on = e < S.hi[c0 + r * CPR];
+    jj[r] = load4(reinterpret_cast<const uint32_t *>(a.g.idx), e, a.g.nnz, on);
+    ww[r] = load4(a.g.w, e, a.g.nnz, on);
   }
-  const uint64_t lm = __ballot(lossy);
-  const uint64_t seg = P == 64 ? lm : (lm >> base_lane) & ((1ull << P) - 1);
-  const int32_t d = valid ? community_of_self<ALGO>(a, i) : 0;
-  uint32_t kd = 0;
-  const bool need2 = seg != 0 && second_pass(a, ALGO);  // same for all lanes of a row
-  if (!need2) {
+}
+
+// The loaded window into LDS: the key C[j] (refinement: j inside the row's bound) and the
+// weight, (EMPTY, 0) for skipped entries and past a chunk's end.  keyout: the keys also
+// go to the key stream.
+template <int K, int ALGO>
+__device__ MGCD_INLINE void stage_window(const SweepArgs &a, RowShare<K> &S, int64_t s0, v4u (&jj)[ROUNDS],
+                                         const v4u (&ww)[ROUNDS], uint32_t *keyout) {
+  const int lane = lane_id(), l = lane % LPC, c0 = (threadIdx.x / WAVE) * (WCH / 4) + lane / LPC;
+  // Every gather is issued on every lane with a valid index (0 where there is no entry)
+  // and masked with an OR afterwards, so that all of them are in flight together.
+  v4u kk[ROUNDS];
+  int left[ROUNDS];  // entries of the chunk from this lane's first on, at most 4 matter
 #pragma unroll
-    for (int p = 0; p < K; ++p) kd += key[p] == (uint32_t)d ? ex[p] : 0u;
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int64_t n = S.hi[c0 + r * CPR] - (S.lo[c0 + r * CPR] + s0 + 4 * l);
+    left[r] = n > 4 ? 4 : (int)n;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) jj[r][u] = u < left[r] ? jj[r][u] : 0u;
+  }
+  if (ALGO == ALGO_REFINE) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kk[r][u] = (uint32_t)a.bound[(int32_t)jj[r][u]];
+  } else if (!a.ident) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kk[r][u] = (uint32_t)a.C[(int32_t)jj[r][u]];
   } else {
 #pragma unroll
-    for (int p = 0; p < K; ++p) ex[p] = 0;
+    for (int r = 0; r < ROUNDS; ++r) kk[r] = jj[r];
   }
-  // pass 2 over the stashed keys (no second gather), staged like pass 1; rows whose
-  // sketch was exact take no part
-  const int64_t chi2 = need2 ? chi : clo;
-  int64_t maxlen2 = chi2 - clo;
 #pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    int64_t x = __shfl_xor(maxlen2, o);
-    maxlen2 = x > maxlen2 ? x : maxlen2;
-  }
-  for (int64_t s0 = 0; s0 < maxlen2; s0 += WIN) {
-    stage_window<ALGO, false>(a, win, i, bi, clo, chi2, s0, keybuf);
-    wave_sync();
-    uint32_t kk[WIN], ww[WIN];
-    read_window(win, kk, ww);
-    wave_sync();
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int c = c0 + r * CPR;
+    const uint32_t i = (uint32_t)S.row[c], b = (uint32_t)S.bnd[c];
+    v4u k, w;
 #pragma unroll
-    for (int t = 0; t < WIN; ++t) {
-      const uint32_t c = kk[t], w = ww[t];
-#pragma unroll
-      for (int p = 0; p < K; ++p) ex[p] += key[p] == c ? w : 0u;
-      kd += c == (uint32_t)d ? w : 0u;
+    for (int u = 0; u < 4; ++u) {
+      const bool skip = u >= left[r] || jj[r][u] == i || (ALGO == ALGO_REFINE && kk[r][u] != b);
+      k[u] = (ALGO == ALGO_REFINE ? jj[r][u] : kk[r][u]) | (skip ? EMPTY : 0u);
+      w[u] = skip ? 0u : ww[r][u];
     }
-  }
-  if (maxlen2 > 0) {
-    for (int o = P / 2; o > 0; o >>= 1) {
+    *reinterpret_cast<v4u *>(&S.key[c][4 * l]) = k;
+    *reinterpret_cast<v4u *>(&S.wt[c][4 * l]) = w;
+    if (keyout && left[r] > 0) {
+      typedef uint32_t v4a __attribute__((ext_vector_type(4), aligned(4)));
+      uint32_t *o = keyout + S.lo[c] + s0 + 4 * l;
+      if (left[r] == 4) {
+        *reinterpret_cast<v4a *>(o) = k;
+      } else {
 #pragma unroll
-      for (int p = 0; p < K; ++p) {
-        const uint32_t x = __shfl_xor(ex[p], o);
-        ex[p] += need2 ? x : 0u;
+        for (int u = 0; u < 3; ++u)
+          if (u < left[r]) o[u] = k[u];
       }
-      const uint32_t x = __shfl_xor(kd, o);
-      kd += need2 ? x : 0u;
     }
   }
-  if (valid && q == 0) {
+}
+
+// The longest chunk of this wave's 16 (this lane's quad has len entries).
+__device__ inline int64_t wave_max_chunk(int64_t len) {
+#pragma unroll
+  for (int o = QUAD; o < WAVE; o <<= 1) {
+    const int64_t x = __shfl_xor(len, o);
+    len = x > len ? x : len;
+  }
+  return uniform(len);
+}
+
+// Work item w: the first bk.ngroups are the groups of long rows, then the buckets' rows
+// from b = 6 down to b = 0.  Block-uniform.  ct: the counts of the row decided by this
+// thread (first wave).
+template <int K, int ALGO, int MODE>
+__device__ MGCD_INLINE void row_item(const SweepArgs &a, const Buckets &bk, int64_t L, uint32_t *keybuf,
+                                RowShare<K> &S, int64_t w, Counters &ct) {
+  constexpr int SL = QuadSketch<K, MODE>::S;
+  const int t = threadIdx.x;
+  const int c = t / QUAD, ql = t % QUAD;  // this lane's quad and its place there
+  const bool group = w < bk.ngroups;
+  int logp = 0;
+  int64_t wb = w;
+  if (group) {
+    logp = 6;
+  } else {
+    wb = w - bk.ngroups;
+    logp = 6;
+    while (logp > 0 && wb >= bk.item_end[logp]) --logp;
+    wb -= bk.item_begin[logp];
+  }
+  const int P = 1 << logp;
+  // the first wave describes the 64 chunks and reads early what the rows' decisions need
+  if (t < WCH) {
+    int64_t lo = 0, hi = 0, nc = 0;
+    int32_t i = 0, d = 0, b = 0;
+    uint32_t Ki = 0, Sd = 0;
+    bool lead = false;
+    if (group) {
+      const int32_t m = bk.gowner[w];
+      const int64_t base = (w - bk.gstart[m]) * WCH;  // the group's first chunk in the row
+      i = bk.multi[m];
+      if (!frozen(a, i)) {
+        nc = bk.cstart[m + 1] - bk.cstart[m] - base;
+        nc = nc < WCH ? nc : WCH;
+        const int64_t rhi = a.g.off[i + 1];
+        lo = a.g.off[i] + (base + t) * L;
+        hi = t < nc ? (lo + L < rhi ? lo + L : rhi) : lo;
+        if (ALGO == ALGO_REFINE) b = a.bound[i];
+      }
+    } else {
+      const int q = t & (P - 1);
+      const int64_t r = wb * (WCH >> logp) + (t >> logp);
+      const bool listed = r < bk.nrows[logp];
+      i = listed ? bk.rows[logp][r] : 0;
+      if (listed) {
+        if (frozen(a, i)) {
+          if (q == 0) a.Cnew[i] = community_of_self<ALGO>(a, i);
+        } else {
+          const int64_t rlo = a.g.off[i], rhi = a.g.off[i + 1];
+          nc = (rhi - rlo + L - 1) / L;
+          lo = rlo + q * L;
+          hi = q < nc ? (lo + L < rhi ? lo + L : rhi) : lo;
+          if (ALGO == ALGO_REFINE) b = a.bound[i];
+          d = community_of_self<ALGO>(a, i);
+          lead = q == 0;
+          if (lead && ALGO != ALGO_LPA) {
+            Ki = a.K[i];
+            Sd = a.Sig[d];
+          }
+        }
+      }
+    }
+    // longest chunks to the first quads, to within an eighth of 32, 64 or 128 entries
+    const int n = hi - lo > 128 ? 128 : (int)(hi - lo);
+    const int sh = __ballot(n > 64) ? 4 : __ballot(n > 32) ? 3 : 2;
+    const int bin = (n + (1 << sh) - 1) >> sh;
+    int slot = 0, base = 0;
+#pragma unroll
+    for (int v = 8; v >= 0; --v) {
+      const uint64_t m = __ballot(bin == v);
+      slot = bin == v ? base + (int)__popcll(m & lanemask_lt()) : slot;
+      base += (int)__popcll(m);
+    }
+    S.lo[slot] = lo;
+    S.hi[slot] = hi;
+    S.row[slot] = i;
+    S.bnd[slot] = b;
+    S.chunk[slot] = t;
+    S.nch[t] = (int32_t)nc;
+    S.lead[t] = lead ? i : -1;
+    S.ki[t] = Ki;
+    S.sd[t] = Sd;
+    S.own[t] = (uint32_t)d;
+    S.need[t] = 0;
+    S.lossy[t] = 0;
+    if (t == 0) S.any = 0;
+  }
+  __syncthreads();
+  const int64_t clo = S.lo[c], chi = S.hi[c], len = chi - clo;
+  const int ch = S.chunk[c];
+  const int64_t maxlen = wave_max_chunk(len);
+  QuadSketch<K, MODE> s;
+  s.reset();
+  const bool windows = maxlen > CAP;  // wave-uniform: pass 2 reads the key stream
+  uint32_t *const keyout = group || windows ? keybuf : nullptr;
+  v4u jj[ROUNDS], ww[ROUNDS];
+  load_window(a, S, 0, jj, ww);
+  for (int64_t s0 = 0; s0 < maxlen; s0 += CAP) {
+    stage_window<K, ALGO>(a, S, s0, jj, ww, keyout);
+    wave_sync();
+    if (s0 + CAP < maxlen) load_window(a, S, s0 + CAP, jj, ww);  // in flight during the fold
+    const int n = (int)(maxlen - s0 < CAP ? maxlen - s0 : CAP);
+#pragma unroll 2
+    for (int e = 0; e < n; e += 4) {
+      const v4u k = *reinterpret_cast<const v4u *>(&S.key[c][e]);
+      const v4u x = *reinterpret_cast<const v4u *>(&S.wt[c][e]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s.update(k[u], x[u]);
+    }
+    wave_sync();
+  }
+  s.finalize();
+  const bool merged = logp > 0;  // block-uniform
+  const bool lost = quad_or(s.lost) != 0;
+  bool need = lost && second_pass(a, ALGO);
+  if (merged) {
+    if (lost) S.lossy[ch & ~(P - 1)] = 1;
+  } else if (need && ql == 0) {
+    S.need[ch] = 1;
+  }
+  if (merged || !need) {
+#pragma unroll
+    for (int p = 0; p < SL; ++p) {
+      if (p * QUAD + ql < K) {
+        S.sk[ch][p * QUAD + ql] = s.key[p];
+        S.sv[ch][p * QUAD + ql] = s.val[p];
+      }
+    }
+  }
+  if (merged) {
+    __syncthreads();
+    // level l: node x (a multiple of 2^(l+1) chunks) takes in node x + 2^l if the row has
+    // it, a quad per merge: the first two waves for level 0, the first for the others
+#pragma unroll 1
+    for (int l = 0; l < logp; ++l) {
+      if (t < WAVE * (l == 0 ? 2 : 1)) {
+        const int x = c << (l + 1);
+        if (x < WCH && ((x & (P - 1)) >> l) + 1 < ((S.nch[x] + (1 << l) - 1) >> l)) {
+          const int y = x + (1 << l);
+          uint32_t bk_[SL], bv_[SL];
+#pragma unroll
+          for (int p = 0; p < SL; ++p) {
+            const bool h = p * QUAD + ql < K;
+            s.key[p] = h ? S.sk[x][p * QUAD + ql] : EMPTY;
+            s.val[p] = h ? S.sv[x][p * QUAD + ql] : 0u;
+            bk_[p] = h ? S.sk[y][p * QUAD + ql] : EMPTY;
+            bv_[p] = h ? S.sv[y][p * QUAD + ql] : 0u;
+          }
+          s.lost = 0;
+          s.merge(bk_, bv_);
+#pragma unroll
+          for (int p = 0; p < SL; ++p) {
+            if (p * QUAD + ql < K) {
+              S.sk[x][p * QUAD + ql] = s.key[p];
+              S.sv[x][p * QUAD + ql] = s.val[p];
+            }
+          }
+          if (s.lost) S.lossy[x & ~(P - 1)] = 1;
+        }
+        wave_sync();
+      }
+      if (l == 0) __syncthreads();
+    }
+    if (group) {
+      if (t < K) bk.sk[w * K + t] = Pair{S.sk[0][t], S.sv[0][t]};
+      if (t == 0) bk.skflag[w] = S.lossy[0];
+      return;
+    }
+    if (t < WCH && S.lead[t] >= 0 && S.lossy[t] && second_pass(a, ALGO)) {
+      S.need[t] = 1;
+      S.any = 1;
+#pragma unroll
+      for (int p = 0; p <= K; ++p) S.sv[t][p] = 0;  // pass 2 counts here
+    }
+    __syncthreads();
+  }
+  if (!merged || S.any) {
+    const int lc = ch & ~(P - 1);  // the row's first chunk
+    if (merged) need = S.need[lc] != 0;
+    const int64_t maxlen2 = wave_max_chunk(need ? len : 0);
+    if (maxlen2 > 0) {
+      uint32_t ck[K], cx[K], kd = 0;
+      const uint32_t dk = S.own[lc];
+      if (merged) {
+#pragma unroll
+        for (int p = 0; p < K; ++p) ck[p] = S.sk[lc][p];
+      } else {  // the quad's own slots
+#pragma unroll
+        for (int p = 0; p < K; ++p) {
+          const uint32_t x = s.key[p / QUAD];
+          ck[p] = p % QUAD == 0 ? quad_bcast<0>(x) : p % QUAD == 1 ? quad_bcast<1>(x)
+                  : p % QUAD == 2 ? quad_bcast<2>(x) : quad_bcast<3>(x);
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < K; ++p) cx[p] = 0;
+      if (windows) __threadfence_block();  // the wave's key stream entries are written
+      for (int64_t e = QUAD * ql; e < maxlen2; e += QUAD * QUAD) {
+        v4u k, x;
+        if (!windows) {
+          k = *reinterpret_cast<const v4u *>(&S.key[c][e]);
+          x = *reinterpret_cast<const v4u *>(&S.wt[c][e]);
+        } else {
+          const bool on = need && e < len;
+          k = load4(keybuf, clo + e, a.g.nnz, on);
+          x = load4(a.g.w, clo + e, a.g.nnz, on);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] = on && e + u < len && k[u] != EMPTY ? x[u] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+          for (int p = 0; p < K; ++p) cx[p] += ck[p] == k[u] ? x[u] : 0u;
+          kd += k[u] == dk ? x[u] : 0u;
+        }
+      }
+      kd = quad_sum(kd);
+#pragma unroll
+      for (int p = 0; p < K; ++p) cx[p] = quad_sum(cx[p]);
+      if (need && merged) {
+#pragma unroll
+        for (int p = 0; p < K; ++p)
+          if (ql == p % QUAD && cx[p]) atomicAdd(&S.sv[lc][p], cx[p]);
+        if (ql == 0 && kd) atomicAdd(&S.sv[lc][K], kd);
+      } else if (need) {
+#pragma unroll
+        for (int p = 0; p < K; ++p) {
+          if (ql == p % QUAD) {
+            S.sk[ch][p] = ck[p];
+            S.sv[ch][p] = cx[p];
+          }
+        }
+        if (ql == 0) S.sv[ch][K] = kd;
+      }
+    }
+    __syncthreads();
+  }
+  if (t < WCH && S.lead[t] >= 0) {
+    const int32_t i = S.lead[t], d = (int32_t)S.own[t];
+    uint32_t key[K], ex[K];
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      key[p] = S.sk[t][p];
+      ex[p] = S.sv[t][p];
+    }
+    uint32_t kd = 0;
+    if (S.need[t]) {
+      kd = S.sv[t][K];
+    } else {
+#pragma unroll
+      for (int p = 0; p < K; ++p) kd += key[p] == (uint32_t)d ? ex[p] : 0u;
+    }
     int32_t best = -1;
     int64_t bestG = 0;
     const int64_t W = ALGO == ALGO_LPA ? 0 : (int64_t)weight_of(a, i);
-    const int64_t Ki = ALGO == ALGO_LPA ? 0 : (int64_t)a.K[i];
-    const int64_t Sd = ALGO == ALGO_LPA ? 0 : (int64_t)a.Sig[d];
-    ct.cand += consider_slots<K, ALGO>(a, W, d, Ki, Sd, kd, key, ex, best, bestG);
+    ct.cand += consider_slots<K, ALGO>(a, W, d, S.ki[t], S.sd[t], kd, key, ex, best, bestG);
     finish<ALGO>(a, i, d, best, bestG, ct);
   }
 }
 
-// The main sweep kernel: the first bk.ngroups waves sketch the groups of 64 chunks
-// of long rows (their merge, pass 2 and decision follow in k_long_*), the rest
-// take the row buckets.
-template <int K, int ALGO, int MODE, bool PERSIST>
-__global__ void __launch_bounds__(BLOCK) MGCD_ROWS_OCCUPANCY(K)
-    k_move_rows(SweepArgs a, const Buckets bk, int64_t L, uint32_t *keybuf) {
-  __shared__ __attribute__((aligned(16))) uint32_t swin[BLOCK / WAVE][WAVE * WROW];
-  uint32_t *const win = swin[threadIdx.x / WAVE];
-  if constexpr (!PERSIST) {
-    const int64_t wave = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
-    Counters ct;
-    if (wave < bk.ngroups)
-      long_group<K, ALGO, MODE>(a, bk, L, keybuf, win, wave);
-    else
-      row_work<K, ALGO, MODE>(a, bk, L, keybuf, win, wave - bk.ngroups, ct);
-    flush_counters(a, ct);
+// ---- MG: light rows, a quad of lanes per row ---------------------------------------------
+
+// Rows of one chunk with at most LIGHT_MAX entries, 16 per wave and nothing shared between
+// waves: a lane loads a quarter of its row with 128-bit loads and keeps keys and weights
+// in registers; every entry is broadcast to the quad by DPP moves for Algorithm 1 and, if
+// the sketch lost weight, again for pass 2, in which each lane counts its own slots; the
+// decision, too, is spread over the quad's slots.  No LDS and 47 VGPRs at k = 8: eight
+// waves per SIMD.  192 planted graphs (2.5 M rows of about 16 entries) in one batch: 381 us
+// per sweep, 728 us with a lane per row, 418 us in the workgroup form above; LPA on one
+// planted graph of 10,000 vertices (one wave's latency): 6.5 us per sweep, 15.8 before.
+// Bound by VALU issue (72 % on R-MAT 2^20's light rows), then latency.
+constexpr int LIGHT_R = LIGHT_MAX / 16;  // 128-bit loads per lane
+
+// The best of a quad's candidates (this lane's slots key, ex): the rule of consider_slots.
+// Every lane of the quad returns the best; the result is the number of this lane's
+// candidates whose totals were read.
+template <int K, int ALGO, int S>
+__device__ MGCD_INLINE int consider_quad(const SweepArgs &a, int64_t W, int32_t d, int64_t Ki, int64_t Sd,
+                                         uint32_t kd, const uint32_t (&key)[S], const uint32_t (&ex)[S],
+                                         int32_t &best, int64_t &bestG) {
+  const uint32_t ud = (uint32_t)d;
+  int reads = 0;
+  if constexpr (ALGO == ALGO_LPA) {
+#pragma unroll
+    for (int p = 0; p < S; ++p)
+      consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)key[p], ex[p], 0u, key[p] != EMPTY, best, bestG);
   } else {
-    // persistent (batched runs): every wave takes work items from its counter of the
-    // queue (the items of the grid's order -- long-row groups, then the row buckets
-    // heaviest first -- whose index is c mod QLANES), QGRAB at a time, until none is
-    // left; nothing at all once every graph has stopped
+    // the heaviest candidate other than d (ties: the lowest slot) is scored first
+    uint32_t x0 = 0;
+#pragma unroll
+    for (int p = 0; p < S; ++p) x0 = key[p] != EMPTY && key[p] != ud ? umax(x0, ex[p]) : x0;
+    x0 = quad_max(x0);
+    uint32_t f = 255;
+#pragma unroll
+    for (int p = S - 1; p >= 0; --p)
+      f = key[p] != EMPTY && key[p] != ud && ex[p] == x0 ? (uint32_t)(p * QUAD + lane_id() % QUAD) : f;
+    const uint32_t f0 = quad_min(f);
+    const bool mine = f == f0 && f0 != 255;
+    uint32_t c0 = 0;
+#pragma unroll
+    for (int p = 0; p < S; ++p) c0 = f == (uint32_t)(p * QUAD + lane_id() % QUAD) ? key[p] : c0;
+    c0 = quad_or(mine ? c0 : 0u);  // one lane has it
+    const bool any = f0 != 255;
+    const uint32_t s0 = a.Sig[any ? (int32_t)c0 : d];
+    consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)c0, x0, s0, any, best, bestG);
+    reads = mine;
+    const int64_t own = mul32(Ki, Sd - Ki);  // U(c) = W (k_c - k_d) + K_i (Sigma_d - K_i)
+    bool live[S];
+    uint32_t sc[S];
+#pragma unroll
+    for (int p = 0; p < S; ++p) {
+      const int64_t U = mul32(W, (int64_t)ex[p] - (int64_t)kd) + own;
+      const int32_t c = (int32_t)key[p];
+      live[p] = key[p] != EMPTY && key[p] != ud && !(any && key[p] == c0) && U > 0 &&
+                (best < 0 || U > bestG || (U == bestG && c < best));
+      sc[p] = a.Sig[live[p] ? c : d];
+    }
+#pragma unroll
+    for (int p = 0; p < S; ++p) {
+      consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)key[p], ex[p], sc[p], live[p], best, bestG);
+      reads += live[p];
+    }
+  }
+  // the quad's best: larger gain first, then the lower id
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    uint32_t lo = (uint32_t)bestG, hi = (uint32_t)((uint64_t)bestG >> 32), c = (uint32_t)best;
+    lo = o ? quad_perm<QP_XOR2>(lo) : quad_perm<QP_XOR1>(lo);
+    hi = o ? quad_perm<QP_XOR2>(hi) : quad_perm<QP_XOR1>(hi);
+    const int32_t c2 = (int32_t)(o ? quad_perm<QP_XOR2>(c) : quad_perm<QP_XOR1>(c));
+    const int64_t g2 = (int64_t)(((uint64_t)hi << 32) | lo);
+    const bool take = c2 >= 0 && (best < 0 || g2 > bestG || (g2 == bestG && c2 < best));
+    best = take ? c2 : best;
+    bestG = take ? g2 : bestG;
+  }
+  return reads;
+}
+
+// Positions 16 r .. n - 1 (n wave-uniform) of the quads' rows, each broadcast in order.
+template <int R, int r = 0, typename F>
+__device__ MGCD_INLINE void each_entry(int n, const uint32_t (&kk)[R][4], const uint32_t (&ww)[R][4], F &&f) {
+  if constexpr (r < R) {
+    if (16 * r >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(quad_bcast<0>(kk[r][u]), quad_bcast<0>(ww[r][u]));
+    if (16 * r + 4 >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(quad_bcast<1>(kk[r][u]), quad_bcast<1>(ww[r][u]));
+    if (16 * r + 8 >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(quad_bcast<2>(kk[r][u]), quad_bcast<2>(ww[r][u]));
+    if (16 * r + 12 >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(quad_bcast<3>(kk[r][u]), quad_bcast<3>(ww[r][u]));
+    each_entry<R, r + 1>(n, kk, ww, f);
+  }
+}
+
+// Work item w: rows 16 w .. 16 w + 15 of the list, one wave.
+template <int K, int ALGO, int MODE>
+__device__ MGCD_INLINE void light_item(const SweepArgs &a, const int32_t *rows, int64_t nrows, int64_t w,
+                                       Counters &ct) {
+  constexpr int R = LIGHT_R, SL = QuadSketch<K, MODE>::S;
+  const int lane = lane_id(), ql = lane % QUAD;
+  const int64_t r = w * (WAVE / QUAD) + lane / QUAD;
+  const bool listed = r < nrows;
+  const int32_t i = listed ? rows[r] : 0;
+  // what the row needs is read before it is known whether its graph still moves
+  const int64_t rlo = a.g.off[i], rhi = a.g.off[i + 1];
+  const int32_t d = community_of_self<ALGO>(a, i);
+  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
+  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+  const int32_t g = a.gid ? a.gid[i] : 0;
+  const uint32_t Sd = ALGO == ALGO_LPA ? 0u : a.Sig[d];
+  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[g] : (int64_t)a.W;
+  const bool valid = listed && !(a.halt && *a.halt) && !(a.gid && !a.active[g]);
+  if (listed && !valid && ql == 0) a.Cnew[i] = d;
+  const int64_t lo = valid ? rlo : 0, hi = valid ? rhi : 0;
+  // this lane's entries lo + 16 x + 4 ql + u
+  uint32_t kk[R][4], ww[R][4];
+  const int left = (int)(hi - lo) - 4 * ql;
+  const int64_t e = lo + 4 * ql;
+#pragma unroll
+  for (int x = 0; x < R; ++x) {
+    const v4u j = load4(reinterpret_cast<const uint32_t *>(a.g.idx), e + 16 * x, a.g.nnz, 16 * x < left);
+    const v4u y = load4(a.g.w, e + 16 * x, a.g.nnz, 16 * x < left);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      kk[x][u] = 16 * x + u < left ? j[u] : 0u;  // a valid id: the gathers need no branch
+      ww[x][u] = 16 * x + u < left && j[u] != (uint32_t)i ? y[u] : 0u;
+    }
+  }
+  if (ALGO == ALGO_REFINE) {
+    uint32_t bb[R][4];
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) bb[x][u] = (uint32_t)a.bound[(int32_t)kk[x][u]];
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ww[x][u] = bb[x][u] == (uint32_t)b ? ww[x][u] : 0u;
+  } else if (!a.ident) {
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kk[x][u] = (uint32_t)a.C[(int32_t)kk[x][u]];
+  }
+  // real entries have weights above 0
+#pragma unroll
+  for (int x = 0; x < R; ++x)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) kk[x][u] = ww[x][u] ? kk[x][u] : EMPTY;
+  const int n = (int)wave_max_chunk(hi - lo);
+  QuadSketch<K, MODE> s;
+  s.reset();
+  each_entry<R>(n, kk, ww, [&](uint32_t c, uint32_t x) MGCD_LAMBDA { s.update(c, x); });
+  s.finalize();
+  const bool need = quad_or(s.lost) != 0 && second_pass(a, ALGO);
+  uint32_t kd = 0;
+  if (__ballot(need)) {
+    uint32_t cx[SL];
+#pragma unroll
+    for (int p = 0; p < SL; ++p) cx[p] = 0;
+    each_entry<R>(n, kk, ww, [&](uint32_t c, uint32_t x) MGCD_LAMBDA {
+#pragma unroll
+      for (int p = 0; p < SL; ++p) cx[p] += s.key[p] == c ? x : 0u;
+    });
+#pragma unroll
+    for (int p = 0; p < SL; ++p) s.val[p] = need ? cx[p] : s.val[p];
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kd += kk[x][u] == (uint32_t)d ? ww[x][u] : 0u;
+  }
+  if (!need) {
+    kd = 0;
+#pragma unroll
+    for (int p = 0; p < SL; ++p) kd += s.key[p] == (uint32_t)d ? s.val[p] : 0u;
+  }
+  kd = quad_sum(kd);
+  if (valid) {
+    int32_t best = -1;
+    int64_t bestG = 0;
+    const int reads = consider_quad<K, ALGO, SL>(a, W, d, Ki, Sd, kd, s.key, s.val, best, bestG);
+    ct.cand += reads;
+    if (ql == 0) finish<ALGO>(a, i, d, best, bestG, ct);
+  }
+}
+
+template <int K>
+constexpr int row_waves_per_simd() {  // = workgroups per CU: what LDS leaves room for
+  return K >= 16 ? 5 : 6;
+}
+template <int K>
+constexpr int light_waves_per_simd() {  // what registers leave room for
+  return K >= 16 ? 6 : 8;
+}
+
+// The main sweep kernel: a workgroup per work item of the long and ordinary rows, then
+// workgroups for the light rows, which fill the chip while the last heavy ones end.
+// PERSIST (batched runs; no light rows): as many workgroups as stay resident take work
+// items from their counter of the queue (the items of the grid's order whose index is
+// c mod QLANES), QGRAB at a time, until none is left.
+template <int K, int ALGO, int MODE, bool PERSIST>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_waves_per_simd<K>())))
+    k_move_rows(SweepArgs a, const Buckets bk, int64_t L, uint32_t *keybuf, int64_t total, const int32_t *light,
+                int64_t nlight, unsigned long long *queue) {
+  __shared__ RowShare<K> S;
+  Counters ct;
+  if constexpr (!PERSIST) {
+    if (blockIdx.x < total) {
+      row_item<K, ALGO, MODE>(a, bk, L, keybuf, S, blockIdx.x, ct);
+      if (threadIdx.x < WAVE) flush_wave_counters(a, ct);
+    } else {
+      const int64_t w = (blockIdx.x - total) * (BLOCK / WAVE) + threadIdx.x / WAVE;
+      light_item<K, ALGO, MODE>(a, light, nlight, uniform(w), ct);
+      flush_counters(a, ct);
+    }
+  } else {
     if (level_over(a)) return;
-    Counters ct;
-    const int64_t total = bk.ngroups + bk.wave_end[0];
-    const int c = (int)(((int64_t)blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE) % QLANES);
-    unsigned long long *q = a.queue + (int64_t)c * QSTRIDE;
+    GraphCounts gc{-1, 0, 0, 0};
+    const int64_t c = blockIdx.x % QLANES;
+    unsigned long long *qc = queue + c * QSTRIDE;
     for (;;) {
-      unsigned long long j0 = 0;
-      if (lane_id() == 0) j0 = atomicAdd(q, (unsigned long long)QGRAB);
-      const int64_t j = uniform((int64_t)__shfl(j0, 0));
+      __syncthreads();  // the last item's shared state has been read
+      if (threadIdx.x == 0) S.item = (int64_t)atomicAdd(qc, (unsigned long long)QGRAB);
+      __syncthreads();
+      const int64_t j = uniform(S.item);
       if (c + j * QLANES >= total) break;
 #pragma unroll 1
-      for (int t = 0; t < QGRAB; ++t) {
-        const int64_t wave = c + (j + t) * QLANES;  // wave-uniform
-        if (wave >= total) break;
-        if (wave < bk.ngroups) {
-          long_group<K, ALGO, MODE, true>(a, bk, L, keybuf, win, wave);
-        } else {
-          row_work<K, ALGO, MODE, true>(a, bk, L, keybuf, win, wave - bk.ngroups, ct);
-          if (a.gctr) flush_graph_counters(a, ct);  // the next item's rows may be another graph's
-        }
+      for (int r = 0; r < QGRAB; ++r) {
+        const int64_t w = c + (j + r) * QLANES;  // block-uniform
+        if (w >= total) break;
+        if (r > 0) __syncthreads();
+        row_item<K, ALGO, MODE>(a, bk, L, keybuf, S, w, ct);
+        if (threadIdx.x < WAVE) gather_graph_counts(a, ct, gc);
       }
     }
+    if (threadIdx.x == 0) commit_graph_counts(a, gc);
+  }
+}
+
+// A level of light rows alone (its own kernel has a third more waves per SIMD than
+// k_move_rows).  PERSIST as in k_move_rows, a wave taking the items.
+template <int K, int ALGO, int MODE, bool PERSIST>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(light_waves_per_simd<K>())))
+    k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, unsigned long long *queue) {
+  const int64_t wave = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  Counters ct;
+  if constexpr (!PERSIST) {
+    light_item<K, ALGO, MODE>(a, rows, nrows, wave, ct);
     flush_counters(a, ct);
+  } else {
+    if (level_over(a)) return;
+    GraphCounts gc{-1, 0, 0, 0};
+    const int64_t total = (nrows + WAVE / QUAD - 1) / (WAVE / QUAD);
+    const int64_t c = wave % QLANES;
+    unsigned long long *qc = queue + c * QSTRIDE;
+    for (;;) {
+      unsigned long long j0 = 0;
+      if (lane_id() == 0) j0 = atomicAdd(qc, (unsigned long long)1);
+      // LGRAB neighbouring items: mostly rows of one graph, whose counts go out together
+      const int64_t w0 = (c + uniform((int64_t)__shfl(j0, 0)) * QLANES) * LGRAB;
+      if (w0 >= total) break;
+#pragma unroll 1
+      for (int r = 0; r < LGRAB && w0 + r < total; ++r) {
+        light_item<K, ALGO, MODE>(a, rows, nrows, w0 + r, ct);
+        gather_graph_counts(a, ct, gc);
+      }
+    }
+    if (lane_id() == 0) commit_graph_counts(a, gc);
   }
 }
 
@@ -1620,8 +2046,11 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n) {
 //   every mode: rows without entries (category 8) are sorted last and listed in no
 //          kernel's work: their label can never change, so no sweep writes it, and
 //          callers keep both label buffers equal for them.
-constexpr int NCAT = 10;
+//   MG:    10 = light rows: category 0 with at most LIGHT_MAX entries (they follow the
+//          other single-chunk rows in the heavy-first order).
+constexpr int NCAT = 11;
 constexpr int CAT_EMPTY = 8;
+constexpr int CAT_LIGHT = 10;
 constexpr int CAT_SHORT = 9;  // MG: rows whose sketch cannot lose weight (exact one-lane kernel)
 
 __global__ void __launch_bounds__(BLOCK)
@@ -1653,10 +2082,10 @@ __global__ void __launch_bounds__(BLOCK)
       k = (uint64_t)(cat * 64 + 64 - b);  // heavy rows first in each tier
     } else if (deg <= sp.mg_short) {  // after the single-chunk rows, heavy rows first
       cat = CAT_SHORT;
-      k = (uint64_t)(128 + 64 - b);
+      k = (uint64_t)(128 + 64 - b);  // b <= 5: below 200
     } else if (deg <= L) {
-      cat = 0;
-      k = (uint64_t)(64 - b);  // heavy rows first
+      cat = deg <= LIGHT_MAX ? CAT_LIGHT : 0;
+      k = (uint64_t)(64 - b) + (deg <= LIGHT_MAX ? 64 : 0);  // heavy rows first, then light ones
     } else {
       int64_t nc = (deg + L - 1) / L;
       int lp = 0;
@@ -1870,7 +2299,9 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
   int64_t pos = 0;
   s.single = order;
   s.nsingle = (int64_t)h[0];
-  pos = s.nsingle;
+  s.light = order + s.nsingle;
+  s.nlight = (int64_t)h[CAT_LIGHT];
+  pos = s.nsingle + s.nlight;
   s.tier[0] = order + pos;  // short rows
   s.ntier[0] = (int64_t)h[CAT_SHORT];
   pos += s.ntier[0];
@@ -1915,11 +2346,11 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
       const int64_t rows = b == 0 ? s.nsingle : s.npacked[b];
       bk.rows[b] = b == 0 ? s.single : s.packed[b];
       bk.nrows[b] = rows;
-      bk.wave_begin[b] = w;
-      w += ceil_div(rows << b, WAVE);
-      bk.wave_end[b] = w;
+      bk.item_begin[b] = w;
+      w += ceil_div(rows << b, WCH);
+      bk.item_end[b] = w;
     }
-    s.row_waves = w;
+    s.row_items = w;
     bk.ngroups = s.ngroups;
     bk.multi = s.multi;
     bk.gowner = s.gowner;
@@ -1937,30 +2368,47 @@ static inline void mark(hipEvent_t *ev, int i, hipStream_t st) {
   if (ev) MGCD_HIP(hipEventRecord(ev[i], st));
 }
 
-// Workgroups of the main sweep kernel resident at once on the current device: its LDS
-// windows (36 KiB per workgroup) leave room for four per compute unit.
-static int64_t resident_blocks() {
+// Compute units of the current device.
+static int64_t compute_units() {
   int dev = 0, cus = 0;
   MGCD_HIP(hipGetDevice(&dev));
   MGCD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  return 4 * (int64_t)(cus > 0 ? cus : 1);
+  return cus > 0 ? cus : 1;
+}
+
+// One launch of the main sweep kernel over `items` work items; persistent (a.queue): as
+// many workgroups as stay resident at once, each pulling work until the queue is empty.
+template <int K, int ALGO, int MODE>
+static void launch_rows(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st) {
+  const int64_t items = s.ngroups + s.row_items, lblocks = ceil_div(s.nlight, BLOCK / QUAD);
+  const bool own = a.queue || items == 0;  // the light rows in a launch of their own
+  if (items > 0) {
+    if (a.queue) {
+      const int64_t grid = std::min<int64_t>(items, compute_units() * row_waves_per_simd<K>());
+      k_move_rows<K, ALGO, MODE, true><<<(unsigned)grid, BLOCK, 0, st>>>(a, s.buckets, L, s.keybuf, items, nullptr, 0,
+                                                                        a.queue);
+    } else {
+      k_move_rows<K, ALGO, MODE, false><<<(unsigned)(items + lblocks), BLOCK, 0, st>>>(
+          a, s.buckets, L, s.keybuf, items, s.light, s.nlight, nullptr);
+    }
+    MGCD_LAUNCHED();
+  }
+  if (own && lblocks > 0) {
+    if (a.queue) {
+      const int64_t grid = std::min<int64_t>(lblocks, compute_units() * light_waves_per_simd<K>());
+      k_move_light<K, ALGO, MODE, true><<<(unsigned)grid, BLOCK, 0, st>>>(a, s.light, s.nlight,
+                                                                         a.queue + QLANES * QSTRIDE);
+    } else {
+      k_move_light<K, ALGO, MODE, false><<<(unsigned)lblocks, BLOCK, 0, st>>>(a, s.light, s.nlight, nullptr);
+    }
+    MGCD_LAUNCHED();
+  }
 }
 
 template <int K, int ALGO, int MODE>
 static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st, hipEvent_t *ev) {
   mark(ev, 0, st);
-  const int64_t waves = s.ngroups + s.row_waves;
-  if (waves > 0) {
-    // persistent (a.queue): as many workgroups as stay resident at once, each pulling
-    // work until the queue is empty
-    const int64_t blocks = ceil_div(waves, BLOCK / WAVE);
-    if (a.queue)
-      k_move_rows<K, ALGO, MODE, true><<<(unsigned)std::min<int64_t>(blocks, resident_blocks()), BLOCK, 0, st>>>(
-          a, s.buckets, L, s.keybuf);
-    else
-      k_move_rows<K, ALGO, MODE, false><<<(unsigned)blocks, BLOCK, 0, st>>>(a, s.buckets, L, s.keybuf);
-    MGCD_LAUNCHED();
-  }
+  launch_rows<K, ALGO, MODE>(a, s, L, st);
   mark(ev, 1, st);
   // long rows: rest of the merge tree, pass 2, decision
   if (s.nmulti > 0) {
@@ -2106,12 +2554,15 @@ void launch_sweep(const SweepArgs &a, const Schedule &s, int algo, int mode, int
 
 // ---- bookkeeping kernels ---------------------------------------------------------------
 
+// Run by one whole wave: each lane takes its copy of the sweep's counters.
 __device__ inline void level_converge(int algo, const LevelRule &r) {
-  // Read and clear in one atomic step: a plain load of these uniform addresses may
-  // become a scalar load, which a following vector store of 0 can overtake.
-  unsigned long long *ctr = r.ctr;
-  const unsigned long long moved = atomicExch(&ctr[0], 0ull), prop = atomicExch(&ctr[1], 0ull),
-                           sumG = atomicExch(&ctr[2], 0ull), cands = atomicExch(&ctr[3], 0ull);
+  // Read and clear in one atomic step: a plain load of these addresses may overtake the
+  // store of 0 that follows it.
+  static_assert(SPREAD == WAVE, "one copy of the counters per lane");
+  unsigned long long *ctr = r.ctr + lane_id() * CTR_STRIDE;
+  const unsigned long long moved = wave_sum(atomicExch(&ctr[0], 0ull)), prop = wave_sum(atomicExch(&ctr[1], 0ull)),
+                           sumG = wave_sum(atomicExch(&ctr[2], 0ull)), cands = wave_sum(atomicExch(&ctr[3], 0ull));
+  if (lane_id() != 0) return;
   LevelState *ls = r.ls;
   if (ls->halt) return;
   ls->cands += cands;
@@ -2127,7 +2578,7 @@ __global__ void k_apply_moves(const int32_t *Cold, const int32_t *Cnew, const ui
                               int32_t n, LevelRule rule) {
   int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (rule.live && *rule.live == 0) return;  // batched: the sweep did nothing
-  if (rule.ls && i == 0) level_converge(ALGO_MOVE, rule);  // the sweep's counters are final
+  if (rule.ls && i < WAVE) level_converge(ALGO_MOVE, rule);  // the sweep's counters are final
   if (i >= n) return;
   int32_t d = Cold[i], c = Cnew[i];
   if (c == d) return;
@@ -2204,7 +2655,7 @@ __global__ void k_iota(int32_t *p, int64_t n) {
 __global__ void k_level_converge(int algo, LevelRule r) { level_converge(algo, r); }
 
 void launch_level_converge(int algo, const LevelRule &r, hipStream_t st) {
-  k_level_converge<<<1, 1, 0, st>>>(algo, r);
+  k_level_converge<<<1, WAVE, 0, st>>>(algo, r);
   MGCD_LAUNCHED();
 }
 

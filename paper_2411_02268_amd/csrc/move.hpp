@@ -5,6 +5,13 @@
 
 namespace mgcd {
 
+// The sweep's counters: SPREAD copies, each on a cache line of its own.
+constexpr int CTR_STRIDE = 16;
+constexpr int64_t CTR_WORDS = (int64_t)SPREAD * CTR_STRIDE;
+
+// Rows of one chunk with at most LIGHT_MAX entries take the light rows' kernel.
+constexpr int LIGHT_MAX = 32;
+
 // Everything one synchronous sweep reads and writes.
 struct SweepArgs {
   Graph g;
@@ -16,7 +23,9 @@ struct SweepArgs {
   int32_t dir;           // -1 lower ids only, +1 higher ids only, 0 any
   int32_t *Cnew;         // new membership (refinement: proposed target)
   int64_t *gain;         // optional: gain of each vertex's best move
-  unsigned long long *ctr;  // [moved, proposals, sum of gains, candidates] (device)
+  // [moved, proposals, sum of gains, candidates] (device): SPREAD copies, CTR_STRIDE
+  // apart, whose sums count (a workgroup adds to the copy of its index)
+  unsigned long long *ctr;
   // Batched runs (many graphs as one disjoint union): graph of every vertex, its
   // graph's total weight, whether that graph still moves, per-graph counters
   // [3 * graph + {moved, proposals, sum of gains}].  Null for a single graph.
@@ -87,18 +96,21 @@ void launch_zero_state(LevelState *ls, hipStream_t st);
 // The persistent main sweep kernel's work queue: QLANES counters, each on a cache line
 // of its own (QSTRIDE u64 apart); counter c hands out work items c, c + QLANES, ...
 // (an interleaved share of the heaviest-first order), QGRAB at a time, so that the
-// waves' atomics spread over QLANES addresses and a grab serves many items.
-constexpr int QLANES = 64, QSTRIDE = 16, QGRAB = 16;
+// workgroups' atomics spread over QLANES addresses and a grab serves several items.
+// The light rows' kernel has counters of its own after these; it grabs LGRAB neighbouring
+// items of 16 rows at a time.
+constexpr int QLANES = 64, QSTRIDE = 16, QGRAB = 4, LGRAB = 8;
+constexpr int64_t QWORDS = 2 * (int64_t)QLANES * QSTRIDE;
 
-// Row buckets of the main sweep kernel: rows needing 2^b lanes (b = 0..6).
-// The grid of the main sweep kernel: first one wave per group of 64 chunks of the
-// long rows (more than 64 chunks), then the row buckets.
+// Row buckets of the main sweep kernel: rows needing 2^b chunks (b = 0..6).  Its work
+// items (one workgroup each) are first the groups of 64 chunks of the long rows (more
+// than 64 chunks), then the row buckets.
 struct Buckets {
-  int64_t wave_begin[7];  // row waves of bucket b: [wave_begin[b], wave_end[b]), counted
-  int64_t wave_end[7];    // after the long-row groups; b = 6 first; wave_end[0] = total
+  int64_t item_begin[7];  // items of bucket b: [item_begin[b], item_end[b]), counted after
+  int64_t item_end[7];    // the long-row groups; b = 6 first; item_end[0] = total
   const int32_t *rows[7];
   int64_t nrows[7];
-  int64_t ngroups;        // long-row groups (their waves come first)
+  int64_t ngroups;        // long-row groups (their items come first)
   const int32_t *multi;   // long rows
   const int32_t *gowner;  // [ngroups] long row of each group
   const int64_t *gstart;  // [nmulti+1] first group of each long row
@@ -110,8 +122,10 @@ struct Buckets {
 // Per-level work lists, built once per level by build_schedule.
 struct Schedule {
   // MG mode
-  int32_t *single = nullptr;  // vertices whose row fits one chunk (deg <= L), heavy first
+  int32_t *single = nullptr;  // vertices of more than LIGHT_MAX entries in one chunk, heavy first
   int64_t nsingle = 0;
+  int32_t *light = nullptr;   // light rows, heavy first
+  int64_t nlight = 0;
   int32_t *packed[7] = {};    // [b] long rows of at most 2^b chunks (b = 1..6)
   int64_t npacked[7] = {};
   int32_t *multi = nullptr;   // rows of more than 64 chunks, ascending id
@@ -121,8 +135,8 @@ struct Schedule {
   int64_t nchunks = 0;
   int64_t maxdeg = 0;          // longest row
   Buckets buckets{};           // bucket table of k_move_rows (passed by value)
-  int64_t row_waves = 0;
-  uint32_t *keybuf = nullptr; // [nnz] keys C[j] gathered in pass 1, read by pass 2
+  int64_t row_items = 0;
+  uint32_t *keybuf = nullptr; // [nnz] keys C[j] of rows that pass 2 re-reads, written by pass 1
   int64_t *gstart = nullptr;  // [nmulti+1] first group of 64 chunks of each multi vertex
   int32_t *gowner = nullptr;  // [ngroups] multi index of each group
   int64_t ngroups = 0;

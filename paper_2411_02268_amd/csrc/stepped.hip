@@ -659,10 +659,10 @@ void StepEngine::end_level(StepJob *j, const Lane &l) {
     Schedule sch;
     build_schedule(j->cur, sched_params(&p_), sch, a, st);
     int32_t *prop = a.take<int32_t>(nl), *nprop = a.take<int32_t>(nl), *from = a.take<int32_t>(nl);
-    unsigned long long *ctr = a.take<unsigned long long>(4);
+    unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
     SweepArgs r{j->cur, nullptr, j->C, K, K, j->W, 0, prop, nullptr, ctr};
     launch_iota(prop, nl, st);  // a row without entries proposes itself
-    launch_zero_u64(ctr, 4, st);
+    launch_zero_u64(ctr, CTR_WORDS, st);
     launch_sweep(r, sch, ALGO_REFINE, p_.mode, p_.k, p_.chunk_len, st);
     launch_refine_accept(prop, nprop, from, j->R, nl, st);
     a.release(mk);
@@ -766,12 +766,12 @@ void StepEngine::repack() {
   u.git = (int32_t *)(u.table + tl.git);
   u.gdir = (int8_t *)(u.table + tl.gdir);
   u.gctr = a.take<unsigned long long>(3 * (int64_t)count);
-  u.ctr = a.take<unsigned long long>(4);
+  u.ctr = a.take<unsigned long long>(CTR_WORDS);
   u.res = a.take<StepResult>(count);
   u.lv = a.take<uint32_t>(2);
   MGCD_HIP(hipMemcpyAsync(u.table, ht.data(), tl.total, hipMemcpyHostToDevice, st_));
   launch_zero_u64(u.gctr, 3 * (int64_t)count, st_);
-  launch_zero_u64(u.ctr, 4, st_);
+  launch_zero_u64(u.ctr, CTR_WORDS, st_);
   for (int32_t y0 = 0; y0 < count; y0 += 65535) {
     const int32_t ny = std::min<int32_t>(65535, count - y0);
     dim3 grid((unsigned)std::min<int64_t>(ceil_div(maxi, BLOCK), 4096), (unsigned)ny);
