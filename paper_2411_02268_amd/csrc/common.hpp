@@ -121,6 +121,13 @@ struct Timer {
 // ---- wave helpers (device) -------------------------------------------------------
 __device__ inline int lane_id() { return (int)(threadIdx.x & (WAVE - 1)); }
 
+// Orders a wave's LDS accesses before this point with those after it.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A value that is the same in every lane, moved to a scalar register so that the
 // compiler treats what depends on it as wave-uniform (scalar branches and loops).
 __device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -119,66 +119,81 @@ __global__ void __launch_bounds__(BLOCK)
   hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
 }
 
-// Items are visited in tile order (round r covers items base + r*256 + t), ranked
-// among equal digits with wave ballots, and written to their stable positions.
+// Wave w takes items base + 1024 w .. of the tile in order, 64 per round: an item's rank
+// among the wave's items of its digit is the wave's count so far (its own LDS row, no
+// barrier between rounds) plus its rank among the round's lanes (ballots).  The waves'
+// counts, scanned once per tile, and the tile's digit offsets then give every position.
+// All loads of the tile are in flight together.  On one tile (the smallest sorts) it takes
+// 8 us against 15 for 16 rounds between barriers; 15.5 M pairs in 122 us instead of 129
+// (3 TB/s: there it is bound by the scattered stores, 12 bytes per item in short runs).
 __global__ void __launch_bounds__(BLOCK)
     k_rs_scatter(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t *vout,
                  int64_t n, int shift, const int64_t *offs, int64_t tiles) {
-  __shared__ uint32_t run[RS_BINS];
-  __shared__ uint32_t wcnt[4][RS_BINS];
-  const int t = threadIdx.x, w = t / WAVE;
-  run[t] = 0;
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  const int64_t my_off = offs[(int64_t)t * tiles + blockIdx.x];  // thread t owns digit t
+  constexpr int WAVES = BLOCK / WAVE;
+  __shared__ uint32_t cnt[WAVES][RS_BINS];
   __shared__ int64_t off_lds[RS_BINS];
-  off_lds[t] = my_off;
-  for (int r = 0; r < RS_ITEMS; ++r) {
-    int64_t i = base + (int64_t)r * BLOCK + t;
-    bool valid = i < n;
-    uint64_t key = valid ? kin[i] : 0;
-    uint32_t val = valid ? vin[i] : 0;
-    uint32_t d = (uint32_t)(key >> shift) & 255u;
+  const int t = threadIdx.x, w = t / WAVE;
+  static_assert(BLOCK == RS_BINS, "thread t owns digit t");
+  off_lds[t] = offs[(int64_t)t * tiles + blockIdx.x];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wcnt[q][t] = 0;
-    __syncthreads();
+  for (int q = 0; q < WAVES; ++q) cnt[q][t] = 0;
+  const int64_t first = (int64_t)blockIdx.x * RS_TILE + (int64_t)w * (RS_TILE / WAVES) + lane_id();
+  uint64_t key[RS_ITEMS];
+  uint32_t val[RS_ITEMS], rank[RS_ITEMS];
+#pragma unroll
+  for (int r = 0; r < RS_ITEMS; ++r) {
+    const int64_t i = first + (int64_t)r * WAVE;
+    key[r] = i < n ? kin[i] : 0;
+    val[r] = i < n ? vin[i] : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RS_ITEMS; ++r) {
+    const bool valid = first + (int64_t)r * WAVE < n;
+    const uint32_t d = (uint32_t)(key[r] >> shift) & (RS_BINS - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      bool bit = (d >> b) & 1u;
-      uint64_t m = __ballot(bit);
+      const bool bit = (d >> b) & 1u;
+      const uint64_t m = __ballot(bit);
       peers &= bit ? m : ~m;
     }
-    uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-    if (valid && rank == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    uint32_t c0 = wcnt[0][t], c1 = wcnt[1][t], c2 = wcnt[2][t], c3 = wcnt[3][t];
-    __syncthreads();
-    wcnt[0][t] = 0;
-    wcnt[1][t] = c0;
-    wcnt[2][t] = c0 + c1;
-    wcnt[3][t] = c0 + c1 + c2;
-    uint32_t tot = c0 + c1 + c2 + c3;
-    __syncthreads();
-    if (valid) {
-      int64_t pos = off_lds[d] + run[d] + wcnt[w][d] + rank;
-      kout[pos] = key;
-      vout[pos] = val;
+    const uint32_t before = cnt[w][d];
+    rank[r] = (uint32_t)__popcll(peers & lanemask_lt());
+    wave_sync();
+    if (valid && rank[r] == 0) cnt[w][d] = before + (uint32_t)__popcll(peers);
+    wave_sync();
+    rank[r] += before;
+  }
+  __syncthreads();
+  uint32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < WAVES; ++q) {
+    const uint32_t c = cnt[q][t];
+    cnt[q][t] = sum;
+    sum += c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RS_ITEMS; ++r) {
+    if (first + (int64_t)r * WAVE < n) {
+      const uint32_t d = (uint32_t)(key[r] >> shift) & (RS_BINS - 1);
+      const int64_t pos = off_lds[d] + cnt[w][d] + rank[r];
+      kout[pos] = key[r];
+      vout[pos] = val[r];
     }
-    __syncthreads();
-    run[t] += tot;
-    __syncthreads();
   }
 }
 
 bool radix_sort_pairs(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, int64_t n,
-                      int bits, Arena &a, hipStream_t s) {
-  if (n <= 1 || bits <= 0) return false;
+                      int bits, Arena &a, hipStream_t s, int from) {
+  if (n <= 1 || bits <= from) return false;
   int64_t tiles = ceil_div(n, RS_TILE);
   size_t m = a.mark();
   uint32_t *hist = a.take<uint32_t>(tiles * RS_BINS);
   int64_t *offs = a.take<int64_t>(tiles * RS_BINS);
   bool flip = false;
-  for (int shift = 0; shift < bits; shift += 8) {
+  for (int shift = from; shift < bits; shift += 8) {
     const uint64_t *ki = flip ? k1 : k0;
     const uint32_t *vi = flip ? v1 : v0;
     uint64_t *ko = flip ? k0 : k1;

@@ -16,12 +16,6 @@ constexpr int WROW = 2 * WIN + 4;  // words per lane row: WIN (key, weight) pair
 constexpr int SPR = WAVE / WIN;    // segments staged per load round (WIN lanes each); a
                                    // window takes WIN rounds
 
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ inline void put_pair(uint32_t *win, int src, uint32_t k, uint32_t w) {
   typedef uint32_t v2u __attribute__((ext_vector_type(2)));
   v2u pr;
