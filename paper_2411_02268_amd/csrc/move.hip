@@ -1488,65 +1488,153 @@ __global__ void __launch_bounds__(BLOCK)
 
 // ---- exact mode ----------------------------------------------------------------------
 
-// A row of at most ES entries: keys and weights gathered once into registers, then
-// every distinct key summed at its first occurrence (static indices, unrolled).
-template <int ALGO, int ES>
-__device__ inline void exact_row_regs(const SweepArgs &a, int32_t i, int32_t bi, int64_t lo,
-                                      int64_t hi, int32_t d, Counters &ct) {
-  // Every load is issued on every lane (an absent position reads a valid entry: the
-  // row's first, or entry 0 for an empty row; some row of the wave is non-empty) and
-  // its value masked afterwards, so the loads and gathers of all positions are in
-  // flight together.
-  uint32_t ks[ES], ws[ES];
-  const int64_t safe = hi > lo ? lo : 0;
+// Exact mode, the shortest rows (tier 0, and the rows whose sketch is their exact table):
+// G = 1, 2, 4 or 8 lanes per row of at most 4 G entries, each lane with four neighbouring
+// entries from one 128-bit load.  Every lane sums the weights of its four keys over the
+// whole row (the other lanes' entries come by DPP moves) and scores them; a key that
+// occurs twice is scored twice, to the same value.  The group's best is the row's.
+// With one lane per row every load of a wave touches a line per lane, 64 a piece, and that
+// was the time: a sweep over 0.34 M aggregated rows of up to 16 entries took 70 us and
+// takes 43 (Leiden k = 16 on Chung-Lu 2^22), over R-MAT 2^19's rows of up to 32 entries
+// 66 and 34 us.  Rows of one to three entries (5 M of k-mer chains: 314 and 309 us) are
+// bound by the gathers of C and Sigma, 10 M each from 20 MB tables at the 72 G/s that such
+// gathers reach; a row whose neighbours share its community reads no totals.
+template <int G>
+__device__ inline uint32_t group_perm(uint32_t x, int v) {  // v = 1 .. G - 1: another lane of the group
+  const uint32_t y = v & 4 ? quad_perm<QP_HALF_MIRROR>(x) : x;
+  return (v & 3) == 1 ? quad_perm<QP_XOR1>(y) : (v & 3) == 2 ? quad_perm<QP_XOR2>(y) : (v & 3) == 3 ? quad_perm<QP_XOR3>(y) : y;
+}
+// Lanes of a reduction step over the group: v = 1, 2, 4 ... < G.
+template <int G>
+__device__ inline uint32_t group_sum(uint32_t x) {
 #pragma unroll
-  for (int t = 0; t < ES; ++t) {
-    const bool v = lo + t < hi;
-    const int64_t e = v ? lo + t : safe;
-    const int32_t j = a.g.idx[e];
-    ws[t] = a.g.w[e] & (v ? ~0u : 0u);
-    uint32_t c;
-    if (ALGO == ALGO_REFINE)
-      c = a.bound[j] == bi ? (uint32_t)j : EMPTY;
-    else
-      c = (uint32_t)a.C[j];
-    ks[t] = c | ((v && j != i) ? 0u : EMPTY);  // self-loops are skipped
-  }
-  // table keys: the keys themselves, or their slots in the small table (a slot's
-  // first key stands for it, K_{i->d} is the sum in d's slot)
-  uint32_t ss[ES];
+  for (int v = 1; v < G; v <<= 1) x += group_perm<G>(x, v);
+  return x;
+}
+template <int G>
+__device__ inline uint32_t group_or(uint32_t x) {
 #pragma unroll
-  for (int t = 0; t < ES; ++t) ss[t] = ks[t] != EMPTY ? slot_of(a, ks[t]) : EMPTY;
-  const uint32_t sd = slot_of(a, (uint32_t)d);
-  uint32_t kd = 0;
-#pragma unroll
-  for (int t = 0; t < ES; ++t) kd += ss[t] == sd ? ws[t] : 0u;
-  int32_t best = -1;
-  int64_t bestG = 0;
-  const int64_t W = ALGO == ALGO_LPA ? 0 : (int64_t)weight_of(a, i);
-  const int64_t Ki = ALGO == ALGO_LPA ? 0 : (int64_t)a.K[i];
-  const int64_t Sd = ALGO == ALGO_LPA ? 0 : (int64_t)a.Sig[d];
-  uint32_t sc[ES];
-#pragma unroll
-  for (int t = 0; t < ES; ++t) sc[t] = ALGO == ALGO_LPA ? 0u : a.Sig[ks[t] != EMPTY ? (int32_t)ks[t] : d];
-#pragma unroll
-  for (int t = 0; t < ES; ++t) {
-    const uint32_t c = ks[t];
-    bool first = c != EMPTY;
-#pragma unroll
-    for (int u = 0; u < t; ++u) first &= ss[u] != ss[t];
-    uint32_t kc = 0;
-#pragma unroll
-    for (int u = t; u < ES; ++u) kc += ss[u] == ss[t] ? ws[u] : 0u;
-    consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)c, kc, sc[t], first, best, bestG);
-  }
-  finish<ALGO>(a, i, d, best, bestG, ct);
+  for (int v = 1; v < G; v <<= 1) x |= group_perm<G>(x, v);
+  return x;
 }
 
-// Exact mode, the shortest rows (tier 0): one lane per vertex; K_{i->c} of each
-// distinct key, summed at its first occurrence in the row.  Rows of at most 32
-// entries keep the row in registers (the unroll depth, 2 to 32, follows the longest
-// row of the wave); longer tier-0 rows (a raised exact_small) re-read the row.
+// Rows w * (WAVE / G) .. of list (count of them), one wave.  SMALL: table keys are slots
+// of the small table; a slot's first key (in row order) stands for it.
+template <int ALGO, bool SMALL, int G>
+__device__ MGCD_INLINE void short_item(const SweepArgs &a, const int32_t *list, int64_t count, int64_t w,
+                                       Counters &ct) {
+  const int lane = lane_id(), q = lane % G;
+  const int64_t r = w * (WAVE / G) + lane / G;
+  const bool listed = r < count;
+  const int32_t i = listed ? list[r] : 0;
+  // what the row needs is read before it is known whether its graph still moves
+  const int64_t rlo = a.g.off[i], rhi = a.g.off[i + 1];
+  const int32_t d = community_of_self<ALGO>(a, i);
+  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
+  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+  const int32_t gi = a.gid ? a.gid[i] : 0;
+  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[gi] : (int64_t)a.W;
+  const bool valid = listed && !(a.halt && *a.halt) && !(a.gid && !a.active[gi]);
+  if (listed && !valid && q == 0) a.Cnew[i] = d;
+  const int left = valid ? (int)(rhi - rlo) - 4 * q : 0;
+  const v4u j = load4(reinterpret_cast<const uint32_t *>(a.g.idx), rlo + 4 * q, a.g.nnz, left > 0);
+  const v4u y = load4(a.g.w, rlo + 4 * q, a.g.nnz, left > 0);
+  uint32_t key[4], wt[4], kc[4], sl[4];
+  // every gather is issued on every lane with a valid id and masked afterwards
+#pragma unroll
+  for (int u = 0; u < 4; ++u) key[u] = u < left ? j[u] : 0u;
+  if (ALGO == ALGO_REFINE) {
+    uint32_t bb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bb[u] = (uint32_t)a.bound[(int32_t)key[u]];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) key[u] |= bb[u] == (uint32_t)b ? 0u : EMPTY;
+  } else if (!a.ident) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) key[u] = (uint32_t)a.C[(int32_t)key[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    key[u] |= u < left && j[u] != (uint32_t)i ? 0u : EMPTY;  // self-loops are skipped
+    wt[u] = key[u] != EMPTY ? y[u] : 0u;
+    sl[u] = SMALL && key[u] != EMPTY ? slot_of(a, key[u]) : key[u];
+    kc[u] = 0;
+  }
+  const uint32_t sd = SMALL ? slot_of(a, (uint32_t)d) : (uint32_t)d;
+  uint32_t kd = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) kd += sl[u] == sd ? wt[u] : 0u;
+  kd = group_sum<G>(kd);
+  bool stands[4];  // the key may be the row's choice
+#pragma unroll
+  for (int u = 0; u < 4; ++u) stands[u] = key[u] != EMPTY;
+#pragma unroll
+  for (int v = 0; v < G; ++v) {
+    const uint32_t qo = group_perm<G>((uint32_t)q, v);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const uint32_t so = group_perm<G>(sl[x], v), wo = group_perm<G>(wt[x], v);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        kc[u] += so == sl[u] ? wo : 0u;
+        if (SMALL) stands[u] &= !(so == sl[u] && (qo < (uint32_t)q || (qo == (uint32_t)q && x < u)));
+      }
+    }
+  }
+  int32_t best = -1;
+  int64_t bestG = 0;
+  if constexpr (ALGO == ALGO_LPA) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      consider_v<ALGO>(W, d, 0, 0, kd, (int32_t)key[u], kc[u], 0u, stands[u], best, bestG);
+  } else {
+    // a total is read where it can matter; the other lanes read community 0's together
+    uint32_t any = 0, sc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      stands[u] = stands[u] && key[u] != (uint32_t)d;
+      any |= stands[u];
+    }
+    any = group_or<G>(any);
+    const uint32_t Sd = a.Sig[any ? d : 0];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sc[u] = a.Sig[stands[u] ? (int32_t)key[u] : 0];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)key[u], kc[u], sc[u], stands[u], best, bestG);
+  }
+#pragma unroll
+  for (int v = 1; v < G; v <<= 1) {
+    const uint32_t lo = group_perm<G>((uint32_t)bestG, v), hi = group_perm<G>((uint32_t)((uint64_t)bestG >> 32), v);
+    const int32_t c2 = (int32_t)group_perm<G>((uint32_t)best, v);
+    const int64_t g2 = (int64_t)(((uint64_t)hi << 32) | lo);
+    const bool take = c2 >= 0 && (best < 0 || g2 > bestG || (g2 == bestG && c2 < best));
+    best = take ? c2 : best;
+    bestG = take ? g2 : bestG;
+  }
+  if (valid && q == 0) finish<ALGO>(a, i, d, best, bestG, ct);
+}
+
+// The short rows, classes of 17..32, 8..16, 4..7 and 1..3 entries one after another in
+// the list, each from a wave of its own on.
+template <int ALGO, bool SMALL>
+__global__ void __launch_bounds__(BLOCK) k_exact_short(SweepArgs a, const int32_t *__restrict__ list, ShortRows sr) {
+  if (level_over(a)) return;  // batched: every graph has stopped
+  Counters ct;
+  const int64_t w = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  if (w < sr.wave[1])
+    short_item<ALGO, SMALL, 8>(a, list, sr.row[1], w, ct);
+  else if (w < sr.wave[2])
+    short_item<ALGO, SMALL, 4>(a, list + sr.row[1], sr.row[2] - sr.row[1], w - sr.wave[1], ct);
+  else if (w < sr.wave[3])
+    short_item<ALGO, SMALL, 2>(a, list + sr.row[2], sr.row[3] - sr.row[2], w - sr.wave[2], ct);
+  else if (w < sr.wave[4])
+    short_item<ALGO, SMALL, 1>(a, list + sr.row[3], sr.row[4] - sr.row[3], w - sr.wave[3], ct);
+  flush_counters(a, ct);
+}
+
+// Tier-0 rows of more than 32 entries (a raised exact_small): one lane per row, which
+// re-reads it for every key at its first occurrence.
 template <int ALGO>
 __global__ void __launch_bounds__(BLOCK)
     k_exact_small(SweepArgs a, const int32_t *__restrict__ list, int64_t count) {
@@ -1557,29 +1645,10 @@ __global__ void __launch_bounds__(BLOCK)
   const int32_t i = listed ? list[t] : 0;
   const bool live = listed && !frozen(a, i);
   if (listed && !live) a.Cnew[i] = community_of_self<ALGO>(a, i);
-  const int64_t lo = live ? a.g.off[i] : 0, hi = live ? a.g.off[i + 1] : 0;
-  int64_t maxdeg = hi - lo;
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const int64_t x = __shfl_xor(maxdeg, o);
-    maxdeg = x > maxdeg ? x : maxdeg;
-  }
-  maxdeg = uniform(maxdeg);
-  const int32_t bi = (ALGO == ALGO_REFINE && live) ? a.bound[i] : 0;
-  const int32_t d = live ? community_of_self<ALGO>(a, i) : 0;
-  if (maxdeg == 0) {
-    if (live) finish<ALGO>(a, i, d, -1, 0, ct);  // no neighbours: stay
-  } else if (maxdeg <= 2) {
-    if (live) exact_row_regs<ALGO, 2>(a, i, bi, lo, hi, d, ct);
-  } else if (maxdeg <= 4) {
-    if (live) exact_row_regs<ALGO, 4>(a, i, bi, lo, hi, d, ct);
-  } else if (maxdeg <= 8) {
-    if (live) exact_row_regs<ALGO, 8>(a, i, bi, lo, hi, d, ct);
-  } else if (maxdeg <= 16) {
-    if (live) exact_row_regs<ALGO, 16>(a, i, bi, lo, hi, d, ct);
-  } else if (maxdeg <= 32) {
-    if (live) exact_row_regs<ALGO, 32>(a, i, bi, lo, hi, d, ct);
-  } else if (live) {
+  if (live) {
+    const int64_t lo = a.g.off[i], hi = a.g.off[i + 1];
+    const int32_t bi = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+    const int32_t d = community_of_self<ALGO>(a, i);
     // table key of entry f (EMPTY when Algorithm 1's skips drop it)
     auto tkey = [&](int64_t f) {
       const uint32_t c = stream_key<ALGO>(a, i, a.g.idx[f], bi);
@@ -2048,9 +2117,12 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n) {
 //          callers keep both label buffers equal for them.
 //   MG:    10 = light rows: category 0 with at most LIGHT_MAX entries (they follow the
 //          other single-chunk rows in the heavy-first order).
-constexpr int NCAT = 11;
+//   every mode: 11..15 count the rows of category 0 or 9 that take the short rows' kernel
+//          by class: 1..3, 4..7, 8..15, 16..32 entries, and longer ones.
+constexpr int NCAT = 16;
 constexpr int CAT_EMPTY = 8;
 constexpr int CAT_LIGHT = 10;
+constexpr int CAT_CLASS = 11;
 constexpr int CAT_SHORT = 9;  // MG: rows whose sketch cannot lose weight (exact one-lane kernel)
 
 __global__ void __launch_bounds__(BLOCK)
@@ -2062,26 +2134,31 @@ __global__ void __launch_bounds__(BLOCK)
   if (threadIdx.x < NCAT) bc[threadIdx.x] = 0;
   __syncthreads();
   int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  int cat = -1;
+  int cat = -1, cls = -1;
   int64_t dmax = 0;
   if (i < n) {
     int64_t deg = off[i + 1] - off[i];
     dmax = deg;
     int b = 0;
     while (b < 63 && (deg >> b) != 0) ++b;  // bits of deg
+    if (deg == 32) b = 5;                   // with 16..31: the longest of their class
     uint64_t k;
+    bool shortrow = false;
     if (deg == 0) {
       cat = CAT_EMPTY;
       k = 255;  // after every other key of every mode
     } else if (mode == MODE_EXACT) {
       cat = deg <= sp.exact_t0 ? 0 : deg <= sp.exact_t1 ? 1 : deg <= sp.exact_t2 ? 2 : 3;
       k = cat == 0 ? (uint64_t)(64 - b) : (uint64_t)(128 + cat);
+      shortrow = cat == 0;
     } else if (sp.wave) {  // K >= 32: short rows exact, split rows, the rest one wave each
       // (K = 128 / 256: every other row is a split row, one wave per chunk)
       cat = deg <= sp.exact_t0 ? 0 : (sp.k > WAVE || (deg > L && deg > WAVE_SPLIT)) ? 2 : 1;
       k = (uint64_t)(cat * 64 + 64 - b);  // heavy rows first in each tier
+      shortrow = cat == 0;
     } else if (deg <= sp.mg_short) {  // after the single-chunk rows, heavy rows first
       cat = CAT_SHORT;
+      shortrow = true;
       k = (uint64_t)(128 + 64 - b);  // b <= 5: below 200
     } else if (deg <= L) {
       cat = deg <= LIGHT_MAX ? CAT_LIGHT : 0;
@@ -2095,10 +2172,11 @@ __global__ void __launch_bounds__(BLOCK)
     }
     key[i] = k;
     val[i] = (uint32_t)i;
+    if (shortrow) cls = CAT_CLASS + (b <= 2 ? 0 : b <= 5 ? b - 2 : 4);
   }
 #pragma unroll
   for (int q = 0; q < NCAT; ++q) {
-    uint64_t m = __ballot(cat == q);
+    uint64_t m = __ballot(cat == q || cls == q);
     if (lane_id() == 0 && m) atomicAdd(&bc[q], (unsigned long long)__popcll(m));
   }
   __syncthreads();
@@ -2225,6 +2303,15 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
   unsigned long long h[NCAT + 1];
   read_spread(cnt, NCAT, h, st);
   s.maxdeg = (int64_t)h[NCAT];
+  {  // the short rows' classes, heavy first: longer ones, then 8, 4, 2 and 1 lanes per row
+    ShortRows &sr = s.shorts;
+    s.ntail = (int64_t)h[CAT_CLASS + 4];
+    for (int q = 0; q < 4; ++q) {
+      const int64_t rows = (int64_t)h[CAT_CLASS + 3 - q];
+      sr.row[q + 1] = sr.row[q] + rows;
+      sr.wave[q + 1] = sr.wave[q] + ceil_div(rows * (8 >> q), WAVE);
+    }
+  }
   if (sp.wave) {
     s.tier[0] = order;
     s.ntier[0] = (int64_t)h[0];
@@ -2405,6 +2492,20 @@ static void launch_rows(const SweepArgs &a, const Schedule &s, int64_t L, hipStr
   }
 }
 
+// Tier 0: the list's longer rows (a raised exact_small), then the short rows.
+template <int ALGO, bool SMALL = false>
+static void launch_short(const SweepArgs &a, const Schedule &s, hipStream_t st) {
+  if (s.ntail > 0) {
+    k_exact_small<ALGO><<<grid_for(s.ntail), BLOCK, 0, st>>>(a, s.tier[0], s.ntail);
+    MGCD_LAUNCHED();
+  }
+  if (s.shorts.wave[4] > 0) {
+    k_exact_short<ALGO, SMALL><<<(unsigned)ceil_div(s.shorts.wave[4], BLOCK / WAVE), BLOCK, 0, st>>>(
+        a, s.tier[0] + s.ntail, s.shorts);
+    MGCD_LAUNCHED();
+  }
+}
+
 template <int K, int ALGO, int MODE>
 static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st, hipEvent_t *ev) {
   mark(ev, 0, st);
@@ -2423,20 +2524,14 @@ static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream
     MGCD_LAUNCHED();
   }
   mark(ev, 2, st);
-  if (s.ntier[0] > 0) {  // rows whose sketch is their exact table: the exact one-lane kernel
-    k_exact_small<ALGO><<<grid_for(s.ntier[0]), BLOCK, 0, st>>>(a, s.tier[0], s.ntier[0]);
-    MGCD_LAUNCHED();
-  }
+  launch_short<ALGO>(a, s, st);  // rows whose sketch is their exact table
   mark(ev, 3, st);
 }
 
 template <int ALGO, bool SMALL = false>
 static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, hipEvent_t *ev) {
   mark(ev, 0, st);
-  if (s.ntier[0] > 0) {
-    k_exact_small<ALGO><<<grid_for(s.ntier[0]), BLOCK, 0, st>>>(a, s.tier[0], s.ntier[0]);
-    MGCD_LAUNCHED();
-  }
+  launch_short<ALGO, SMALL>(a, s, st);
   mark(ev, 1, st);
   if (s.ntier[1] > 0) {
     k_exact_wave<ALGO, SMALL><<<(unsigned)ceil_div(s.ntier[1], BLOCK / WAVE), BLOCK, 0, st>>>(
@@ -2467,10 +2562,7 @@ static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, h
 template <int K, int ALGO, int MODE>
 static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st, hipEvent_t *ev) {
   mark(ev, 0, st);
-  if (s.ntier[0] > 0) {  // rows that cannot lose weight: the exact one-lane kernel
-    k_exact_small<ALGO><<<grid_for(s.ntier[0]), BLOCK, 0, st>>>(a, s.tier[0], s.ntier[0]);
-    MGCD_LAUNCHED();
-  }
+  launch_short<ALGO>(a, s, st);  // rows that cannot lose weight
   mark(ev, 1, st);
   if constexpr (K <= WAVE) {  // K = 128 / 256: every row the sketch takes is a split row
     if (s.ntier[1] > 0) {

@@ -119,6 +119,13 @@ struct Buckets {
   uint32_t *skflag;       // [ngroups] group lost weight
 };
 
+// The short rows (at most 32 entries) in classes of 8, 4, 2 and 1 lanes per row: the rows
+// of class q are row[q] .. row[q + 1] of their list, its waves wave[q] .. wave[q + 1].
+struct ShortRows {
+  int64_t row[5];
+  int64_t wave[5];
+};
+
 // Per-level work lists, built once per level by build_schedule.
 struct Schedule {
   // MG mode
@@ -152,6 +159,8 @@ struct Schedule {
   // exact mode
   int32_t *tier[4] = {nullptr, nullptr, nullptr, nullptr};
   int64_t ntier[4] = {0, 0, 0, 0};
+  ShortRows shorts{};         // tier 0: its rows of at most 32 entries, after
+  int64_t ntail = 0;          // the longer ones (a raised exact_small)
   int64_t *hbase = nullptr;   // [ntier[3]+1] global hash region of each tier-3 vertex
   Pair *htab = nullptr;
   uint32_t *hpos = nullptr;   // small table: first row position of each global slot

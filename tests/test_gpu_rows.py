@@ -79,3 +79,29 @@ def test_counts_of_many_small_graphs(mg, algo):
         elab, est = getattr(oracle, algo)(g, k=8)
         assert np.array_equal(labs[i].cpu().numpy(), elab), i
         assert per[i]["iterations"] == est.iterations and per[i]["edges_scanned"] == est.edges_scanned, i
+
+
+@pytest.mark.parametrize("kw,k", [({"mode": 0}, 8), ({"mode": 0, "exact_small": 64}, 8), ({"mode": 5}, 7),
+                                  ({"mode": 5}, 20000), ({"mode": 1, "short_rows": 2}, 16),
+                                  ({"mode": 3, "short_rows": 2}, 4), ({"mode": 1}, 32)])
+def test_short_row_classes(mg, kw, k):
+    """Rows on both sides of each class of the short rows' kernel (1 to 8 lanes per row),
+    the last of them ending with the arrays."""
+    import torch
+    degrees = [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 40, 64, 65] * 5
+    for tail in (1, 2, 4, 5, 31, 32):
+        g = hub_graph(degrees + [tail], 500, 6, seed=tail)
+        dg = mg.to_device(g)
+        rng = np.random.default_rng(k)
+        for groups in (3, 40, g.n):
+            C = rng.integers(0, groups, size=g.n).astype(np.int32)
+            tC = torch.from_numpy(C).to("cuda")
+            for algo, oalgo in ((mg.ALGO_LPA, oracle.ALGO_LPA), (mg.ALGO_LOUVAIN, oracle.ALGO_MOVE)):
+                Cn, gain, ctr = mg.move_sweep(dg, algo, tC, 0, k=k, **kw)
+                eC, eg = oracle.move_sweep(g, oalgo, C, mode=kw["mode"], k=k, direction=0)
+                assert np.array_equal(Cn.cpu().numpy(), eC), (tail, groups, algo)
+                assert ctr[0] == int((eC != C).sum())
+                if algo == mg.ALGO_LOUVAIN:
+                    assert np.array_equal(gain.cpu().numpy(), eg)
+            R = mg.refine(dg, tC, k=k, **kw)
+            assert np.array_equal(R.cpu().numpy(), oracle.refine(g, C, mode=kw["mode"], k=k)), (tail, groups)
