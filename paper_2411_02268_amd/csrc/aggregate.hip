@@ -56,8 +56,7 @@ int32_t renumber(const int32_t *C, int32_t n, int32_t *D, Arena &a, hipStream_t 
   k_dense_map<<<grid_for(n), BLOCK, 0, st>>>(C, dense, n, D, gid, keep);
   MGCD_LAUNCHED();
   int64_t m = 0;
-  MGCD_HIP(hipMemcpyAsync(&m, dense + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(&m, dense + n, sizeof(int64_t), st);
   a.release(mk);
   return (int32_t)m;
 }
@@ -360,8 +359,7 @@ int32_t canonical(const int32_t *C, int32_t n, int32_t *out, Arena &a, hipStream
   k_canon<<<grid_for(n), BLOCK, 0, st>>>(C, minv, rank, n, out);
   MGCD_LAUNCHED();
   int64_t m = 0;
-  MGCD_HIP(hipMemcpyAsync(&m, rank + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(&m, rank + n, sizeof(int64_t), st);
   a.release(mk);
   return (int32_t)m;
 }
@@ -1315,8 +1313,7 @@ static void launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t st) {
 
 static int64_t read_i64(const int64_t *p, hipStream_t st) {
   int64_t h = 0;
-  MGCD_HIP(hipMemcpyAsync(&h, p, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(&h, p, sizeof(int64_t), st);
   return h;
 }
 

@@ -142,8 +142,7 @@ struct Batch {
 
 static unsigned long long read_u64(const unsigned long long *p, hipStream_t st) {
   unsigned long long h = 0;
-  MGCD_HIP(hipMemcpyAsync(&h, p, sizeof(h), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(&h, p, sizeof(h), st);
   return h;
 }
 
@@ -184,8 +183,7 @@ static void write_selected(Batch &b, const int32_t *lab, const std::vector<uint8
   k_gather_i64<<<grid_for(b.count + 1), BLOCK, 0, st>>>(rank, pos_d, val_d, b.count + 1);
   MGCD_LAUNCHED();
   std::vector<int64_t> val(b.count + 1);
-  MGCD_HIP(hipMemcpyAsync(val.data(), val_d, val.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(val.data(), val_d, val.size() * sizeof(int64_t), st);
   for (int32_t g = 0; g < b.count; ++g)
     if (sel[g]) comms[g] = val[g + 1] - val[g];
   a.release(mk);
@@ -346,8 +344,7 @@ static void level_sweeps(LevelSweeps &L, const mgcd_params *p, const Schedule &s
     issue(st);
   }
   uint32_t h[2] = {0, 0};
-  MGCD_HIP(hipMemcpyAsync(h, L.lv, sizeof(h), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(h, L.lv, sizeof(h), st);
   if (h[1] % 2 == 1) std::swap(L.C[0], L.C[1]);  // an odd count of real sweeps ends in C[1]
 }
 
@@ -398,8 +395,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
       MGCD_LAUNCHED();
     }
     int32_t hb = count;
-    MGCD_HIP(hipMemcpyAsync(&hb, bad, sizeof(hb), hipMemcpyDeviceToHost, st));
-    MGCD_HIP(hipStreamSynchronize(st));
+    read_back(&hb, bad, sizeof(hb), st);
     if (hb < count) throw Error(MGCD_E_GRAPH, "graph " + std::to_string(hb) + " failed validation");
   }
   b.gid0 = a.take<int32_t>(N);
@@ -430,8 +426,11 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
       MGCD_LAUNCHED();
     }
     std::vector<unsigned long long> hw(count);
-    MGCD_HIP(hipMemcpyAsync(hw.data(), Wg64, count * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    const unsigned long long wall = read_u64(Wtot, st);
+    unsigned long long wall = 0;
+    HostRead rd(st);
+    rd.add(hw.data(), Wg64, count * sizeof(unsigned long long));
+    rd.add(&wall, Wtot, sizeof(wall));
+    rd.wait();
     // W_g sums the rows' K, which are 32-bit: a row of 2^32 or more would wrap and
     // drop below its true weight, so the W_g must add up to the exact (64-bit) total
     unsigned long long wsum = 0;
@@ -446,8 +445,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
   std::vector<uint64_t> W(count);
   {
     std::vector<unsigned long long> hw(count);
-    MGCD_HIP(hipMemcpyAsync(hw.data(), Wg64, count * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    MGCD_HIP(hipStreamSynchronize(st));
+    read_back(hw.data(), Wg64, count * sizeof(unsigned long long), st);
     for (int32_t g = 0; g < count; ++g) W[g] = hw[g];
   }
 
@@ -475,8 +473,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
   // per-level stats from the device: sweeps, entries, movers per graph
   auto collect = [&](const std::vector<uint8_t> &was_active) {
     std::vector<long long> h(3 * (size_t)count);
-    MGCD_HIP(hipMemcpyAsync(h.data(), stat, h.size() * sizeof(long long), hipMemcpyDeviceToHost, st));
-    MGCD_HIP(hipStreamSynchronize(st));
+    read_back(h.data(), stat, h.size() * sizeof(long long), st);
     long long sweeps = 0;
     for (int32_t g = 0; g < count; ++g) {
       if (!was_active[g] || h[3 * g] == 0) continue;
@@ -593,8 +590,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
       k_gather_i64<<<grid_for(count + 1), BLOCK, 0, st>>>(dense, tmp_d, nb_d, count + 1);
       MGCD_LAUNCHED();
       std::vector<int64_t> db(count + 1);
-      MGCD_HIP(hipMemcpyAsync(db.data(), nb_d, db.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipStreamSynchronize(st));
+      read_back(db.data(), nb_d, db.size() * sizeof(int64_t), st);
       std::vector<uint8_t> stop(count, 0);
       bool cont = false;
       for (int32_t g = 0; g < count; ++g) {
@@ -625,8 +621,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
       MGCD_LAUNCHED();
       k_gather_i64<<<grid_for(count + 1), BLOCK, 0, st>>>(dense, tmp_d, nb_d, count + 1);
       MGCD_LAUNCHED();
-      MGCD_HIP(hipMemcpyAsync(db.data(), nb_d, db.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipStreamSynchronize(st));
+      read_back(db.data(), nb_d, db.size() * sizeof(int64_t), st);
       auto &sl = slot[next_slot];
       const int64_t nnz2 = aggregate(cur, D, m, agg_mode(p), p->k_aggregate, p->chunk_len, 0, sl.off, sl.idx,
                                      sl.w, a, st);
@@ -657,8 +652,7 @@ void run_batched(int algo, const mgcd_csr *graphs, int32_t count, const mgcd_par
       k_gather_i64<<<grid_for(count + 1), BLOCK, 0, st>>>(sl.off, tmp_d, nb_d, count + 1);
       MGCD_LAUNCHED();
       std::vector<int64_t> eb2(count + 1);
-      MGCD_HIP(hipMemcpyAsync(eb2.data(), nb_d, eb2.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipStreamSynchronize(st));
+      read_back(eb2.data(), nb_d, eb2.size() * sizeof(int64_t), st);
       for (int32_t g = 0; g < count; ++g) nnz_cur[g] = finished[g] ? 0 : eb2[g + 1] - eb2[g];
       std::swap(gid_cur, gid_next);
       ms_agg += tm.stop();

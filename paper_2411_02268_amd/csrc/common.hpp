@@ -4,6 +4,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -96,6 +97,66 @@ struct Arena {
   void release(size_t m) { used = m; }
 };
 
+// ---- small reads from the device (host) ---------------------------------------------
+// Results that the host waits for land in pinned memory first: a copy into pageable
+// memory is staged by the runtime and its round trip takes 22 us, into pinned memory 14.
+// A read leases a pinned block for its own duration from a pool of at most POOL_BLOCKS
+// (any thread, stream and device; a block beyond the pool is freed at once).
+constexpr size_t PINNED_BYTES = 16 * 1024;
+void *pinned_lease();            // null when none can be had: the read is pageable then
+void pinned_return(void *block);
+inline thread_local bool no_pinned = false;  // this thread's calls may not allocate
+
+struct HostRead {
+  explicit HostRead(hipStream_t s) : st(s) {}
+  HostRead(const HostRead &) = delete;
+  HostRead &operator=(const HostRead &) = delete;
+  ~HostRead() {
+    if (!block) return;
+    if (count) (void)hipStreamSynchronize(st);  // an error on the way: nothing may still write to it
+    pinned_return(block);
+  }
+  void add(void *dst, const void *src, size_t bytes) {
+    if (!block && !tried && !no_pinned) {
+      block = static_cast<char *>(pinned_lease());
+      tried = true;
+    }
+    if (!block || count == MAX || used + bytes > PINNED_BYTES) {
+      MGCD_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st));
+      return;
+    }
+    piece[count++] = Piece{dst, used, bytes};
+    MGCD_HIP(hipMemcpyAsync(block + used, src, bytes, hipMemcpyDeviceToHost, st));
+    used += (bytes + 15) & ~(size_t)15;
+  }
+  void wait() {
+    MGCD_HIP(hipStreamSynchronize(st));
+    for (int q = 0; q < count; ++q) std::memcpy(piece[q].dst, block + piece[q].at, piece[q].bytes);
+    count = 0;
+    used = 0;
+  }
+
+ private:
+  static constexpr int MAX = 4;
+  struct Piece {
+    void *dst;
+    size_t at, bytes;
+  };
+  hipStream_t st;
+  char *block = nullptr;
+  bool tried = false;
+  size_t used = 0;
+  int count = 0;
+  Piece piece[MAX];
+};
+
+// Copies device memory to the host and waits for the stream.
+inline void read_back(void *dst, const void *src, size_t bytes, hipStream_t st) {
+  HostRead r(st);
+  r.add(dst, src, bytes);
+  r.wait();
+}
+
 // ---- device time of a stretch of stream work (host) --------------------------------
 struct Timer {
   hipEvent_t a = nullptr, b = nullptr;
@@ -116,6 +177,40 @@ struct Timer {
     MGCD_HIP(hipEventElapsedTime(&ms, a, b));
     return ms;
   }
+};
+
+// ---- device time by phase (host): one event per boundary, read once at the end -----------
+struct PhaseClock {
+  explicit PhaseClock(hipStream_t s) : st(s) { mark(-1); }
+  ~PhaseClock() {
+    for (hipEvent_t e : ev) (void)hipEventDestroy(e);
+  }
+  // The stream's work since the last mark belongs to phase p (< 0: to none).
+  void mark(int p) {
+    hipEvent_t e = nullptr;
+    MGCD_HIP(hipEventCreate(&e));
+    ev.push_back(e);
+    phase.push_back(p);
+    MGCD_HIP(hipEventRecord(e, st));
+  }
+  // Milliseconds of phases 0 .. n - 1 into ms; returns the time from first to last mark.
+  float read(float *ms, int n) {
+    MGCD_HIP(hipEventSynchronize(ev.back()));
+    float total = 0;
+    for (int q = 0; q < n; ++q) ms[q] = 0;
+    for (size_t x = 1; x < ev.size(); ++x) {
+      float t = 0;
+      MGCD_HIP(hipEventElapsedTime(&t, ev[x - 1], ev[x]));
+      if (phase[x] >= 0 && phase[x] < n) ms[phase[x]] += t;
+      total += t;
+    }
+    return total;
+  }
+
+ private:
+  hipStream_t st;
+  std::vector<hipEvent_t> ev;
+  std::vector<int> phase;
 };
 
 // ---- wave helpers (device) -------------------------------------------------------
@@ -175,8 +270,7 @@ __device__ inline int spread_copy() { return (int)(blockIdx.x & (SPREAD - 1)); }
 inline void read_spread(const unsigned long long *dev, int nsum, unsigned long long *out,
                         hipStream_t st) {
   std::vector<unsigned long long> h((size_t)SPREAD * (nsum + 1));
-  MGCD_HIP(hipMemcpyAsync(h.data(), dev, h.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(h.data(), dev, h.size() * sizeof(unsigned long long), st);
   for (int q = 0; q <= nsum; ++q) out[q] = 0;
   for (int c = 0; c < SPREAD; ++c) {
     const unsigned long long *x = h.data() + (size_t)c * (nsum + 1);

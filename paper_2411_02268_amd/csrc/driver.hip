@@ -34,10 +34,46 @@ void set_last_error(const std::string &msg) { g_last_error = msg; }
 // where it is.
 constexpr int SEG = 4;
 
-// Per-kernel-class device time of level-0 sweeps: four events per sweep of a segment.
+// ---- pinned blocks of HostRead --------------------------------------------------------
+constexpr size_t POOL_BLOCKS = 32;
+static std::mutex g_pinned_mu;
+static std::vector<void *> g_pinned;  // free blocks
+
+void *pinned_lease() {
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if (!g_pinned.empty()) {
+      void *p = g_pinned.back();
+      g_pinned.pop_back();
+      return p;
+    }
+  }
+  void *p = nullptr;
+  if (hipHostMalloc(&p, PINNED_BYTES, hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+
+void pinned_return(void *block) {
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if (g_pinned.size() < POOL_BLOCKS) {
+      g_pinned.push_back(block);
+      return;
+    }
+  }
+  (void)hipHostFree(block);
+}
+
+// Device time of the level-0 sweeps by kernel class: by the device clock where a sweep is
+// one class (LevelState::ticks), else by events around the classes that have kernels.
 struct ClassTimer {
   hipEvent_t ev[SEG][4] = {};
-  ClassTimer() {
+  const Schedule *sch = nullptr;
+  explicit ClassTimer(const Schedule *s) : sch(s) {
+    if (!timed()) return;
     for (auto &row : ev)
       for (auto &e : row) MGCD_HIP(hipEventCreate(&e));
   }
@@ -46,13 +82,24 @@ struct ClassTimer {
       for (auto &e : row)
         if (e) (void)hipEventDestroy(e);
   }
+  bool timed() const { return sch && !sch->clock; }
+  hipEvent_t *events(int j) { return timed() ? ev[j] : nullptr; }
   void add(mgcd_stats &s, int j) {  // after sweep j of the segment has completed
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 3 && timed(); ++q) {
+      if (!(sch->classes >> q & 1u)) continue;
       float ms = 0;
       MGCD_HIP(hipEventElapsedTime(&ms, ev[j][q], ev[j][q + 1]));
       s.ms_l0_kernel[q] += ms;
     }
     s.l0_sweeps += 1;
+  }
+  void finish(mgcd_stats &s, const LevelState &h) {  // the level's ticks, to its only class
+    if (!sch || !sch->clock) return;
+    int dev = 0, khz = 0;
+    MGCD_HIP(hipGetDevice(&dev));
+    MGCD_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+    const int q = sch->classes == 4u ? 2 : 0;
+    if (khz > 0) s.ms_l0_kernel[q] += (float)((double)h.ticks / khz);
   }
 };
 
@@ -112,8 +159,7 @@ static Graph view(const mgcd_csr *g) {
 template <typename T>
 static T read_dev(const T *p, hipStream_t st) {
   T h{};
-  MGCD_HIP(hipMemcpyAsync(&h, p, sizeof(T), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(&h, p, sizeof(T), st);
   return h;
 }
 
@@ -149,8 +195,7 @@ struct Counts {
 
 static Counts read_counts(const unsigned long long *ctr, hipStream_t st) {
   std::vector<unsigned long long> h(CTR_WORDS);
-  MGCD_HIP(hipMemcpyAsync(h.data(), ctr, CTR_WORDS * sizeof(h[0]), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(h.data(), ctr, CTR_WORDS * sizeof(h[0]), st);
   Counts c{0, 0, 0};
   for (int x = 0; x < SPREAD; ++x) {
     c.moved += h[(size_t)x * CTR_STRIDE];
@@ -192,8 +237,7 @@ static void run_lpa(const mgcd_csr *gin, const mgcd_params *p, int32_t *out, Are
   check_params(p);
   Graph g = view(gin);
   const int32_t n = g.n;
-  Timer total(st), lm(st);
-  total.start();
+  PhaseClock clock(st);
   uint32_t *K = a.take<uint32_t>(n);
   prepare(g, p, K, a, st);
   int32_t *Ca = a.take<int32_t>(n), *Cb = a.take<int32_t>(n);
@@ -217,34 +261,37 @@ static void run_lpa(const mgcd_csr *gin, const mgcd_params *p, int32_t *out, Are
   Schedule sch;
   build_schedule(gs, sched_params(p), sch, a, st);
   LevelState *ls = a.take<LevelState>(1);
+  uint64_t *stamp = a.take<uint64_t>(1);
   mgcd_stats s{};
-  ClassTimer ct;
-  lm.start();
-  launch_zero_u64(ctr, CTR_WORDS, st);
-  launch_zero_state(ls, st);
+  ClassTimer ct(&sch);
+  clock.mark(-1);
+  launch_level_start(ls, ctr, st);
   if (n > 0) {
     LevelState h = run_sweeps(p->max_iterations, ls, st, &ct, s, false, [&](int it, int j) {
       SweepArgs args{gs, Ca, nullptr, Ks, nullptr, 0, 0, Cb, nullptr, ctr};
       args.halt = &ls->halt;
       args.one_scan = p->one_scan;
       args.ident = !sto && it == 0;  // every vertex starts alone (on the copy: C = perm)
-      launch_sweep(args, sch, ALGO_LPA, p->mode, p->k, p->chunk_len, st, ct.ev[j]);
-      launch_level_converge(ALGO_LPA, LevelRule{ctr, ls, g.nnz, n, p->tolerance, 0.0}, st);
+      LevelRule rule{ctr, ls, g.nnz, n, p->tolerance, 0.0};
+      if (sch.clock) rule.stamp = args.stamp = stamp;
+      launch_sweep(args, sch, ALGO_LPA, p->mode, p->k, p->chunk_len, st, ct.events(j));
+      launch_level_converge(ALGO_LPA, rule, st);
       std::swap(Ca, Cb);  // a halted sweep copies C, so either buffer holds the result
     });
     s.iterations = h.sweeps;
     s.edges_scanned = (int64_t)h.edges;
     s.moved_last = (int64_t)h.moved_last;
+    ct.finish(s, h);
   }
   if (sto) {  // back to vertices: C[v] = Ca[pos[v]]
     launch_compose(sc.pos, Ca, Ck, n, st);
     Ca = Ck;
   }
-  const float ms_lm = lm.stop();
+  clock.mark(0);
   s.communities = canonical(Ca, n, out, a, st);
   s.passes = 1;
-  s.ms_local_move = ms_lm;
-  s.ms_total = total.stop();
+  clock.mark(-1);
+  s.ms_total = clock.read(&s.ms_local_move, 1);
   if (stats) *stats = s;
 }
 
@@ -257,8 +304,7 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
   Graph g0 = view(gin);
   const int32_t n = g0.n;
   const int64_t nnz = g0.nnz;
-  Timer total(st), tm(st);
-  total.start();
+  PhaseClock clock(st);  // phases: 0 local moving, 1 refinement, 2 aggregation
   mgcd_stats s{};
   uint32_t *Kbuf[2] = {a.take<uint32_t>(n), a.take<uint32_t>(n)};
   const uint64_t W = prepare(g0, p, Kbuf[0], a, st);
@@ -271,6 +317,7 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
   int32_t *from = leiden ? a.take<int32_t>(n) : nullptr;
   unsigned long long *ctr = a.take<unsigned long long>(CTR_WORDS);
   LevelState *ls = a.take<LevelState>(1);
+  uint64_t *stamp = a.take<uint64_t>(1);
   struct Slot {
     int64_t *off;
     int32_t *idx;
@@ -286,16 +333,14 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
   Graph cur = g0;
   int kcur = 0, next_slot = 0;
   double tol = p->tolerance;
-  float ms_lm = 0, ms_ref = 0, ms_agg = 0;
   const double WW = (double)W * (double)W;
-  ClassTimer ct;
+  clock.mark(-1);
   for (int pass = 0; pass < p->max_passes && n > 0; ++pass) {
     const int32_t nl = cur.n;
     uint32_t *K = Kbuf[kcur];
     s.passes += 1;
     size_t mark = a.mark();
     Schedule sch;
-    tm.start();
     if (!leiden) launch_iota(Ca, nl, st);
     // level 0 may move on the degree-ordered copy: labels by position whose values are
     // the communities' own ids (keys, ties, directions and Sigma unchanged)
@@ -316,8 +361,8 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
     // rows without entries are in no sweep: both label buffers start equal
     if (nl > 0) MGCD_HIP(hipMemcpyAsync(Cb, Ca, (size_t)nl * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     launch_community_totals(Ca, Km, Sig, nl, st);
-    launch_zero_u64(ctr, CTR_WORDS, st);
-    launch_zero_state(ls, st);
+    launch_level_start(ls, ctr, st);
+    ClassTimer ct(pass == 0 ? &sch : nullptr);
     LevelState h = run_sweeps(p->max_iterations, ls, st, pass == 0 ? &ct : nullptr, s,
                               pass > 0 && nl <= GROW_MAX_N, [&](int it, int j) {
       SweepArgs args{gm, Ca, nullptr, Km, Sig, W, (it % 2 == 0) ? -1 : 1, Cb, nullptr, ctr};
@@ -325,10 +370,13 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
       // a level starts from singletons (Leiden after its first: from the refined
       // partition's communities); on the copy C holds perm, not positions
       args.ident = !sto && it == 0 && (!leiden || pass == 0);
-      launch_sweep(args, sch, ALGO_MOVE, p->mode, p->k, p->chunk_len, st, pass == 0 ? ct.ev[j] : nullptr);
+      const bool ticks = pass == 0 && sch.clock;
+      if (ticks) args.stamp = stamp;
+      launch_sweep(args, sch, ALGO_MOVE, p->mode, p->k, p->chunk_len, st, pass == 0 ? ct.events(j) : nullptr);
       // a sweep without positive moves, or a halted one, leaves C_new equal to C; the
       // same launch applies the stopping rule to this sweep's counters
-      const LevelRule rule{ctr, ls, cur.nnz, nl, tol, WW};
+      LevelRule rule{ctr, ls, cur.nnz, nl, tol, WW};
+      if (ticks) rule.stamp = stamp;
       launch_apply_moves(Ca, Cb, Km, Sig, nl, st, &rule);
       std::swap(Ca, Cb);
     });
@@ -338,40 +386,40 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
       Cb = Cw;
       if (leiden) build_schedule(cur, sched_params(p), sch, a, st);
     }
-    ms_lm += tm.stop();
-    if (pass == 0) s.l0_candidates = (int64_t)h.cands;
+    clock.mark(0);
+    if (pass == 0) {
+      s.l0_candidates = (int64_t)h.cands;
+      ct.finish(s, h);
+    }
     s.iterations += h.sweeps;
     s.edges_scanned += (int64_t)h.edges;
     s.moved_last = (int64_t)h.moved_last;
     int32_t m;
     bool last;
     if (leiden) {
-      tm.start();
       SweepArgs r{cur, nullptr, Ca, K, K, W, 0, prop, nullptr, ctr};
       launch_iota(prop, nl, st);  // a row without entries proposes itself
       launch_zero_u64(ctr, CTR_WORDS, st);
       launch_sweep(r, sch, ALGO_REFINE, p->mode, p->k, p->chunk_len, st);
       launch_refine_accept(prop, nprop, from, Cb, nl, st);  // Cb <- refined R
-      ms_ref += tm.stop();
+      clock.mark(1);
       a.release(mark);
-      tm.start();
       m = renumber(Cb, nl, D, a, st);
       last = pass == p->max_passes - 1 || (double)m > p->aggregation_tolerance * (double)nl;
       if (last) {
         launch_compose(top, Ca, top, n, st);  // final community of every input vertex
-        ms_agg += tm.stop();
+        clock.mark(2);
         break;
       }
       renumber(Ca, nl, Dc, a, st);
       launch_compose(top, D, top, n, st);
     } else {
       a.release(mark);
-      tm.start();
       m = renumber(Ca, nl, D, a, st);
       launch_compose(top, D, top, n, st);
       last = pass == p->max_passes - 1 || (double)m > p->aggregation_tolerance * (double)nl;
       if (last) {
-        ms_agg += tm.stop();
+        clock.mark(2);
         break;
       }
     }
@@ -383,17 +431,19 @@ static void run_levels(bool leiden, const mgcd_csr *gin, const mgcd_params *p, i
       launch_scatter_labels(D, Dc, Cb, nl, st);  // super-vertex starts in its community
       std::swap(Ca, Cb);
     }
-    ms_agg += tm.stop();
+    clock.mark(2);
     cur = Graph{m, nnz2, sl.off, sl.idx, sl.w};
     next_slot = 1 - next_slot;
     kcur = 1 - kcur;
     tol /= p->tolerance_drop;
   }
   s.communities = canonical(top, n, out, a, st);
-  s.ms_local_move = ms_lm;
-  s.ms_refine = ms_ref;
-  s.ms_aggregate = ms_agg;
-  s.ms_total = total.stop();
+  clock.mark(-1);
+  float ms[3];
+  s.ms_total = clock.read(ms, 3);
+  s.ms_local_move = ms[0];
+  s.ms_refine = ms[1];
+  s.ms_aggregate = ms[2];
   if (stats) *stats = s;
 }
 
@@ -465,8 +515,11 @@ static void modularity_in(const Graph &g, const int32_t *C, double *q, void *ws,
   launch_degrees(g, K, Wd, a, st);
   modularity_terms(g, C, K, terms, a, st);
   unsigned long long ht[2 * SPREAD], h[2] = {0, 0};
-  MGCD_HIP(hipMemcpyAsync(ht, terms, sizeof(ht), hipMemcpyDeviceToHost, st));
-  uint64_t W = read_dev(Wd, st);
+  unsigned long long W = 0;
+  HostRead rd(st);
+  rd.add(ht, terms, sizeof(ht));
+  rd.add(&W, Wd, sizeof(W));
+  rd.wait();
   for (int c = 0; c < SPREAD; ++c) {
     h[0] += ht[2 * c];
     h[1] += ht[2 * c + 1];
@@ -631,6 +684,10 @@ int modularity_noalloc(const mgcd_csr *gin, const int32_t *C, double *q, void *s
                                         std::to_string(need) + " bytes of its " +
                                         std::to_string(NOALLOC_SCRATCH_BYTES) + "-byte device scratch)");
     hipStream_t st = (hipStream_t)stream;
+    struct NoPinned {  // the call allocates nothing, pinned host memory included
+      NoPinned() { no_pinned = true; }
+      ~NoPinned() { no_pinned = false; }
+    } guard;
     modularity_in(g, C, q, scratch_of_stream(st), NOALLOC_SCRATCH_BYTES, st);
   });
 }

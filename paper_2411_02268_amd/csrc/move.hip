@@ -272,6 +272,11 @@ __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
   }
 }
 
+// The device clock at the start of a sweep of one kernel class (SweepArgs::stamp).
+__device__ inline void stamp_start(const SweepArgs &a) {
+  if (a.stamp && blockIdx.x == 0 && threadIdx.x == 0) *a.stamp = wall_clock64();
+}
+
 // Key of entry (i -> j) in the stream of vertex i, or EMPTY when Algorithm 1's
 // early exits skip it (self-loop; refinement across bounds).
 template <int ALGO>
@@ -1103,6 +1108,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_
                 int64_t nlight, unsigned long long *queue) {
   __shared__ RowShare<K> S;
   Counters ct;
+  stamp_start(a);
   if constexpr (!PERSIST) {
     if (blockIdx.x < total) {
       row_item<K, ALGO, MODE>(a, bk, L, keybuf, S, blockIdx.x, ct);
@@ -1143,6 +1149,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ligh
     k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, unsigned long long *queue) {
   const int64_t wave = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
+  stamp_start(a);
   if constexpr (!PERSIST) {
     light_item<K, ALGO, MODE>(a, rows, nrows, wave, ct);
     flush_counters(a, ct);
@@ -1621,6 +1628,7 @@ template <int ALGO, bool SMALL>
 __global__ void __launch_bounds__(BLOCK) k_exact_short(SweepArgs a, const int32_t *__restrict__ list, ShortRows sr) {
   if (level_over(a)) return;  // batched: every graph has stopped
   Counters ct;
+  stamp_start(a);
   const int64_t w = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   if (w < sr.wave[1])
     short_item<ALGO, SMALL, 8>(a, list, sr.row[1], w, ct);
@@ -2280,7 +2288,7 @@ size_t schedule_ws_bytes(int32_t n, int64_t nnz, int mode, int k, int64_t L) {
   return b + 64 * 1024;
 }
 
-void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena &a, hipStream_t st) {
+static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena &a, hipStream_t st) {
   SchedParams sp = sp_in;
   if (sp.short_auto && g.nnz > sp.mg_short * (int64_t)g.n) sp.mg_short = 0;
   const int mode = sp.mode, k = sp.k;
@@ -2326,8 +2334,7 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
       k_chunk_counts<<<grid_for(s.nmulti), BLOCK, 0, st>>>(g.off, s.multi, s.nmulti, L, nch);
       MGCD_LAUNCHED();
       scan_i64(nch, s.cstart, s.nmulti, s.cstart + s.nmulti, a, st);
-      MGCD_HIP(hipMemcpyAsync(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipStreamSynchronize(st));
+      read_back(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), st);
       s.owner = a.take<int32_t>(s.nchunks);
       k_chunk_owner<<<(unsigned)s.nmulti, BLOCK, 0, st>>>(s.cstart, s.nmulti, s.owner);
       MGCD_LAUNCHED();
@@ -2362,10 +2369,11 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
       MGCD_LAUNCHED();
       scan_i64(ntab, s.tstart, c3, s.tstart + c3, a, st);
       int64_t tot = 0;  // table slots, insert and scan segments in one host round trip
-      MGCD_HIP(hipMemcpyAsync(&tot, s.hbase + c3, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipMemcpyAsync(&s.nseg, s.sstart + c3, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipMemcpyAsync(&s.ntseg, s.tstart + c3, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      MGCD_HIP(hipStreamSynchronize(st));
+      HostRead rd(st);
+      rd.add(&tot, s.hbase + c3, sizeof(int64_t));
+      rd.add(&s.nseg, s.sstart + c3, sizeof(int64_t));
+      rd.add(&s.ntseg, s.tstart + c3, sizeof(int64_t));
+      rd.wait();
       s.sowner = a.take<int32_t>(s.nseg);
       k_chunk_owner<<<(unsigned)c3, BLOCK, 0, st>>>(s.sstart, c3, s.sowner);
       MGCD_LAUNCHED();
@@ -2411,9 +2419,10 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
     MGCD_LAUNCHED();
     scan_i64(ng, s.gstart, s.nmulti, s.gstart + s.nmulti, a, st);
     // chunk and group totals in one host round trip
-    MGCD_HIP(hipMemcpyAsync(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    MGCD_HIP(hipMemcpyAsync(&s.ngroups, s.gstart + s.nmulti, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    MGCD_HIP(hipStreamSynchronize(st));
+    HostRead rd(st);
+    rd.add(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t));
+    rd.add(&s.ngroups, s.gstart + s.nmulti, sizeof(int64_t));
+    rd.wait();
     s.owner = a.take<int32_t>(s.nchunks);
     k_chunk_owner<<<(unsigned)s.nmulti, BLOCK, 0, st>>>(s.cstart, s.nmulti, s.owner);
     MGCD_LAUNCHED();
@@ -2449,10 +2458,42 @@ void build_schedule(const Graph &g, const SchedParams &sp_in, Schedule &s, Arena
   }
 }
 
+static void set_classes(Schedule &s, const SchedParams &sp);
+
+void build_schedule(const Graph &g, const SchedParams &sp, Schedule &s, Arena &a, hipStream_t st) {
+  build_lists(g, sp, s, a, st);
+  set_classes(s, sp);
+}
+
 // ---- launch -------------------------------------------------------------------------
 
-static inline void mark(hipEvent_t *ev, int i, hipStream_t st) {
-  if (ev) MGCD_HIP(hipEventRecord(ev[i], st));
+// Event i of a sweep bounds the kernel classes i - 1 and i: recorded (4 us of the stream's
+// time each) only where one of them has kernels.
+static inline void mark(const Schedule &s, hipEvent_t *ev, int i, hipStream_t st) {
+  if (ev && (s.classes & (1u << i | (i > 0 ? 1u << (i - 1) : 0u)) & 7u)) MGCD_HIP(hipEventRecord(ev[i], st));
+}
+
+// The kernel classes that a sweep on this schedule has (bits, as launched below); `clock`:
+// one class, whose first kernel writes SweepArgs::stamp.
+static void set_classes(Schedule &s, const SchedParams &sp) {
+  const bool shorts = s.ntail > 0 || s.shorts.wave[4] > 0;
+  bool c[3];
+  if (sp.wave) {
+    c[0] = shorts;
+    c[1] = s.ntier[1] > 0;
+    c[2] = s.nmulti > 0;
+  } else if (sp.mode == MODE_EXACT) {
+    c[0] = shorts;
+    c[1] = s.ntier[1] > 0 || s.ntier[2] > 0;
+    c[2] = s.ntier[3] > 0;
+  } else {
+    c[0] = s.ngroups + s.row_items > 0 || s.nlight > 0;
+    c[1] = s.nmulti > 0;
+    c[2] = shorts;
+  }
+  s.classes = (c[0] ? 1u : 0u) | (c[1] ? 2u : 0u) | (c[2] ? 4u : 0u);
+  const bool mg = !sp.wave && sp.mode != MODE_EXACT;
+  s.clock = (s.classes == 1u && (mg || s.ntail == 0)) || (mg && s.classes == 4u);
 }
 
 // Compute units of the current device.
@@ -2508,9 +2549,9 @@ static void launch_short(const SweepArgs &a, const Schedule &s, hipStream_t st) 
 
 template <int K, int ALGO, int MODE>
 static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st, hipEvent_t *ev) {
-  mark(ev, 0, st);
+  mark(s, ev, 0, st);
   launch_rows<K, ALGO, MODE>(a, s, L, st);
-  mark(ev, 1, st);
+  mark(s, ev, 1, st);
   // long rows: rest of the merge tree, pass 2, decision
   if (s.nmulti > 0) {
     k_long_merge<K, ALGO><<<(unsigned)s.nmulti, BLOCK, 0, st>>>(a, s.multi, s.gstart, s.sk,
@@ -2523,16 +2564,16 @@ static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream
                                                                  s.cflag, s.part);
     MGCD_LAUNCHED();
   }
-  mark(ev, 2, st);
+  mark(s, ev, 2, st);
   launch_short<ALGO>(a, s, st);  // rows whose sketch is their exact table
-  mark(ev, 3, st);
+  mark(s, ev, 3, st);
 }
 
 template <int ALGO, bool SMALL = false>
 static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, hipEvent_t *ev) {
-  mark(ev, 0, st);
+  mark(s, ev, 0, st);
   launch_short<ALGO, SMALL>(a, s, st);
-  mark(ev, 1, st);
+  mark(s, ev, 1, st);
   if (s.ntier[1] > 0) {
     k_exact_wave<ALGO, SMALL><<<(unsigned)ceil_div(s.ntier[1], BLOCK / WAVE), BLOCK, 0, st>>>(
         a, s.tier[1], s.ntier[1]);
@@ -2542,7 +2583,7 @@ static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, h
     k_exact_table<ALGO, 8192, SMALL><<<(unsigned)s.ntier[2], BLOCK, 0, st>>>(a, s.tier[2]);
     MGCD_LAUNCHED();
   }
-  mark(ev, 2, st);
+  mark(s, ev, 2, st);
   if (s.ntier[3] > 0) {
     k_gtab_insert<ALGO, SMALL><<<(unsigned)s.nseg, BLOCK, 0, st>>>(a, s.tier[3], s.hbase, s.sstart, s.sowner,
                                                                   s.htab, s.hpos);
@@ -2556,14 +2597,14 @@ static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, h
                                                                 s.pgain);
     MGCD_LAUNCHED();
   }
-  mark(ev, 3, st);
+  mark(s, ev, 3, st);
 }
 
 template <int K, int ALGO, int MODE>
 static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStream_t st, hipEvent_t *ev) {
-  mark(ev, 0, st);
+  mark(s, ev, 0, st);
   launch_short<ALGO>(a, s, st);  // rows that cannot lose weight
-  mark(ev, 1, st);
+  mark(s, ev, 1, st);
   if constexpr (K <= WAVE) {  // K = 128 / 256: every row the sketch takes is a split row
     if (s.ntier[1] > 0) {
       const unsigned grid = (unsigned)ceil_div(s.ntier[1], BLOCK / WAVE);
@@ -2575,7 +2616,7 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
       MGCD_LAUNCHED();
     }
   }
-  mark(ev, 2, st);
+  mark(s, ev, 2, st);
   if (s.nmulti > 0) {  // split rows
     const unsigned cgrid = (unsigned)ceil_div(s.nchunks, BLOCK / WAVE);
     k_wave_chunks<K, ALGO, MODE><<<cgrid, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L,
@@ -2596,7 +2637,7 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
         a, s.multi, s.cstart, s.nmulti, s.wnode, s.wflag, s.wcount);
     MGCD_LAUNCHED();
   }
-  mark(ev, 3, st);
+  mark(s, ev, 3, st);
 }
 
 template <int ALGO, int MODE>
@@ -2661,6 +2702,10 @@ __device__ inline void level_converge(int algo, const LevelRule &r) {
   ls->sweeps += 1;
   ls->edges += (unsigned long long)r.nnz;
   ls->moved_last = moved;
+  if (r.stamp) {
+    const uint64_t now = wall_clock64(), then = *r.stamp;
+    ls->ticks += now > then ? now - then : 0;
+  }
   const bool stop = algo == ALGO_LPA ? (double)moved <= r.tol * (double)r.n
                                      : prop == 0 || 2.0 * (double)sumG <= r.tol * r.WW;
   if (stop) ls->halt = 1;
@@ -2751,10 +2796,15 @@ void launch_level_converge(int algo, const LevelRule &r, hipStream_t st) {
   MGCD_LAUNCHED();
 }
 
-__global__ void k_zero_state(LevelState *ls) { *ls = LevelState{0, 0, 0, 0, 0}; }
+// A level's start: its state and the sweep counters (may be null) cleared.
+__global__ void k_level_start(LevelState *ls, unsigned long long *ctr) {
+  if (threadIdx.x == 0) *ls = LevelState{0, 0, 0, 0, 0, 0};
+  if (ctr)
+    for (int64_t i = threadIdx.x; i < CTR_WORDS; i += BLOCK) ctr[i] = 0;
+}
 
-void launch_zero_state(LevelState *ls, hipStream_t st) {
-  k_zero_state<<<1, 1, 0, st>>>(ls);
+void launch_level_start(LevelState *ls, unsigned long long *ctr, hipStream_t st) {
+  k_level_start<<<1, BLOCK, 0, st>>>(ls, ctr);
   MGCD_LAUNCHED();
 }
 

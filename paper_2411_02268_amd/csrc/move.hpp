@@ -56,6 +56,9 @@ struct SweepArgs {
   // starts from singletons): the kernels may take a neighbour's community as j without
   // reading C, which must still hold the identity.
   int32_t ident = 0;
+  // Device clock of the sweep's start, written by its first kernel (schedules with
+  // `clock`); null: not asked for.
+  uint64_t *stamp = nullptr;
 };
 
 // The table key of community (or vertex) c: itself, or its slot in the small table.
@@ -76,6 +79,7 @@ struct LevelState {
   unsigned long long edges;
   unsigned long long moved_last;
   unsigned long long cands;
+  unsigned long long ticks;  // device clock spent in the counted sweeps (LevelRule::stamp)
 };
 // A level's stopping rule: LPA stops when movers <= tol * n, Louvain local moving
 // when no vertex has a positive move or 2 * summed gain <= tol * W^2 (WW = W^2).
@@ -88,10 +92,11 @@ struct LevelRule {
   int32_t n = 0;
   double tol = 0, WW = 0;
   const uint32_t *live = nullptr;  // batched: 0 graphs moving -> no Sigma update
+  const uint64_t *stamp = nullptr;  // the sweep's start: the time since then is counted
 };
 // After a sweep: apply the rule to the sweep's counters and update the state.
 void launch_level_converge(int algo, const LevelRule &r, hipStream_t st);
-void launch_zero_state(LevelState *ls, hipStream_t st);
+void launch_level_start(LevelState *ls, unsigned long long *ctr, hipStream_t st);
 
 // The persistent main sweep kernel's work queue: QLANES counters, each on a cache line
 // of its own (QSTRIDE u64 apart); counter c hands out work items c, c + QLANES, ...
@@ -156,6 +161,8 @@ struct Schedule {
   Pair *wnode = nullptr;      // [nchunks * k] chunk sketches, merged in place level by level
   uint32_t *wflag = nullptr;  // [nchunks] the node's sketches or merges lost weight
   uint32_t *wcount = nullptr; // [nmulti * (k+1)] pass-2 counts per candidate slot, then K_{i->d}
+  unsigned classes = 0;       // kernel classes of a sweep (bits 0 .. 2)
+  bool clock = false;         // ... one class, whose first kernel can stamp the device clock
   // exact mode
   int32_t *tier[4] = {nullptr, nullptr, nullptr, nullptr};
   int64_t ntier[4] = {0, 0, 0, 0};
@@ -252,8 +259,8 @@ inline SchedParams sched_params(const mgcd_params *p) {
 size_t schedule_ws_bytes(int32_t n, int64_t nnz, int mode, int k, int64_t L);
 
 // One sweep of `algo` (ALGO_LPA / ALGO_MOVE / ALGO_REFINE) over all vertices.
-// ev (optional, 4 events): recorded before the first kernel class and after each
-// of the three classes, for per-class timing.
+// ev (optional, 4 events): event i is recorded between the kernel classes i - 1 and i where
+// one of them has kernels (Schedule::classes), for per-class timing.
 void launch_sweep(const SweepArgs &a, const Schedule &s, int algo, int mode, int k, int64_t L,
                   hipStream_t st, hipEvent_t *ev = nullptr);
 

@@ -453,13 +453,11 @@ bool StepEngine::prepare(StepJob *j, const Lane &l) {
     if (p_.validate) {  // before anything reads the rows
       launch_zero_u64(scr, 2, l.st);
       launch_validate(g, scr, l.st);
-      MGCD_HIP(hipMemcpyAsync(&h, scr, sizeof(h), hipMemcpyDeviceToHost, l.st));
-      MGCD_HIP(hipStreamSynchronize(l.st));
+      read_back(&h, scr, sizeof(h), l.st);
       if (h != 0) throw Error(MGCD_E_GRAPH, "CSR failed validation");
     }
     launch_degrees(g, j->K[0], scr + 1, a, l.st);
-    MGCD_HIP(hipMemcpyAsync(&h, scr + 1, sizeof(h), hipMemcpyDeviceToHost, l.st));
-    MGCD_HIP(hipStreamSynchronize(l.st));
+    read_back(&h, scr + 1, sizeof(h), l.st);
     if (h >= (1ull << 31)) throw Error(MGCD_E_OVERFLOW, "total edge weight must be below 2^31");
     j->W = h;
     j->cur = g;
@@ -501,8 +499,7 @@ static std::vector<int64_t> gather(Arena &a, const int64_t *src, const std::vect
   int64_t *od = a.take<int64_t>((int64_t)pos.size());
   k_step_gather<<<grid_of((int64_t)pos.size()), BLOCK, 0, st>>>(src, pd, od, (int32_t)pos.size());
   MGCD_LAUNCHED();
-  MGCD_HIP(hipMemcpyAsync(h.data(), od, h.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(h.data(), od, h.size() * sizeof(int64_t), st);
   a.release(mk);
   return h;
 }
@@ -589,8 +586,7 @@ void StepEngine::admit_together(const std::vector<StepJob *> &js) {
     launch_degrees(Graph{c.n, c.nnz, c.offsets, c.indices, c.weights}, ok[q]->K[0], Wd + q, a, st);
   }
   std::vector<unsigned long long> W(ok.size());
-  MGCD_HIP(hipMemcpyAsync(W.data(), Wd, W.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-  MGCD_HIP(hipStreamSynchronize(st));
+  read_back(W.data(), Wd, W.size() * sizeof(unsigned long long), st);
   std::vector<StartDesc> sd;
   int64_t nmax = 1;
   for (size_t q = 0; q < ok.size(); ++q) {
@@ -828,9 +824,10 @@ void StepEngine::step(std::vector<StepJob *> &finished) {
     std::swap(C[0], C[1]);
   }
   uint32_t lv[2] = {0, 0};
-  MGCD_HIP(hipMemcpyAsync(u.hres.data(), u.res, (size_t)u.count * sizeof(StepResult), hipMemcpyDeviceToHost, st_));
-  MGCD_HIP(hipMemcpyAsync(lv, u.lv, sizeof(lv), hipMemcpyDeviceToHost, st_));
-  MGCD_HIP(hipStreamSynchronize(st_));
+  HostRead rd(st_);
+  rd.add(u.hres.data(), u.res, (size_t)u.count * sizeof(StepResult));
+  rd.add(lv, u.lv, sizeof(lv));
+  rd.wait();
   // the labels are in the buffer the last sweep in which some graph moved wrote
   if (lv[1] % 2 == 1) std::swap(u.C[0], u.C[1]);
   ctr_.sweeps_moving += lv[1];
