@@ -1073,48 +1073,44 @@ __global__ void __launch_bounds__(BLOCK)
 
 // ---- aggregation driver -----------------------------------------------------------------
 
-// K = 32 or 64: one wave per community holds a WaveSketch (slot p in lane p).  The
-// community's stream (members in ascending id, each row in CSR order) is loaded 64
-// entries at a time and folded in stream order; every L positions the chunk sketch
-// goes into the fixed merge tree.  The row is the positive slots sorted by key: each
-// lane's rank is the number of smaller keys, found by scanning the 64 lanes.
-template <int K, int MODE, int DEPTH>
+// The load of wave_chunk for the staged streams.
+struct StreamLoad {
+  const uint32_t *__restrict__ skey, *__restrict__ sw;
+  __device__ inline void operator()(int64_t q, bool in, uint32_t &key, uint32_t &w) const {
+    key = in ? __builtin_nontemporal_load(skey + q) : EMPTY;
+    w = in ? __builtin_nontemporal_load(sw + q) : 0u;
+  }
+};
+
+// K = 32 or 64: one wave per community.  The community's stream (members in ascending id,
+// each row in CSR order) is sketched chunk by chunk (wave_chunk), each chunk's sketch going
+// into the fixed merge tree.  The row is the positive slots sorted by key: each lane's rank
+// is the number of smaller keys, found by scanning the 64 lanes.
+template <int K, int MODE>
 __global__ void __launch_bounds__(BLOCK)
-    k_agg_wave(AggStreams s, const int32_t *__restrict__ comms, int64_t ncomm, int64_t L,
+    k_agg_wave(AggStreams s, const int32_t *__restrict__ comms, int64_t ncomm, int64_t L, int depth,
                Pair *rows, uint32_t *rcount) {
   static_assert(K <= WAVE, "one slot per lane; larger sketches split every stream");
-  __shared__ uint32_t sstack[BLOCK / WAVE][DEPTH * 2 * WAVE];
+  extern __shared__ uint32_t wave_lds[];
   const int lane = lane_id();
   const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   if (r >= ncomm) return;
   const int32_t c = uniform(comms[r]);
-  WaveSketch<K, MODE> sk;
-  sk.reset();
-  WaveTree<K, DEPTH> tree{sstack[threadIdx.x / WAVE]};
-  int64_t left = L;  // positions left in the current chunk
+  const int wave = uniform((int32_t)(threadIdx.x / WAVE));
+  WaveTree<K> tree(wave_lds + wave * (WaveMap<K>::WORDS + depth * 2 * WAVE), depth);
+  const StreamLoad load{s.skey, s.sw};
+  uint32_t k1[1], v1[1];
   const int64_t base = uniform(s.P[s.mstart[c]]), end = uniform(s.P[s.mstart[c + 1]]);
-  for (int64_t q0 = base; q0 < end; q0 += WAVE) {
-    const int64_t q = q0 + lane;
-    const bool v = q < end;
-    const uint32_t key = v ? __builtin_nontemporal_load(s.skey + q) : EMPTY;
-    const uint32_t w = v ? __builtin_nontemporal_load(s.sw + q) : 0u;
-    const int nb = end - q0 < WAVE ? (int)(end - q0) : WAVE;
-    for (int u = 0; u < nb; ++u) {
-      sk.update(lane_value(key, u), lane_value(w, u));
-      if (--left == 0) {  // end of a chunk
-        sk.finalize();
-        tree.push(sk.key[0], sk.val[0]);
-        sk.reset();
-        left = L;
-      }
+  if (end - base <= L) {
+    wave_chunk<K, MODE>(tree.map, base, end, load, k1, v1);
+  } else {
+    for (int64_t q0 = base; q0 < end; q0 += L) {
+      wave_chunk<K, MODE>(tree.map, q0, end - q0 < L ? end : q0 + L, load, k1, v1);
+      tree.push(k1, v1);
     }
+    tree.result(k1, v1);
   }
-  if (left != L) {  // the last, partial chunk
-    sk.finalize();
-    tree.push(sk.key[0], sk.val[0]);
-  }
-  uint32_t ck, cv;
-  tree.result(ck, cv);
+  const uint32_t ck = k1[0], cv = v1[0];
   uint32_t rank = 0;
   for (int u = 0; u < WAVE; ++u) rank += lane_value(ck, u) < ck ? 1u : 0u;
   const uint64_t pos = __ballot(cv > 0);
@@ -1127,37 +1123,40 @@ __global__ void __launch_bounds__(BLOCK)
 struct AggSplit {
   const int32_t *multi;   // [nmulti] split communities
   int64_t nmulti;
-  const int64_t *cstart;  // [nmulti+1] first chunk of each
-  const int32_t *owner;   // [nchunks] index into multi of each chunk
-  int64_t nchunks;
-  Pair *node;             // [nchunks * K] chunk sketches, merged in place level by level
+  const int64_t *cstart;  // [nmulti+1] first node (wave_group(K) chunks) of each
+  const int32_t *owner;   // [nchunks] index into multi of each node
+  int64_t nchunks;        // nodes
+  Pair *node;             // [nchunks * K] sketches of the nodes, merged in place level by level
 };
 
-// One wave per chunk of a split stream: its sketch, finalised, into the chunk's node.
+// One wave per chunk of a split stream: its sketch, finalised; the workgroup's chunks (eight
+// neighbouring ones of a stream, K = 128 / 256: each alone) become one node.
 template <int K, int MODE>
-__global__ void __launch_bounds__(BLOCK) k_aggw_chunks(AggStreams s, AggSplit sp, int64_t L) {
-  const int lane = lane_id();
-  const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+__global__ void __launch_bounds__(wave_group_block(K)) k_aggw_chunks(AggStreams s, AggSplit sp, int64_t L) {
+  constexpr int S = WaveSlots<K>::S, G = wave_group(K), WAVES = wave_group_waves(K);
+  __shared__ uint32_t smap[WAVES][WaveMap<K>::WORDS];
+  const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
+  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
   if (q >= sp.nchunks) return;
   const int32_t x = uniform(sp.owner[q]);
   const int32_t c = uniform(sp.multi[x]);
   const int64_t end = uniform(s.P[s.mstart[c + 1]]);
-  const int64_t p0 = uniform(s.P[s.mstart[c]]) + (q - sp.cstart[x]) * L;
+  const int64_t first = uniform(s.P[s.mstart[c]]) + (q - uniform(sp.cstart[x])) * G * L;
+  const int64_t p0 = first + (G > 1 ? wave * L : 0);
   const int64_t p1 = p0 + L < end ? p0 + L : end;
-  WaveSketch<K, MODE> sk;
-  sk.reset();
-  for (int64_t q0 = p0; q0 < p1; q0 += WAVE) {
-    const int64_t t = q0 + lane;
-    const bool v = t < p1;
-    const uint32_t key = v ? __builtin_nontemporal_load(s.skey + t) : EMPTY;
-    const uint32_t w = v ? __builtin_nontemporal_load(s.sw + t) : 0u;
-    const int nb = p1 - q0 < WAVE ? (int)(p1 - q0) : WAVE;
-    for (int u = 0; u < nb; ++u) sk.update(lane_value(key, u), lane_value(w, u));
+  const WaveMap<K> map(smap[wave]);
+  uint32_t ck[S], cv[S];
+  bool lossy = false;
+  if (G == 1 || p0 < p1) lossy = wave_chunk<K, MODE>(map, p0, p1, StreamLoad{s.skey, s.sw}, ck, cv);
+  if constexpr (G > 1) {
+    __shared__ Pair snode[WAVES][K];
+    __shared__ uint32_t sflag[WAVES];
+    merge_group<K>(map, snode, sflag, wave, (end - first + L - 1) / L, ck, cv, lossy);
+    if (wave != 0) return;
   }
-  sk.finalize();
 #pragma unroll
-  for (int r = 0; r < WaveSlots<K>::S; ++r)
-    if (r * WAVE + lane < K) sp.node[q * K + r * WAVE + lane] = Pair{sk.key[r], sk.val[r]};
+  for (int r = 0; r < S; ++r)
+    if (r * WAVE + lane < K) sp.node[q * K + r * WAVE + lane] = Pair{ck[r], cv[r]};
 }
 
 // Level `level` of the merge tree of every split stream (node x of a stream, x a
@@ -1165,7 +1164,7 @@ __global__ void __launch_bounds__(BLOCK) k_aggw_chunks(AggStreams s, AggSplit sp
 // is carried).
 template <int K>
 __global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level) {
-  const int lane = lane_id();
+  __shared__ uint32_t smap[BLOCK / WAVE][WaveMap<K>::WORDS];
   const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   if (q >= sp.nchunks) return;
   const int32_t x = uniform(sp.owner[q]);
@@ -1173,27 +1172,20 @@ __global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level) {
   if (((q - sp.cstart[x]) & (2 * half - 1)) != 0) return;
   const int64_t r = q + half;
   if (r >= sp.cstart[x + 1]) return;
-  constexpr int S = WaveSlots<K>::S;
-  uint32_t ak[S], av[S], bk[S], bv[S];
-#pragma unroll
-  for (int u = 0; u < S; ++u) {
-    const int p = u * WAVE + lane;
-    ak[u] = EMPTY;
-    av[u] = 0;
-    bk[u] = EMPTY;
-    bv[u] = 0;
-    if (p < K) {
-      const Pair pa = sp.node[q * K + p], pb = sp.node[r * K + p];
-      ak[u] = pa.key;
-      av[u] = pa.val;
-      bk[u] = pb.key;
-      bv[u] = pb.val;
-    }
+  merge_nodes<K>(WaveMap<K>(smap[uniform((int32_t)(threadIdx.x / WAVE))]), sp.node, q, r);
+}
+
+// Levels from `level` on of every split stream, one workgroup each, as in the sweeps.
+template <int K>
+__global__ void __launch_bounds__(TREE_BLOCK) k_aggw_tree(AggSplit sp, int level) {
+  __shared__ uint32_t smap[TREE_BLOCK / WAVE][WaveMap<K>::WORDS];
+  const int64_t q0 = sp.cstart[blockIdx.x], n = sp.cstart[blockIdx.x + 1] - q0;
+  const int wave = uniform((int32_t)(threadIdx.x / WAVE));
+  for (int64_t half = (int64_t)1 << level; half < n; half *= 2) {  // block-uniform
+    for (int64_t x = wave * 2 * half; x + half < n; x += TREE_BLOCK / WAVE * 2 * half)
+      merge_nodes<K>(WaveMap<K>(smap[wave]), sp.node, q0 + x, q0 + x + half);
+    __syncthreads();
   }
-  wave_merge<K>(ak, av, bk, bv);
-#pragma unroll
-  for (int u = 0; u < S; ++u)
-    if (u * WAVE + lane < K) sp.node[q * K + u * WAVE + lane] = Pair{ak[u], av[u]};
 }
 
 // The row of every split stream: the root's positive slots sorted by key.
@@ -1241,25 +1233,27 @@ template <int K, int MODE>
 static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, const AggSplit &sp,
                      int64_t L, Pair *rows, uint32_t *rcount, int64_t max_len, hipStream_t st) {
   if (sp.nmulti > 0) {
-    const unsigned cgrid = (unsigned)ceil_div(sp.nchunks, BLOCK / WAVE);
-    k_aggw_chunks<K, MODE><<<cgrid, BLOCK, 0, st>>>(s, sp, L);
+    k_aggw_chunks<K, MODE><<<wave_group_grid(K, sp.nchunks), wave_group_block(K), 0, st>>>(s, sp, L);
     MGCD_LAUNCHED();
-    const int64_t maxch = (max_len + L - 1) / L;
-    for (int l = 0; ((int64_t)1 << l) < maxch; ++l) {
-      k_aggw_level<K><<<cgrid, BLOCK, 0, st>>>(sp, l);
+    const int64_t G = wave_group(K), maxch = (max_len + G * L - 1) / (G * L);
+    int l = 0;
+    for (; (maxch >> l) > TREE_NODES; ++l) {
+      k_aggw_level<K><<<(unsigned)ceil_div(sp.nchunks, BLOCK / WAVE), BLOCK, 0, st>>>(sp, l);
+      MGCD_LAUNCHED();
+    }
+    if (((int64_t)1 << l) < maxch) {
+      k_aggw_tree<K><<<(unsigned)sp.nmulti, TREE_BLOCK, 0, st>>>(sp, l);
       MGCD_LAUNCHED();
     }
     k_aggw_rows<K><<<(unsigned)ceil_div(sp.nmulti, BLOCK / WAVE), BLOCK, 0, st>>>(sp, rows, rcount);
     MGCD_LAUNCHED();
-    max_len = L > WAVE_SPLIT ? L : WAVE_SPLIT;  // the longest stream left for one wave
   }
   if (ncomm > 0) {
     if constexpr (K <= WAVE) {
       const unsigned grid = (unsigned)ceil_div(ncomm, BLOCK / WAVE);
-      if (wave_depth_for(max_len, L) == WDEPTH_SHALLOW)
-        k_agg_wave<K, MODE, WDEPTH_SHALLOW><<<grid, BLOCK, 0, st>>>(s, comms, ncomm, L, rows, rcount);
-      else
-        k_agg_wave<K, MODE, WDEPTH><<<grid, BLOCK, 0, st>>>(s, comms, ncomm, L, rows, rcount);
+      const int depth = wave_tree_depth(WAVE_SPLIT, L);  // longer streams are one chunk or split
+      k_agg_wave<K, MODE><<<grid, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(s, comms, ncomm, L, depth,
+                                                                                    rows, rcount);
     } else {
       k_empty_rows<<<grid_for(ncomm), BLOCK, 0, st>>>(comms, ncomm, rcount);
     }
@@ -1428,7 +1422,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   if (nmulti > 0) {
     int64_t *nch = a.take<int64_t>(nmulti);
     cstart = a.take<int64_t>(nmulti + 1);
-    k_comm_chunks<<<grid_for(nmulti), BLOCK, 0, st>>>(mstart, P, multi, nmulti, L, nch);
+    k_comm_chunks<<<grid_for(nmulti), BLOCK, 0, st>>>(mstart, P, multi, nmulti, wave ? wave_group(k) * L : L, nch);
     MGCD_LAUNCHED();
     scan_i64(nch, cstart, nmulti, cstart + nmulti, a, st);
   }

@@ -1177,22 +1177,66 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ligh
 
 // ---- MG with K = 32 or 64: one wave per row -------------------------------------------
 
+// The load of wave_chunk for a row of the graph: the entry's key (written to the key
+// stream) and weight.
+template <int ALGO>
+struct RowLoad {
+  const SweepArgs &a;
+  int32_t i, bi;
+  uint32_t *keybuf;
+  __device__ inline void operator()(int64_t e, bool in, uint32_t &key, uint32_t &w) const {
+    const int32_t j = in ? __builtin_nontemporal_load(a.g.idx + e) : 0;
+    w = in ? __builtin_nontemporal_load(a.g.w + e) : 0u;
+    key = EMPTY;
+    if (in) {
+      key = stream_key<ALGO>(a, i, j, bi);
+      keybuf[e] = key;
+    }
+  }
+};
+
+// Pass 2 in a wave's map: the candidates' cells, then positions e, e + step, .. below hi of
+// the key stream, each item added to its candidate's cell; the result is this lane's part
+// of the weight towards d.
+template <int K>
+__device__ inline void pass2_cells(WaveMap<K> map, const uint32_t (&ck)[WaveSlots<K>::S],
+                                   uint32_t (&cell)[WaveSlots<K>::S]) {
+  map.clear();
+  bool fresh;
+#pragma unroll
+  for (int u = 0; u < WaveSlots<K>::S; ++u) cell[u] = ck[u] != EMPTY ? map.claim(ck[u], fresh) : 0u;
+  wave_sync();
+}
+
+template <int K>
+__device__ inline uint32_t pass2_items(const SweepArgs &a, WaveMap<K> map, int64_t e, int64_t hi, int step,
+                                       const uint32_t *__restrict__ keybuf, uint32_t d) {
+  uint32_t kd = 0;
+  for (; e < hi; e += step) {
+    const uint32_t key = __builtin_nontemporal_load(keybuf + e);
+    const uint32_t w = __builtin_nontemporal_load(a.g.w + e);
+    kd += key == d ? w : 0u;
+    if (key != EMPTY) map.add_present(key, w);
+  }
+  return kd;
+}
+
 // Rows longer than 32 entries when K is 32 or 64 (shorter rows cannot lose weight
-// under Algorithm 1 or the textbook rule and take the exact one-lane kernel).  One
-// wave per row holds a WaveSketch (slot p in lane p).  Pass 1: the row is loaded 64
-// entries at a time (coalesced index and weight loads, 64 label gathers in flight,
-// keys written to the key stream) and folded in stream order, one wave-uniform item
-// at a time; every L positions the chunk sketch goes into the fixed merge tree
-// (WaveTree).  Pass 2 (lossy rows only): the key stream again, each item added to the
-// lane whose candidate matches.  Decision: every lane scores its candidate, a
+// under Algorithm 1 or the textbook rule and take the short rows' kernel).  One wave per
+// row.  Pass 1: each chunk's sketch (wave_chunk, keys written to the key stream) goes into
+// the fixed merge tree (WaveTree).  Pass 2 (lossy rows only): the key stream again, each
+// item added to its candidate's cell.  Decision: every lane scores its candidate, a
 // butterfly keeps the best (lowest id on ties), lane 0 records it.
-template <int K, int ALGO, int MODE, int DEPTH>
+// Bound by the latency of the fold's steps (LDS probes; item by item once a chunk has more
+// than K keys).  R-MAT 2^18, K = 64, Leiden's 16 sweeps: 1258 us with an item-by-item fold
+// of every entry and of pass 2, 524 us with the map (first sweeps 91 and 50 us).
+template <int K, int ALGO, int MODE>
 __global__ void __launch_bounds__(BLOCK)
-    k_wave_rows(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t L,
+    k_wave_rows(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t L, int depth,
                 uint32_t *keybuf) {
   static_assert(K <= WAVE, "one slot per lane; larger sketches take the split rows");
   if (level_over(a)) return;  // batched: every graph has stopped
-  __shared__ uint32_t sstack[BLOCK / WAVE][DEPTH * 2 * WAVE];
+  extern __shared__ uint32_t wave_lds[];
   const int lane = lane_id();
   const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
@@ -1204,68 +1248,39 @@ __global__ void __launch_bounds__(BLOCK)
     const int64_t lo = uniform(a.g.off[i]), hi = uniform(a.g.off[i + 1]);
     const int32_t bi = ALGO == ALGO_REFINE ? uniform(a.bound[i]) : 0;
     const int32_t d = uniform(community_of_self<ALGO>(a, i));
-    WaveSketch<K, MODE> s;
-    s.reset();
-    WaveTree<K, DEPTH> tree{sstack[threadIdx.x / WAVE]};
+    const RowLoad<ALGO> load{a, i, bi, keybuf};
+    const int wave = uniform((int32_t)(threadIdx.x / WAVE));
+    WaveTree<K> tree(wave_lds + wave * (WaveMap<K>::WORDS + depth * 2 * WAVE), depth);
+    uint32_t ck[1], cv[1];
     bool lossy = false;
-    int64_t left = L;  // positions left in the current chunk
-    for (int64_t e0 = lo; e0 < hi; e0 += WAVE) {
-      const int64_t e = e0 + lane;
-      const bool v = e < hi;
-      const int32_t j = v ? __builtin_nontemporal_load(a.g.idx + e) : 0;
-      const uint32_t w = v ? __builtin_nontemporal_load(a.g.w + e) : 0u;
-      uint32_t key = EMPTY;
-      if (v) {
-        key = stream_key<ALGO>(a, i, j, bi);
-        keybuf[e] = key;
+    if (hi - lo <= L) {
+      lossy = wave_chunk<K, MODE>(tree.map, lo, hi, load, ck, cv);
+    } else {
+      for (int64_t c0 = lo; c0 < hi; c0 += L) {
+        lossy |= wave_chunk<K, MODE>(tree.map, c0, hi - c0 < L ? hi : c0 + L, load, ck, cv);
+        tree.push(ck, cv);
       }
-      const int nb = hi - e0 < WAVE ? (int)(hi - e0) : WAVE;
-      for (int t = 0; t < nb; ++t) {
-        const uint32_t c = lane_value(key, t);
-        if (c != EMPTY) s.update(c, lane_value(w, t));
-        if (--left == 0) {  // end of a chunk
-          lossy |= s.lossy;
-          s.finalize();
-          tree.push(s.key[0], s.val[0]);
-          s.reset();
-          left = L;
-        }
-      }
+      tree.result(ck, cv);
+      lossy |= tree.lossy;
     }
-    if (left != L) {  // the last, partial chunk
-      lossy |= s.lossy;
-      s.finalize();
-      tree.push(s.key[0], s.val[0]);
-    }
-    uint32_t ck, cv;
-    tree.result(ck, cv);
-    lossy |= tree.lossy;
     uint32_t kd = 0;
     if (!lossy || !second_pass(a, ALGO)) {
-      kd = wave_sum(ck == (uint32_t)d ? cv : 0u);
+      kd = ck[0] == (uint32_t)d ? cv[0] : 0u;
     } else {
-      cv = 0;
-      for (int64_t e0 = lo; e0 < hi; e0 += WAVE) {
-        const int64_t e = e0 + lane;
-        const bool v = e < hi;
-        const uint32_t key = v ? __builtin_nontemporal_load(keybuf + e) : EMPTY;
-        const uint32_t w = v ? __builtin_nontemporal_load(a.g.w + e) : 0u;
-        kd += key == (uint32_t)d ? w : 0u;
-        const int nb = hi - e0 < WAVE ? (int)(hi - e0) : WAVE;
-        for (int t = 0; t < nb; ++t) {
-          const uint32_t c = lane_value(key, t);
-          if (c != EMPTY && ck == c) cv += lane_value(w, t);
-        }
-      }
-      kd = wave_sum(kd);
+      uint32_t cell[1];
+      pass2_cells<K>(tree.map, ck, cell);
+      kd = pass2_items<K>(a, tree.map, lo + lane, hi, WAVE, keybuf, (uint32_t)d);
+      wave_sync();
+      cv[0] = ck[0] != EMPTY ? tree.map.val[cell[0]] : 0u;
     }
+    kd = wave_sum(kd);
     int32_t best = -1;
     int64_t bestG = 0;
-    if (ck != EMPTY) {
+    if (ck[0] != EMPTY) {
       const int64_t W = ALGO == ALGO_LPA ? 0 : (int64_t)weight_of(a, i);
       const int64_t Ki = ALGO == ALGO_LPA ? 0 : (int64_t)a.K[i];
       const int64_t Sd = ALGO == ALGO_LPA ? 0 : (int64_t)a.Sig[d];
-      consider<ALGO>(a, W, d, Ki, Sd, kd, (int32_t)ck, cv, best, bestG);
+      consider<ALGO>(a, W, d, Ki, Sd, kd, (int32_t)ck[0], cv[0], best, bestG);
     }
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) {
@@ -1281,61 +1296,64 @@ __global__ void __launch_bounds__(BLOCK)
   flush_counters(a, ct);
 }
 
-// Rows of more than max(L, WAVE_SPLIT) entries when K is 32 or 64 ("split rows"): the
-// same sketch, merge tree and decision as k_wave_rows, with the work spread over waves
-// so that a hub row does not hold one wave for its whole length.
+// Rows of more than max(L, WAVE_SPLIT) entries when K is 32 or 64, and every row past the
+// short ones when K is 128 or 256 ("split rows"): the same sketch, merge tree and decision
+// as k_wave_rows, with the work spread over waves so that a hub row does not hold one wave
+// for its whole length.
 //   k_wave_chunks: one wave per chunk: its Algorithm 1 sketch (keys written to the key
-//                  stream), finalised, into the chunk's node;
+//                  stream), finalised; the workgroup's chunks (eight neighbouring ones of a
+//                  row) are merged into one node (merge_group);
 //   k_wave_level:  one launch per tree level l: node x of a row (x a multiple of
 //                  2^(l+1)) takes in node x + 2^l if that exists, left operand first,
-//                  an odd last node is carried; after ceil(log2(chunks)) levels node 0
+//                  an odd last node is carried; after ceil(log2(nodes)) levels node 0
 //                  is the root, the same tree as WaveTree;
-//   k_wave_count:  pass 2 of lossy rows, one wave per chunk, integer sums added into
-//                  the row's counts (order-independent);
+//   k_wave_tree:   the levels at which every row has at most TREE_NODES nodes left, in one
+//                  launch: one workgroup per row, a barrier between levels;
+//   k_wave_count:  pass 2 of lossy rows, one workgroup per node's chunks (K = 128 / 256: one
+//                  wave), integer sums added into the row's counts (order-independent);
 //   k_wave_decide: one wave per row: scores and the decision, as in k_wave_rows.
+// cstart and owner are those of the nodes.
+// Bound as k_wave_rows by the latency of the fold.  R-MAT 2^18, K = 64, Leiden's 16 sweeps:
+// chunks, levels and counts took 568, 1170 and 328 us; chunks (with their three levels),
+// trees and counts now take 496, 120 and 145 us.
 template <int K, int ALGO, int MODE>
-__global__ void __launch_bounds__(BLOCK)
+__global__ void __launch_bounds__(wave_group_block(K))
     k_wave_chunks(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
-                  const int32_t *__restrict__ owner, int64_t nchunks, int64_t L, uint32_t *keybuf,
+                  const int32_t *__restrict__ owner, int64_t nnodes, int64_t L, uint32_t *keybuf,
                   Pair *node, uint32_t *nflag, uint32_t *count) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  const int lane = lane_id();
-  const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
-  if (q >= nchunks) return;
+  constexpr int S = WaveSlots<K>::S, G = wave_group(K), WAVES = wave_group_waves(K);
+  __shared__ uint32_t smap[WAVES][WaveMap<K>::WORDS];
+  const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
+  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
+  if (q >= nnodes) return;
   const int32_t m = uniform(owner[q]);
   const int32_t i = uniform(rows[m]);
-  if (q == cstart[m]) {  // the row's K + 1 pass-2 counts start at zero in every sweep
+  const int64_t x = q - uniform(cstart[m]);  // node within the row
+  if (x == 0) {  // the row's K + 1 pass-2 counts start at zero in every sweep
     uint32_t *cm = count + (int64_t)m * (K + 1);
-    for (int p = lane; p <= K; p += WAVE) cm[p] = 0u;
+    for (int p = G > 1 ? (int)threadIdx.x : lane; p <= K; p += G > 1 ? WAVES * WAVE : WAVE) cm[p] = 0u;
   }
   if (frozen(a, i)) return;
-  const int64_t rhi = uniform(a.g.off[i + 1]);
-  const int64_t lo = uniform(a.g.off[i]) + (q - cstart[m]) * L;
+  const int64_t rhi = uniform(a.g.off[i + 1]), first = uniform(a.g.off[i]) + x * G * L;
+  const int64_t lo = first + (G > 1 ? wave * L : 0);
   const int64_t hi = lo + L < rhi ? lo + L : rhi;
   const int32_t bi = ALGO == ALGO_REFINE ? uniform(a.bound[i]) : 0;
-  WaveSketch<K, MODE> s;
-  s.reset();
-  for (int64_t e0 = lo; e0 < hi; e0 += WAVE) {
-    const int64_t e = e0 + lane;
-    const bool v = e < hi;
-    const int32_t j = v ? __builtin_nontemporal_load(a.g.idx + e) : 0;
-    const uint32_t w = v ? __builtin_nontemporal_load(a.g.w + e) : 0u;
-    uint32_t key = EMPTY;
-    if (v) {
-      key = stream_key<ALGO>(a, i, j, bi);
-      keybuf[e] = key;
-    }
-    const int nb = hi - e0 < WAVE ? (int)(hi - e0) : WAVE;
-    for (int t = 0; t < nb; ++t) {
-      const uint32_t c = lane_value(key, t);
-      if (c != EMPTY) s.update(c, lane_value(w, t));
-    }
+  const WaveMap<K> map(smap[wave]);
+  uint32_t ck[S], cv[S];
+  bool lossy = false;
+  if (G == 1 || lo < hi)
+    lossy = wave_chunk<K, MODE>(map, lo, hi, RowLoad<ALGO>{a, i, bi, keybuf}, ck, cv);
+  if constexpr (G > 1) {
+    __shared__ Pair snode[WAVES][K];
+    __shared__ uint32_t sflag[WAVES];
+    merge_group<K>(map, snode, sflag, wave, (rhi - first + L - 1) / L, ck, cv, lossy);
+    if (wave != 0) return;
   }
-  s.finalize();
 #pragma unroll
-  for (int r = 0; r < WaveSlots<K>::S; ++r)
-    if (r * WAVE + lane < K) node[q * K + r * WAVE + lane] = Pair{s.key[r], s.val[r]};
-  if (lane == 0) nflag[q] = s.lossy ? 1u : 0u;
+  for (int r = 0; r < S; ++r)
+    if (r * WAVE + lane < K) node[q * K + r * WAVE + lane] = Pair{ck[r], cv[r]};
+  if (lane == 0) nflag[q] = lossy ? 1u : 0u;
 }
 
 template <int K>
@@ -1344,7 +1362,7 @@ __global__ void __launch_bounds__(BLOCK)
                  const int32_t *__restrict__ owner, int64_t nchunks, int level, Pair *node,
                  uint32_t *nflag) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  const int lane = lane_id();
+  __shared__ uint32_t smap[BLOCK / WAVE][WaveMap<K>::WORDS];
   const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   if (q >= nchunks) return;
   const int32_t m = uniform(owner[q]);
@@ -1353,28 +1371,29 @@ __global__ void __launch_bounds__(BLOCK)
   const int64_t r = q + half;
   if (r >= cstart[m + 1]) return;  // odd last node: carried up
   if (frozen(a, rows[m])) return;
-  constexpr int S = WaveSlots<K>::S;
-  uint32_t ak[S], av[S], bk[S], bv[S];
-#pragma unroll
-  for (int u = 0; u < S; ++u) {
-    const int p = u * WAVE + lane;
-    ak[u] = EMPTY;
-    av[u] = 0;
-    bk[u] = EMPTY;
-    bv[u] = 0;
-    if (p < K) {
-      const Pair pa = node[q * K + p], pb = node[r * K + p];
-      ak[u] = pa.key;
-      av[u] = pa.val;
-      bk[u] = pb.key;
-      bv[u] = pb.val;
+  const bool lossy = merge_nodes<K>(WaveMap<K>(smap[uniform((int32_t)(threadIdx.x / WAVE))]), node, q, r);
+  if (lane_id() == 0) nflag[q] = nflag[q] | nflag[r] | (lossy ? 1u : 0u);
+}
+
+// Levels from `level` on of every split row, one workgroup each; see k_wave_chunks.
+template <int K>
+__global__ void __launch_bounds__(TREE_BLOCK)
+    k_wave_tree(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart, int level,
+                Pair *node, uint32_t *nflag) {
+  if (level_over(a)) return;  // batched: every graph has stopped
+  __shared__ uint32_t smap[TREE_BLOCK / WAVE][WaveMap<K>::WORDS];
+  const int64_t m = blockIdx.x;
+  if (frozen(a, rows[m])) return;
+  const int64_t q0 = cstart[m], n = cstart[m + 1] - q0;
+  const int wave = uniform((int32_t)(threadIdx.x / WAVE));
+  for (int64_t half = (int64_t)1 << level; half < n; half *= 2) {  // block-uniform
+    for (int64_t x = wave * 2 * half; x + half < n; x += TREE_BLOCK / WAVE * 2 * half) {
+      const int64_t q = q0 + x, r = q + half;
+      const bool lossy = merge_nodes<K>(WaveMap<K>(smap[wave]), node, q, r);
+      if (lane_id() == 0) nflag[q] = nflag[q] | nflag[r] | (lossy ? 1u : 0u);
     }
+    __syncthreads();
   }
-  const bool lossy = wave_merge<K>(ak, av, bk, bv);
-#pragma unroll
-  for (int u = 0; u < S; ++u)
-    if (u * WAVE + lane < K) node[q * K + u * WAVE + lane] = Pair{ak[u], av[u]};
-  if (lane == 0) nflag[q] = nflag[q] | nflag[r] | (lossy ? 1u : 0u);
 }
 
 // The root of split row m: keys of positive slots, other slots EMPTY.
@@ -1395,48 +1414,55 @@ __device__ inline void wave_root(const Pair *node, const int64_t *cstart, int32_
 }
 
 template <int K, int ALGO>
-__global__ void __launch_bounds__(BLOCK)
+__global__ void __launch_bounds__(wave_group_block(K))
     k_wave_count(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
-                 const int32_t *__restrict__ owner, int64_t nchunks, int64_t L,
+                 const int32_t *__restrict__ owner, int64_t nnodes, int64_t L,
                  const uint32_t *__restrict__ keybuf, const Pair *__restrict__ node,
                  const uint32_t *__restrict__ nflag, uint32_t *count) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  const int lane = lane_id();
-  const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
-  if (q >= nchunks) return;
+  constexpr int S = WaveSlots<K>::S, G = wave_group(K), WAVES = wave_group_waves(K);
+  __shared__ uint32_t smap[G > 1 ? 1 : WAVES][WaveMap<K>::WORDS];
+  __shared__ uint32_t skd;
+  const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
+  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
+  if (q >= nnodes) return;
   const int32_t m = uniform(owner[q]);
   const int32_t i = uniform(rows[m]);
-  if (frozen(a, i) || !nflag[cstart[m]]) return;
+  const int64_t q0 = uniform(cstart[m]);
+  if (frozen(a, i) || !uniform(nflag[q0])) return;
   const int64_t rhi = uniform(a.g.off[i + 1]);
-  const int64_t lo = uniform(a.g.off[i]) + (q - cstart[m]) * L;
-  const int64_t hi = lo + L < rhi ? lo + L : rhi;
+  const int64_t lo = uniform(a.g.off[i]) + (q - q0) * G * L;
+  const int64_t hi = lo + G * L < rhi ? lo + G * L : rhi;
   const uint32_t d = (uint32_t)uniform(community_of_self<ALGO>(a, i));
-  constexpr int S = WaveSlots<K>::S;
-  uint32_t ck[S], cv0[S], cv[S];
-  wave_root<K>(node, cstart, m, ck, cv0);
-#pragma unroll
-  for (int u = 0; u < S; ++u) cv[u] = 0;
-  uint32_t kd = 0;
-  for (int64_t e0 = lo; e0 < hi; e0 += WAVE) {
-    const int64_t e = e0 + lane;
-    const bool v = e < hi;
-    const uint32_t key = v ? __builtin_nontemporal_load(keybuf + e) : EMPTY;
-    const uint32_t w = v ? __builtin_nontemporal_load(a.g.w + e) : 0u;
-    kd += key == d ? w : 0u;
-    const int nb = hi - e0 < WAVE ? (int)(hi - e0) : WAVE;
-    for (int t = 0; t < nb; ++t) {
-      const uint32_t c = lane_value(key, t);
-      const uint32_t wt = lane_value(w, t);
-#pragma unroll
-      for (int u = 0; u < S; ++u)
-        if (c != EMPTY && ck[u] == c) cv[u] += wt;
-    }
+  const WaveMap<K> map(smap[G > 1 ? 0 : wave]);  // the workgroup's (or wave's)
+  uint32_t ck[S], cv[S], cell[S];
+  wave_root<K>(node, cstart, m, ck, cv);
+  if (G == 1 || wave == 0) pass2_cells<K>(map, ck, cell);
+  if constexpr (G > 1) {
+    if (threadIdx.x == 0) skd = 0;
+    __syncthreads();
   }
+  uint32_t kd;
+  if constexpr (G > 1)
+    kd = pass2_items<K>(a, map, lo + threadIdx.x, hi, WAVES * WAVE, keybuf, d);
+  else
+    kd = pass2_items<K>(a, map, lo + lane, hi, WAVE, keybuf, d);
   kd = wave_sum(kd);
+  if constexpr (G > 1) {
+    if (lane == 0 && kd) atomicAdd(&skd, kd);
+    __syncthreads();
+    if (wave != 0) return;
+    kd = skd;
+  } else {
+    wave_sync();
+  }
   uint32_t *cm = count + (int64_t)m * (K + 1);
 #pragma unroll
-  for (int u = 0; u < S; ++u)
-    if (u * WAVE + lane < K && cv[u]) atomicAdd(&cm[u * WAVE + lane], cv[u]);
+  for (int u = 0; u < S; ++u) {
+    if (ck[u] == EMPTY) continue;
+    const uint32_t v = map.val[cell[u]];
+    if (v) atomicAdd(&cm[u * WAVE + lane], v);
+  }
   if (lane == 0 && kd) atomicAdd(&cm[K], kd);
 }
 
@@ -2331,7 +2357,7 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
     if (s.nmulti > 0) {
       int64_t *nch = a.take<int64_t>(s.nmulti);
       s.cstart = a.take<int64_t>(s.nmulti + 1);
-      k_chunk_counts<<<grid_for(s.nmulti), BLOCK, 0, st>>>(g.off, s.multi, s.nmulti, L, nch);
+      k_chunk_counts<<<grid_for(s.nmulti), BLOCK, 0, st>>>(g.off, s.multi, s.nmulti, wave_group(k) * L, nch);
       MGCD_LAUNCHED();
       scan_i64(nch, s.cstart, s.nmulti, s.cstart + s.nmulti, a, st);
       read_back(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), st);
@@ -2608,28 +2634,31 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
   if constexpr (K <= WAVE) {  // K = 128 / 256: every row the sketch takes is a split row
     if (s.ntier[1] > 0) {
       const unsigned grid = (unsigned)ceil_div(s.ntier[1], BLOCK / WAVE);
-      if (wave_depth_for(s.nmulti > 0 ? (L > WAVE_SPLIT ? L : WAVE_SPLIT) : s.maxdeg, L) == WDEPTH_SHALLOW)
-        k_wave_rows<K, ALGO, MODE, WDEPTH_SHALLOW><<<grid, BLOCK, 0, st>>>(a, s.tier[1], s.ntier[1], L,
-                                                                           s.keybuf);
-      else
-        k_wave_rows<K, ALGO, MODE, WDEPTH><<<grid, BLOCK, 0, st>>>(a, s.tier[1], s.ntier[1], L, s.keybuf);
+      const int depth = wave_tree_depth(WAVE_SPLIT, L);  // longer rows are one chunk or split
+      k_wave_rows<K, ALGO, MODE><<<grid, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(
+          a, s.tier[1], s.ntier[1], L, depth, s.keybuf);
       MGCD_LAUNCHED();
     }
   }
   mark(s, ev, 2, st);
   if (s.nmulti > 0) {  // split rows
-    const unsigned cgrid = (unsigned)ceil_div(s.nchunks, BLOCK / WAVE);
-    k_wave_chunks<K, ALGO, MODE><<<cgrid, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L,
+    const unsigned cgrid = wave_group_grid(K, s.nchunks);
+    k_wave_chunks<K, ALGO, MODE><<<cgrid, wave_group_block(K), 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L,
                                                           s.keybuf, s.wnode, s.wflag, s.wcount);
     MGCD_LAUNCHED();
-    const int64_t maxch = (s.maxdeg + L - 1) / L;
-    for (int l = 0; ((int64_t)1 << l) < maxch; ++l) {
-      k_wave_level<K><<<cgrid, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, l, s.wnode,
+    const int64_t G = wave_group(K), maxch = (s.maxdeg + G * L - 1) / (G * L);
+    int l = 0;
+    for (; (maxch >> l) > TREE_NODES; ++l) {
+      k_wave_level<K><<<(unsigned)ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, l, s.wnode,
                                                s.wflag);
       MGCD_LAUNCHED();
     }
+    if (((int64_t)1 << l) < maxch) {
+      k_wave_tree<K><<<(unsigned)s.nmulti, TREE_BLOCK, 0, st>>>(a, s.multi, s.cstart, l, s.wnode, s.wflag);
+      MGCD_LAUNCHED();
+    }
     if (second_pass(a, ALGO)) {
-      k_wave_count<K, ALGO><<<cgrid, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L, s.keybuf,
+      k_wave_count<K, ALGO><<<cgrid, wave_group_block(K), 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L, s.keybuf,
                                                      s.wnode, s.wflag, s.wcount);
       MGCD_LAUNCHED();
     }

@@ -157,8 +157,9 @@ struct Schedule {
   uint32_t *part = nullptr;   // [nchunks * (k+1)] pass-2 counts per chunk of a lossy long row
   Pair *cand = nullptr;       // [nmulti * k] merged candidates of each long row
   uint32_t *cflag = nullptr;  // [nmulti] 0 decided, 1 lossy, 2 frozen
-  // MG with K = 32 / 64: multi, cstart and owner list the split rows and their chunks
-  Pair *wnode = nullptr;      // [nchunks * k] chunk sketches, merged in place level by level
+  // MG with K >= 32: multi, cstart and owner list the split rows and their nodes
+  // (wave_group(k) chunks each; nchunks of them)
+  Pair *wnode = nullptr;      // [nchunks * k] sketches of the nodes, merged in place
   uint32_t *wflag = nullptr;  // [nchunks] the node's sketches or merges lost weight
   uint32_t *wcount = nullptr; // [nmulti * (k+1)] pass-2 counts per candidate slot, then K_{i->d}
   unsigned classes = 0;       // kernel classes of a sweep (bits 0 .. 2)
@@ -211,6 +212,13 @@ constexpr int64_t GSEG = 4096, TSEG = 8192;
 // K = 32 / 64: rows of more than max(L, WAVE_SPLIT) entries are split over one wave per
 // chunk (schedule only: the merge tree and the results are those of one wave per row)
 constexpr int64_t WAVE_SPLIT = 512;
+// A level of the merge tree of split rows is a launch of its own while a row has more than
+// TREE_NODES nodes; the levels above are one launch, a workgroup of TREE_BLOCK threads per
+// row, which has eight merges in flight at about 1.8 us each.  At 64 nodes its four rounds
+// take what a launch takes (6 to 10 us); with a launch for every level the trees of
+// R-MAT 2^18's split rows (at most 28 nodes) took 73 us a sweep, in one launch 7 to 14.
+constexpr int64_t TREE_NODES = 64;
+constexpr int TREE_BLOCK = 512;
 
 void build_schedule(const Graph &g, const SchedParams &sp, Schedule &s, Arena &a, hipStream_t st);
 
