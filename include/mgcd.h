@@ -99,10 +99,10 @@ typedef struct {
                              power of two up to 64 (default 64); rows of more chunks
                              take the long-row path                                  */
   int32_t exact_small;    /* exact mode: rows of at most this many entries use one
-                             lane each (default 32)                                  */
-  int32_t exact_lds;      /* exact mode: rows up to this use a 1024-slot LDS table
-                             (default and maximum 512)                               */
-  int32_t exact_lds_big;  /* exact mode: rows up to this use an 8192-slot LDS table
+                             to eight lanes each (default 32; of more than 32: one)  */
+  int32_t exact_lds;      /* exact mode: rows up to this (of at most 256 entries) use a
+                             wave with an LDS table (default and maximum 512)        */
+  int32_t exact_lds_big;  /* exact mode: rows up to this use a workgroup with an LDS table
                              (default and maximum 4096); longer rows a global table  */
   int32_t direct_launch;  /* batched runs: 0 (default) issues each level's sweeps as
                              one captured HIP graph, 1 launches them one by one      */
@@ -126,7 +126,7 @@ typedef struct {
   int32_t short_rows;     /* MGCD_MODE_ALG1 / _STD with k <= 16: a row of at most k
                              entries holds at most k distinct keys, so its sketch never
                              loses weight and equals its exact table.  Such rows are
-                             decided on the exact one-lane kernel: 0 (default) when the
+                             decided on the short rows' kernel: 0 (default) when the
                              level's average row has at most k entries, 1 never (the
                              sketch kernels take them), 2 always                     */
 } mgcd_params;
@@ -147,7 +147,7 @@ typedef struct {
      all rows but those that short_rows sends to the exact kernel, plus the chunk
      sketches of rows longer than 64 chunks), [1] the merge, second pass and
      decision of those long rows, [2] rows of at most k entries on the exact
-     one-lane kernel (short_rows).  Exact: [0] rows of at most 32 entries, [1] LDS hash tables,
+     short rows' kernel (short_rows).  Exact: [0] rows of at most 32 entries, [1] LDS hash tables,
      [2] global hash tables. */
   int32_t l0_sweeps;
   int32_t reserved2;

@@ -97,7 +97,7 @@ def tune(mg, sample, algo: int, ks=SKETCH_K, quality: float = 0.99, repeats: int
         lane_t[rl] = sec
     rl = choose_fastest(lane_t)
     # where rows of at most k entries go (k <= 16; schedule only): by the level's average
-    # row, never or always to the exact one-lane kernel
+    # row, never or always to the short rows' kernel
     short_t = {}
     if k <= 16:
         for sr in SHORT_ROWS:

@@ -1716,18 +1716,83 @@ __device__ inline uint32_t hash_slot(uint32_t c, uint32_t mask) {
   return (c * 0x9E3779B1u) & mask;  // Fibonacci hashing, low bits
 }
 
-// Exact mode, tier 1 (rows of up to EXACT_T1_MAX entries): one wave per row with an
+// The wave's best candidate (larger gain first, then lower id; -1: none) into every lane:
+// DPP moves within 16 lanes, then the four rows of 16 by lane reads.
+template <int PERM>
+__device__ inline void best_step(int32_t &best, int64_t &bestG) {
+  const uint32_t lo = quad_perm<PERM>((uint32_t)bestG), hi = quad_perm<PERM>((uint32_t)((uint64_t)bestG >> 32));
+  const int32_t c2 = (int32_t)quad_perm<PERM>((uint32_t)best);
+  const int64_t g2 = (int64_t)(((uint64_t)hi << 32) | lo);
+  const bool take = c2 >= 0 && (best < 0 || g2 > bestG || (g2 == bestG && c2 < best));
+  best = take ? c2 : best;
+  bestG = take ? g2 : bestG;
+}
+__device__ inline void wave_best(int32_t &best, int64_t &bestG) {
+  best_step<QP_XOR1>(best, bestG);
+  best_step<QP_XOR2>(best, bestG);
+  best_step<QP_HALF_MIRROR>(best, bestG);
+  best_step<QP_MIRROR>(best, bestG);
+  int32_t b = -1;
+  int64_t g = 0;
+#pragma unroll
+  for (int r = 0; r < WAVE; r += 16) {
+    const int32_t c2 = lane_value(best, r);
+    const int64_t g2 = (int64_t)(((uint64_t)lane_value((uint32_t)((uint64_t)bestG >> 32), r) << 32) |
+                                 lane_value((uint32_t)bestG, r));
+    const bool take = c2 >= 0 && (b < 0 || g2 > g || (g2 == g && c2 < b));
+    b = take ? c2 : b;
+    g = take ? g2 : g;
+  }
+  best = b;
+  bestG = g;
+}
+
+// Add (c, w) of row position f to the LDS table of mask + 1 slots: its slot; fresh: the key
+// is new.  The table is at most half full.
+template <bool SMALL>
+__device__ inline uint32_t table_add(Pair *tab, uint32_t *pos, uint32_t mask, uint32_t c, uint32_t w, uint32_t f,
+                                     bool &fresh) {
+  uint32_t h = hash_slot(c, mask);
+  for (;;) {
+    const uint32_t prev = atomicCAS(&tab[h].key, EMPTY, c);
+    fresh = prev == EMPTY;
+    if (fresh || prev == c) break;
+    h = (h + 1) & mask;
+  }
+  atomicAdd(&tab[h].val, w);
+  if (SMALL) atomicMin(&pos[h], f);
+  return h;
+}
+
+// The sum of key c (0 if it has none).
+__device__ inline uint32_t table_sum(const Pair *tab, uint32_t mask, uint32_t c) {
+  uint32_t h = hash_slot(c, mask);
+  for (;;) {
+    const Pair p = tab[h];
+    if (p.key == c) return p.val;
+    if (p.key == EMPTY) return 0u;
+    h = (h + 1) & mask;
+  }
+}
+
+// Exact mode, tier 1 (rows of up to EXACT_WAVE_MAX entries): one wave per row with an
 // LDS open-addressing table of its own, sized to the row (the smallest power of two
-// >= 2 * its length, 64 .. 1024 slots), so a block holds four rows instead of one.
+// >= 2 * its length), so a block holds four rows instead of one.  The slots that keys
+// claim are listed, so that the decision visits keys and not slots.
 // Same table keys, sums, first positions (small table) and decision as k_exact_table.
+// Bound by the latency of a row's chain of loads, so by the rows in flight: 4.5 KB per wave
+// let 32 waves live on a CU (8 KB, for rows of up to 512 entries, 20).  A sweep over R-MAT 2^19's
+// rows of 33 to 512 entries took 150 to 176 us here; these of up to 256 take 39 to 47 and
+// the others, with tier 2's, are below.
 template <int ALGO, bool SMALL = false>
 __global__ void __launch_bounds__(BLOCK)
     k_exact_wave(SweepArgs a, const int32_t *__restrict__ list, int64_t count) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  constexpr uint32_t CAPW = 2 * EXACT_T1_MAX;
-  __shared__ Pair wtab[BLOCK / WAVE][CAPW];
+  constexpr uint32_t CAPW = 2 * EXACT_WAVE_MAX;
+  __shared__ __attribute__((aligned(16))) Pair wtab[BLOCK / WAVE][CAPW];
   __shared__ uint32_t wpos[BLOCK / WAVE][SMALL ? CAPW : 1];
-  const int lane = lane_id(), w = threadIdx.x / WAVE;
+  __shared__ uint16_t wcell[BLOCK / WAVE][EXACT_WAVE_MAX];
+  const int lane = lane_id(), w = uniform((int32_t)(threadIdx.x / WAVE));
   const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
   if (r < count) {
@@ -1735,24 +1800,33 @@ __global__ void __launch_bounds__(BLOCK)
     if (frozen(a, i)) {
       if (lane == 0) a.Cnew[i] = community_of_self<ALGO>(a, i);
     } else {
-      const int64_t lo = a.g.off[i], hi = a.g.off[i + 1];
+      const int64_t lo = uniform(a.g.off[i]), hi = uniform(a.g.off[i + 1]);
+      const int32_t bi = ALGO == ALGO_REFINE ? uniform(a.bound[i]) : 0;
+      const int32_t d = uniform(community_of_self<ALGO>(a, i));
+      const auto load = [&](int64_t e, uint32_t &key, uint32_t &wt) {
+        const bool in = e < hi;
+        const int32_t j = in ? __builtin_nontemporal_load(a.g.idx + e) : 0;
+        wt = in ? __builtin_nontemporal_load(a.g.w + e) : 0u;
+        key = in ? stream_key<ALGO>(a, i, j, bi) : EMPTY;
+      };
+      uint32_t key, wt;
+      load(lo + lane, key, wt);  // on its way while the table is cleared
       uint32_t cap = 64;
       while (cap < CAPW && (int64_t)cap < 2 * (hi - lo)) cap <<= 1;
+      const uint32_t mask = cap - 1;
       Pair *tab = wtab[w];
       uint32_t *pos = wpos[w];
-      for (uint32_t x = lane; x < cap; x += WAVE) {
-        tab[x] = Pair{EMPTY, 0u};
-        if (SMALL) pos[x] = 0xFFFFFFFFu;
+      uint16_t *cell = wcell[w];
+      for (uint32_t x = 2 * lane; x < cap; x += 2 * WAVE) {
+        tab[x] = tab[x + 1] = Pair{EMPTY, 0u};
+        if (SMALL) pos[x] = pos[x + 1] = 0xFFFFFFFFu;
       }
       wave_sync();
-      const int32_t bi = ALGO == ALGO_REFINE ? a.bound[i] : 0;
-      const uint32_t mask = cap - 1;
+      int keys = 0;
       for (int64_t e0 = lo; e0 < hi; e0 += WAVE) {  // wave-uniform rounds
-        const int64_t e = e0 + lane;
-        const bool v = e < hi;
-        uint32_t c = v ? stream_key<ALGO>(a, i, a.g.idx[e], bi) : EMPTY;
-        if (c != EMPTY) c = slot_of(a, c);
-        uint32_t w = v ? a.g.w[e] : 0u;
+        uint32_t nkey = EMPTY, nwt = 0;
+        if (e0 + WAVE < hi) load(e0 + WAVE + lane, nkey, nwt);
+        uint32_t c = key != EMPTY ? slot_of(a, key) : EMPTY;
         // the lanes holding the first live lane's key add their weights into that lane
         // (one table update instead of one per lane, which serialise on the slot of a
         // community that many neighbours share; the lane is the group's first position)
@@ -1762,161 +1836,127 @@ __global__ void __launch_bounds__(BLOCK)
           const uint32_t ck = lane_value(c, ld);
           const bool m = c == ck;
           if (__popcll(__ballot(m)) > 1) {
-            const uint32_t sum = wave_sum(m ? w : 0u);
+            const uint32_t sum = wave_sum(m ? wt : 0u);
             if (lane == ld)
-              w = sum;
+              wt = sum;
             else if (m)
               c = EMPTY;
           }
         }
-        if (c == EMPTY) continue;
-        uint32_t h = hash_slot(c, mask);
-        while (true) {
-          const uint32_t prev = atomicCAS(&tab[h].key, EMPTY, c);
-          if (prev == EMPTY || prev == c) {
-            atomicAdd(&tab[h].val, w);
-            if (SMALL) atomicMin(&pos[h], (uint32_t)(e - lo));
-            break;
-          }
-          h = (h + 1) & mask;
-        }
+        bool fresh = false;
+        uint32_t h = 0;
+        if (c != EMPTY) h = table_add<SMALL>(tab, pos, mask, c, wt, (uint32_t)(e0 + lane - lo), fresh);
+        const uint64_t fm = __ballot(fresh);
+        if (fresh) cell[keys + __popcll(fm & lanemask_lt())] = (uint16_t)h;
+        keys += __popcll(fm);
+        key = nkey;
+        wt = nwt;
       }
       wave_sync();
-      const int32_t d = community_of_self<ALGO>(a, i);
-      const uint32_t sd = slot_of(a, (uint32_t)d);
-      uint32_t kd = 0;
-      for (uint32_t x = lane; x < cap; x += WAVE) kd += tab[x].key == sd ? tab[x].val : 0u;
-      kd = wave_sum(kd);
+      const uint32_t kd = table_sum(tab, mask, slot_of(a, (uint32_t)d));
       int32_t best = -1;
       int64_t bestG = 0;
       const int64_t W = ALGO == ALGO_LPA ? 0 : (int64_t)weight_of(a, i);
       const int64_t Ki = ALGO == ALGO_LPA ? 0 : (int64_t)a.K[i];
       const int64_t Sd = ALGO == ALGO_LPA ? 0 : (int64_t)a.Sig[d];
-      for (uint32_t x = lane; x < cap; x += WAVE) {
-        Pair p = tab[x];
-        const bool present = p.key != EMPTY;
-        if (SMALL && present) p.key = stream_key<ALGO>(a, i, a.g.idx[lo + pos[x]], bi);
-        const uint32_t sc = ALGO == ALGO_LPA ? 0u : a.Sig[present ? (int32_t)p.key : d];
-        consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)p.key, p.val, sc, present, best, bestG);
+      for (int x = lane; x < keys; x += WAVE) {
+        Pair p = tab[cell[x]];
+        if (SMALL) p.key = stream_key<ALGO>(a, i, a.g.idx[lo + pos[cell[x]]], bi);
+        consider<ALGO>(a, W, d, Ki, Sd, kd, (int32_t)p.key, p.val, best, bestG);
       }
-      // wave arg-max: larger gain first, then lower community id
-#pragma unroll
-      for (int o = WAVE / 2; o > 0; o >>= 1) {
-        const int32_t ob = __shfl_xor(best, o);
-        const int64_t og = __shfl_xor(bestG, o);
-        const bool take = ob >= 0 && (best < 0 || og > bestG || (og == bestG && ob < best));
-        best = take ? ob : best;
-        bestG = take ? og : bestG;
-      }
+      wave_best(best, bestG);
       if (lane == 0) finish<ALGO>(a, i, d, best, bestG, ct);
     }
   }
   flush_counters(a, ct);
 }
 
-// Exact mode, tier 2: a workgroup per vertex with an open-addressing table (linear
-// probing) of CAP slots in LDS.
-template <int ALGO, int CAP, bool SMALL = false>
-__global__ void __launch_bounds__(BLOCK) k_exact_table(SweepArgs a, const int32_t *__restrict__ list) {
+// Exact mode, tier 2: a workgroup of THREADS per vertex with an open-addressing table
+// (linear probing) in LDS, sized to the row, CAP = 8 * THREADS slots at most: a thread has
+// four entries of the row, whose loads are all on their way before the table is cleared, and
+// the slots that keys claim are listed, so that the decision visits keys and not slots.
+// Bound by latency as k_exact_wave: 256 threads with 2048 slots (rows of fewer than 1024
+// entries) and 1024 with 8192 fill a CU; 256 threads with 8192 slots were 8 waves on a CU
+// and looked at every slot of the largest table for every row: a sweep
+// over R-MAT 2^19's rows of 513 to 4096 entries took 136 to 194 us; rows of 257 to 1023 now
+// take 52 to 73 us and those of 1024 to 4096 23 to 31.
+template <int ALGO, int THREADS, bool SMALL = false>
+__global__ void __launch_bounds__(THREADS) k_exact_table(SweepArgs a, const int32_t *__restrict__ list) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  __shared__ Pair tab[CAP];
+  constexpr int U = 4;
+  constexpr uint32_t CAP = 2 * U * THREADS;
+  __shared__ __attribute__((aligned(16))) Pair tab[CAP];
   __shared__ uint32_t pos[SMALL ? CAP : 1];  // small table: first row position per slot
-  __shared__ uint32_t kd_s;
-  __shared__ int32_t bc[4];
-  __shared__ int64_t bg[4];
+  __shared__ uint16_t cell[CAP / 2];
+  __shared__ uint32_t ncell;
+  __shared__ int32_t bc[THREADS / WAVE];
+  __shared__ int64_t bg[THREADS / WAVE];
   const int t = threadIdx.x;
-  const int32_t i = list[blockIdx.x];
+  const int32_t i = uniform(list[blockIdx.x]);
   if (frozen(a, i)) {  // block-uniform
     if (t == 0) a.Cnew[i] = community_of_self<ALGO>(a, i);
     return;
   }
-  const int64_t lo = a.g.off[i], hi = a.g.off[i + 1];
-  constexpr uint32_t cap = CAP;
-  constexpr bool small = SMALL;  // keys are small-table slots (a.small_slots of them)
-  for (uint32_t x = t; x < cap; x += BLOCK) {
-    tab[x] = Pair{EMPTY, 0u};
-    if (small) pos[x] = 0xFFFFFFFFu;
+  const int64_t lo = uniform(a.g.off[i]), hi = uniform(a.g.off[i + 1]);
+  const int32_t bi = ALGO == ALGO_REFINE ? uniform(a.bound[i]) : 0;
+  const int32_t d = uniform(community_of_self<ALGO>(a, i));
+  // an absent entry reads the row's first and is masked
+  uint32_t cs[U], ws[U];
+  int32_t js[U], bs[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t e = lo + t + u * THREADS, es = e < hi ? e : lo;
+    js[u] = __builtin_nontemporal_load(a.g.idx + es);
+    ws[u] = __builtin_nontemporal_load(a.g.w + es);
+    bs[u] = bi;
   }
-  if (t == 0) kd_s = 0;
-  __syncthreads();
-  const int32_t bi = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+  neighbour_keys<ALGO, U>(a, js, bs, cs);
+  uint32_t cap = 2 * THREADS;
+  while (cap < CAP && (int64_t)cap < 2 * (hi - lo)) cap <<= 1;
   const uint32_t mask = cap - 1;
-  // four entries per thread and round: their loads and gathers are issued together
-  // (an absent entry reads the row's first and is masked), then inserted
-  constexpr int U = 4;
-  for (int64_t e0 = lo + t; e0 < hi; e0 += U * BLOCK) {
-    uint32_t cs[U], ws[U];
-    int32_t js[U], bs[U];
+  for (uint32_t x = 2 * t; x < cap; x += 2 * THREADS) {
+    tab[x] = tab[x + 1] = Pair{EMPTY, 0u};
+    if (SMALL) pos[x] = pos[x + 1] = 0xFFFFFFFFu;
+  }
+  if (t == 0) ncell = 0;
+  __syncthreads();
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t e = e0 + (int64_t)u * BLOCK;
-      const bool v = e < hi;
-      const int64_t es = v ? e : lo;
-      js[u] = a.g.idx[es];
-      bs[u] = bi;
-      ws[u] = a.g.w[es];
-    }
-    neighbour_keys<ALGO, U>(a, js, bs, cs);
-#pragma unroll
-    for (int u = 0; u < U; ++u)  // self-loops are skipped
-      cs[u] |= ((e0 + (int64_t)u * BLOCK) < hi && js[u] != i) ? 0u : EMPTY;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (cs[u] == EMPTY) continue;
-      const uint32_t c = slot_of(a, cs[u]);  // the table key
-      uint32_t h = hash_slot(c, mask);
-      while (true) {
-        uint32_t prev = atomicCAS(&tab[h].key, EMPTY, c);
-        if (prev == EMPTY || prev == c) {
-          atomicAdd(&tab[h].val, ws[u]);
-          if (small) atomicMin(&pos[h], (uint32_t)(e0 + (int64_t)u * BLOCK - lo));
-          break;
-        }
-        h = (h + 1) & mask;
-      }
-    }
+  for (int u = 0; u < U; ++u) {
+    const uint32_t f = (uint32_t)(t + u * THREADS);
+    if (lo + (int64_t)(f & ~(uint32_t)(WAVE - 1)) >= hi) break;  // wave-uniform: no entry left
+    bool fresh = false;
+    uint32_t h = 0;
+    if (lo + f < hi && js[u] != i && cs[u] != EMPTY)  // self-loops are skipped
+      h = table_add<SMALL>(tab, pos, mask, slot_of(a, cs[u]), ws[u], f, fresh);
+    const uint64_t fm = __ballot(fresh);
+    if (fm == 0) continue;
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(&ncell, (uint32_t)__popcll(fm));
+    base = uniform(base);
+    if (fresh) cell[base + __popcll(fm & lanemask_lt())] = (uint16_t)h;
   }
   __syncthreads();
-  const int32_t d = community_of_self<ALGO>(a, i);
-  const uint32_t sd = slot_of(a, (uint32_t)d);
-  for (uint32_t x = t; x < cap; x += BLOCK) {
-    Pair p = tab[x];
-    if (p.key == sd) kd_s = p.val;
-  }
-  __syncthreads();
-  const uint32_t kd = kd_s;
+  const uint32_t kd = table_sum(tab, mask, slot_of(a, (uint32_t)d)), keys = ncell;
   int32_t best = -1;
   int64_t bestG = 0;
   const int64_t W = ALGO == ALGO_LPA ? 0 : (int64_t)weight_of(a, i);
   const int64_t Ki = ALGO == ALGO_LPA ? 0 : (int64_t)a.K[i];
   const int64_t Sd = ALGO == ALGO_LPA ? 0 : (int64_t)a.Sig[d];
-  for (uint32_t x = t; x < cap; x += BLOCK) {
-    Pair p = tab[x];
-    const bool present = p.key != EMPTY;
-    if (small && present) {
-      // the slot stands for its first key: the key of its earliest row entry
-      const uint32_t f = pos[x];
-      p.key = stream_key<ALGO>(a, i, a.g.idx[lo + f], bi);
-    }
-    const uint32_t sc = ALGO == ALGO_LPA ? 0u : a.Sig[present ? (int32_t)p.key : d];
-    consider_v<ALGO>(W, d, Ki, Sd, kd, (int32_t)p.key, p.val, sc, present, best, bestG);
+  for (uint32_t x = t; x < keys; x += THREADS) {
+    Pair p = tab[cell[x]];
+    // a small table's slot stands for its first key: the key of its earliest row entry
+    if (SMALL) p.key = stream_key<ALGO>(a, i, a.g.idx[lo + pos[cell[x]]], bi);
+    consider<ALGO>(a, W, d, Ki, Sd, kd, (int32_t)p.key, p.val, best, bestG);
   }
   // block arg-max: larger gain first, then lower community id
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    int32_t ob = __shfl_xor(best, o);
-    int64_t og = __shfl_xor(bestG, o);
-    bool take = ob >= 0 && (best < 0 || og > bestG || (og == bestG && ob < best));
-    best = take ? ob : best;
-    bestG = take ? og : bestG;
-  }
+  wave_best(best, bestG);
   if (lane_id() == 0) {
     bc[t / WAVE] = best;
     bg[t / WAVE] = bestG;
   }
   __syncthreads();
   if (t == 0) {
-    for (int q = 1; q < 4; ++q) {
+    for (int q = 1; q < THREADS / WAVE; ++q) {
       bool take = bc[q] >= 0 && (best < 0 || bg[q] > bestG || (bg[q] == bestG && bc[q] < best));
       best = take ? bc[q] : best;
       bestG = take ? bg[q] : bestG;
@@ -2145,7 +2185,7 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n) {
 //          most 2^b <= 64 chunks (b = 1..6), 7 = longer rows;
 //   MG with K = 32 / 64: 0 = at most exact_t0 entries, 1 = one wave per row, 2 = split
 //          rows (more than max(L, WAVE_SPLIT) entries);
-//   exact: tiers 0..3 by degree.
+//   exact: tiers 0..3 by degree; 4 counts the tier-2 rows for the smaller workgroup.
 //   every mode: rows without entries (category 8) are sorted last and listed in no
 //          kernel's work: their label can never change, so no sweep writes it, and
 //          callers keep both label buffers equal for them.
@@ -2154,10 +2194,11 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n) {
 //   every mode: 11..15 count the rows of category 0 or 9 that take the short rows' kernel
 //          by class: 1..3, 4..7, 8..15, 16..32 entries, and longer ones.
 constexpr int NCAT = 16;
+constexpr int CAT_BLOCK = 4;  // exact: tier-2 rows of fewer than EXACT_BLOCK_MAX entries
 constexpr int CAT_EMPTY = 8;
 constexpr int CAT_LIGHT = 10;
 constexpr int CAT_CLASS = 11;
-constexpr int CAT_SHORT = 9;  // MG: rows whose sketch cannot lose weight (exact one-lane kernel)
+constexpr int CAT_SHORT = 9;  // MG: rows whose sketch cannot lose weight (short rows' kernel)
 
 __global__ void __launch_bounds__(BLOCK)
     k_schedule_keys(const int64_t *off, int32_t n, SchedParams sp, uint64_t *key, uint32_t *val,
@@ -2182,9 +2223,12 @@ __global__ void __launch_bounds__(BLOCK)
       cat = CAT_EMPTY;
       k = 255;  // after every other key of every mode
     } else if (mode == MODE_EXACT) {
-      cat = deg <= sp.exact_t0 ? 0 : deg <= sp.exact_t1 ? 1 : deg <= sp.exact_t2 ? 2 : 3;
-      k = cat == 0 ? (uint64_t)(64 - b) : (uint64_t)(128 + cat);
+      const int64_t t1 = sp.exact_t1 < EXACT_WAVE_MAX ? sp.exact_t1 : EXACT_WAVE_MAX;
+      cat = deg <= sp.exact_t0 ? 0 : deg <= t1 ? 1 : deg <= sp.exact_t2 ? 2 : 3;
+      // heavy rows first in each tier
+      k = cat == 0 ? (uint64_t)(64 - b) : (uint64_t)(128 + (cat - 1) * 32 + (b < 31 ? 31 - b : 0));
       shortrow = cat == 0;
+      if (cat == 2 && deg < EXACT_BLOCK_MAX) cls = CAT_BLOCK;
     } else if (sp.wave) {  // K >= 32: short rows exact, split rows, the rest one wave each
       // (K = 128 / 256: every other row is a split row, one wave per chunk)
       cat = deg <= sp.exact_t0 ? 0 : (sp.k > WAVE || (deg > L && deg > WAVE_SPLIT)) ? 2 : 1;
@@ -2377,6 +2421,7 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
       s.ntier[q] = (int64_t)h[q];
       pos += (int64_t)h[q];
     }
+    s.nblock = (int64_t)h[CAT_BLOCK];
     if (s.ntier[3] > 0) {
       int64_t c3 = s.ntier[3];
       s.hbase = a.take<int64_t>(c3 + 1);
@@ -2606,8 +2651,16 @@ static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, h
     MGCD_LAUNCHED();
   }
   if (s.ntier[2] > 0) {
-    k_exact_table<ALGO, 8192, SMALL><<<(unsigned)s.ntier[2], BLOCK, 0, st>>>(a, s.tier[2]);
-    MGCD_LAUNCHED();
+    const int64_t big = s.ntier[2] - s.nblock;
+    if (big > 0) {
+      k_exact_table<ALGO, EXACT_T2_MAX / 4, SMALL><<<(unsigned)big, EXACT_T2_MAX / 4, 0, st>>>(a, s.tier[2]);
+      MGCD_LAUNCHED();
+    }
+    if (s.nblock > 0) {
+      k_exact_table<ALGO, EXACT_BLOCK_MAX / 4, SMALL><<<(unsigned)s.nblock, EXACT_BLOCK_MAX / 4, 0, st>>>(
+          a, s.tier[2] + big);
+      MGCD_LAUNCHED();
+    }
   }
   mark(s, ev, 2, st);
   if (s.ntier[3] > 0) {

@@ -167,6 +167,7 @@ struct Schedule {
   // exact mode
   int32_t *tier[4] = {nullptr, nullptr, nullptr, nullptr};
   int64_t ntier[4] = {0, 0, 0, 0};
+  int64_t nblock = 0;         // exact: the last rows of tier 2, fewer than EXACT_BLOCK_MAX entries each
   ShortRows shorts{};         // tier 0: its rows of at most 32 entries, after
   int64_t ntail = 0;          // the longer ones (a raised exact_small)
   int64_t *hbase = nullptr;   // [ntier[3]+1] global hash region of each tier-3 vertex
@@ -188,8 +189,8 @@ struct Schedule {
 //   row_lanes_log2: rows of more than 2^row_lanes_log2 chunks (at most 64) take the
 //                   long-row path;
 //   exact_t0/t1/t2: exact mode, rows of at most t0 entries use one lane each, at most
-//                   t1 (<= 512) the 1024-slot LDS table, at most t2 (<= 4096) the
-//                   8192-slot LDS table, longer rows a global table.
+//                   t1 (<= 512; EXACT_WAVE_MAX) a wave with an LDS table, at most t2
+//                   (<= 4096) a workgroup with an LDS table, longer rows a global table.
 struct SchedParams {
   int mode = MODE_ALG1;
   int k = 8;
@@ -200,13 +201,17 @@ struct SchedParams {
                       // wave each
   // K <= 16, Algorithm 1 or the textbook rule: rows of at most mg_short entries hold at
   // most K distinct keys, so no update or merge ever removes weight and the sketch is
-  // the row's exact table; they take the exact one-lane kernel (0: none).  short_auto:
+  // the row's exact table; they take the short rows' kernel (0: none).  short_auto:
   // only when the graph's average row has at most mg_short entries (most rows are
   // short; on skewed graphs the extra launch costs more than the rows it takes over)
   int64_t mg_short = 0;
   bool short_auto = false;
 };
 constexpr int64_t EXACT_T1_MAX = 512, EXACT_T2_MAX = 4096;
+// Rows of at most EXACT_WAVE_MAX entries (and t1) take a wave each; of tier 2's rows, those
+// of fewer than EXACT_BLOCK_MAX entries take a workgroup of EXACT_BLOCK_MAX / 4 threads,
+// the others one of EXACT_T2_MAX / 4: the LDS of each then lets a CU's waves all live.
+constexpr int64_t EXACT_WAVE_MAX = 256, EXACT_BLOCK_MAX = 1024;
 // exact mode, global tables: entries inserted by one workgroup, slots scored by one
 constexpr int64_t GSEG = 4096, TSEG = 8192;
 // K = 32 / 64: rows of more than max(L, WAVE_SPLIT) entries are split over one wave per
@@ -214,9 +219,10 @@ constexpr int64_t GSEG = 4096, TSEG = 8192;
 constexpr int64_t WAVE_SPLIT = 512;
 // A level of the merge tree of split rows is a launch of its own while a row has more than
 // TREE_NODES nodes; the levels above are one launch, a workgroup of TREE_BLOCK threads per
-// row, which has eight merges in flight at about 1.8 us each.  At 64 nodes its four rounds
-// take what a launch takes (6 to 10 us); with a launch for every level the trees of
-// R-MAT 2^18's split rows (at most 28 nodes) took 73 us a sweep, in one launch 7 to 14.
+// row, which has eight merges in flight at about 1.4 us each.  At 64 nodes its four rounds
+// take about what a launch and its gap take (4.5 us and more; a tree of 49 nodes 10.5); with
+// a launch for every level the trees of R-MAT 2^18's split rows (at most 28 nodes) took
+// 73 us a sweep, in one launch 7 to 14.
 constexpr int64_t TREE_NODES = 64;
 constexpr int TREE_BLOCK = 512;
 

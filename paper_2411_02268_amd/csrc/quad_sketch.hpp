@@ -17,7 +17,7 @@ __device__ inline uint32_t quad_perm(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
 }
 // lanes [1,0,3,2], [2,3,0,1], [3,2,1,0], [1,2,3,0]; and lane 7 - x of each eight
-constexpr int QP_XOR1 = 0xB1, QP_XOR2 = 0x4E, QP_XOR3 = 0x1B, QP_ROT1 = 0x39, QP_HALF_MIRROR = 0x141;
+constexpr int QP_XOR1 = 0xB1, QP_XOR2 = 0x4E, QP_XOR3 = 0x1B, QP_ROT1 = 0x39, QP_HALF_MIRROR = 0x141, QP_MIRROR = 0x140;
 
 // The value of the quad's lane J.
 template <int J>
