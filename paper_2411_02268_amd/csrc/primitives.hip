@@ -124,14 +124,20 @@ __global__ void __launch_bounds__(BLOCK)
 // barrier between rounds) plus its rank among the round's lanes (ballots).  The waves'
 // counts, scanned once per tile, and the tile's digit offsets then give every position.
 // All loads of the tile are in flight together.  On one tile (the smallest sorts) it takes
-// 8 us against 15 for 16 rounds between barriers; 15.5 M pairs in 122 us instead of 129
-// (3 TB/s: there it is bound by the scattered stores, 12 bytes per item in short runs).
+// 8 us against 15 for 16 rounds between barriers.
+// ORDER: the tile is put in order in LDS (keys, then values through the same words) and
+// stored from there, so that a wave's stores are runs of the same digit: bound by the
+// scattered stores, 12 bytes per item to a line each, otherwise.  15.5 M pairs by digits
+// in no order: 218 to 316 us without, 90 to 104 with (3.9 TB/s).
+template <bool ORDER>
 __global__ void __launch_bounds__(BLOCK)
     k_rs_scatter(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t *vout,
                  int64_t n, int shift, const int64_t *offs, int64_t tiles) {
   constexpr int WAVES = BLOCK / WAVE;
   __shared__ uint32_t cnt[WAVES][RS_BINS];
   __shared__ int64_t off_lds[RS_BINS];
+  __shared__ uint64_t sorted[ORDER ? RS_TILE : 1];
+  __shared__ uint32_t wsum[WAVES];
   const int t = threadIdx.x, w = t / WAVE;
   static_assert(BLOCK == RS_BINS, "thread t owns digit t");
   off_lds[t] = offs[(int64_t)t * tiles + blockIdx.x];
@@ -174,16 +180,65 @@ __global__ void __launch_bounds__(BLOCK)
     sum += c;
   }
   __syncthreads();
+  if constexpr (!ORDER) {
 #pragma unroll
-  for (int r = 0; r < RS_ITEMS; ++r) {
-    if (first + (int64_t)r * WAVE < n) {
+    for (int r = 0; r < RS_ITEMS; ++r) {
+      if (first + (int64_t)r * WAVE < n) {
+        const uint32_t d = (uint32_t)(key[r] >> shift) & (RS_BINS - 1);
+        const int64_t pos = off_lds[d] + cnt[w][d] + rank[r];
+        kout[pos] = key[r];
+        vout[pos] = val[r];
+      }
+    }
+  } else {
+    // digit t's first place in the tile, added to the waves' counts and taken off its
+    // offset, which then turns a place into a position
+    const uint32_t incl = wave_inclusive_scan(sum);
+    if (lane_id() == WAVE - 1) wsum[w] = incl;
+    __syncthreads();
+    uint32_t place = incl - sum;
+    for (int q = 0; q < w; ++q) place += wsum[q];
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) cnt[q][t] += place;
+    off_lds[t] -= place;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    const int count = n - base < RS_TILE ? (int)(n - base) : RS_TILE;
+#pragma unroll
+    for (int r = 0; r < RS_ITEMS; ++r) {
       const uint32_t d = (uint32_t)(key[r] >> shift) & (RS_BINS - 1);
-      const int64_t pos = off_lds[d] + cnt[w][d] + rank[r];
-      kout[pos] = key[r];
-      vout[pos] = val[r];
+      rank[r] += cnt[w][d];
+      if (first + (int64_t)r * WAVE < n) sorted[rank[r]] = key[r];
+    }
+    __syncthreads();
+    int64_t pos[RS_ITEMS];
+#pragma unroll
+    for (int r = 0; r < RS_ITEMS; ++r) {
+      const int x = r * BLOCK + t;
+      if (x < count) {
+        const uint64_t k = sorted[x];
+        pos[r] = off_lds[(uint32_t)(k >> shift) & (RS_BINS - 1)] + x;
+        kout[pos[r]] = k;
+      }
+    }
+    __syncthreads();
+    uint32_t *sv = reinterpret_cast<uint32_t *>(sorted);
+#pragma unroll
+    for (int r = 0; r < RS_ITEMS; ++r)
+      if (first + (int64_t)r * WAVE < n) sv[rank[r]] = val[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RS_ITEMS; ++r) {
+      const int x = r * BLOCK + t;
+      if (x < count) vout[pos[r]] = sv[x];
     }
   }
 }
+
+// Sorts of at least so many tiles put them in order before the stores: at 64 tiles that is
+// 11 to 12 us against 9 to 13, at 256 tiles 13 to 15 against 17 to 22 (two more barriers
+// and trips through LDS, which do not pay while the tiles do not fill the chip).
+constexpr int64_t RS_ORDER_TILES = 128;
 
 bool radix_sort_pairs(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, int64_t n,
                       int bits, Arena &a, hipStream_t s, int from) {
@@ -201,7 +256,10 @@ bool radix_sort_pairs(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, in
     k_rs_hist<<<(unsigned)tiles, BLOCK, 0, s>>>(ki, n, shift, hist, tiles);
     MGCD_LAUNCHED();
     scan_u32_i64(hist, offs, tiles * RS_BINS, nullptr, a, s);
-    k_rs_scatter<<<(unsigned)tiles, BLOCK, 0, s>>>(ki, vi, ko, vo, n, shift, offs, tiles);
+    if (tiles >= RS_ORDER_TILES)
+      k_rs_scatter<true><<<(unsigned)tiles, BLOCK, 0, s>>>(ki, vi, ko, vo, n, shift, offs, tiles);
+    else
+      k_rs_scatter<false><<<(unsigned)tiles, BLOCK, 0, s>>>(ki, vi, ko, vo, n, shift, offs, tiles);
     MGCD_LAUNCHED();
     flip = !flip;
   }
