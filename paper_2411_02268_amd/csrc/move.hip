@@ -2036,17 +2036,33 @@ __global__ void __launch_bounds__(BLOCK)
       if (SMALL) atomicMin(&lp[h], (uint32_t)(b0 + t + (int64_t)u * BLOCK - rlo));
     }
     __syncthreads();
-    for (uint32_t x = t; x < LCAP; x += BLOCK) {
-      const uint32_t c = lk[x];
-      if (c == EMPTY) continue;
-      uint32_t h = hash_slot(c, mask);
-      while (true) {
-        const uint32_t prev = atomicCAS(&tab[h].key, EMPTY, c);
-        if (prev == EMPTY || prev == c) break;
-        h = (h + 1) & mask;
+    // key and sum go in by one 64-bit swap when the slot is free, by an add when it holds
+    // the key; four swaps of a thread are under way together (a first sweep over R-MAT
+    // 2^19's rows of more than 4096 entries: 108 us; with a swap of the key and an add one
+    // after another 150 to 179)
+    for (uint32_t x0 = t; x0 < LCAP; x0 += U * BLOCK) {
+      uint32_t c[U], h[U];
+      unsigned long long old[U];
+      const auto swap = [&](uint32_t slot, uint32_t key, uint32_t sum) {
+        return atomicCAS(reinterpret_cast<unsigned long long *>(tab + slot), (unsigned long long)EMPTY,
+                         ((unsigned long long)sum << 32) | key);
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c[u] = lk[x0 + u * BLOCK];
+        h[u] = hash_slot(c[u], mask);
+        if (c[u] != EMPTY) old[u] = swap(h[u], c[u], lv[x0 + u * BLOCK]);
       }
-      atomicAdd(&tab[h].val, lv[x]);
-      if (SMALL) atomicMin(&pos[h], lp[x]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (c[u] == EMPTY) continue;
+        while ((uint32_t)old[u] != EMPTY && (uint32_t)old[u] != c[u]) {
+          h[u] = (h[u] + 1) & mask;
+          old[u] = swap(h[u], c[u], lv[x0 + u * BLOCK]);
+        }
+        if ((uint32_t)old[u] == c[u]) atomicAdd(&tab[h[u]].val, lv[x0 + u * BLOCK]);
+        if (SMALL) atomicMin(&pos[h[u]], lp[x0 + u * BLOCK]);
+      }
     }
     __syncthreads();  // the flush has read the table before the next round clears it
   }
