@@ -144,6 +144,9 @@ void launch_scatter_labels(const int32_t *map, const int32_t *val, int32_t *out,
 // bounds within the tile, stored when the row lies inside the tile and added
 // atomically (to a zeroed K) when it crosses a tile boundary.  Tile totals go to
 // SPREAD copies of W, folded by k_fold_total.
+// Bound by a tile's chain of loads: the weights come as two 128-bit loads per thread straight
+// into the scan, and the bounds of a thread's first row with them.  R-MAT 2^20 (31 M
+// weights): 72 us with weights through LDS, then the bounds; now 57.
 constexpr int DG_ITEMS = 8, DG_TILE = BLOCK * DG_ITEMS;
 
 __device__ inline int32_t row_of_entry(const int64_t *off, int32_t lo, int32_t hi, int64_t e) {
@@ -184,17 +187,25 @@ static int32_t *tile_first_rows(const Graph &g, Arena &a, hipStream_t st) {
   return first;
 }
 
+// Whether the workspace holds the table (a fixed scratch may not: then each workgroup finds
+// its rows by binary search).
+static bool tile_table_fits(const Graph &g, const Arena &a) {
+  const size_t tb = (size_t)(ceil_div(g.nnz, SF_TILE) + 1) * 4;
+  return ((a.used + 255) & ~(size_t)255) + tb <= a.cap;
+}
+
 // Rows of a tile of consecutive CSR entries [e0, e1) (non-empty): the rows meeting it
 // lie in r0 .. r1 (from the tile table, or two binary searches when first is null);
 // every row r0 < r <= r1 that starts inside the tile marks its first position in an
 // LDS count array, whose inclusive prefix sum then gives the entry at tile position x
-// the row r0 + starts[x] (no per-entry search).  Whole-workgroup call; returns r0.
+// the row r0 + starts[x] (no per-entry search).  starts is 16-byte aligned.
+// Whole-workgroup call; returns r0.
 __device__ inline int32_t tile_rows(const Graph &g, int64_t e0, int64_t e1, uint32_t *starts,
                                     const int32_t *first) {
   __shared__ uint32_t wsum[BLOCK / WAVE];
   __shared__ int32_t sr[2];
   const int t = threadIdx.x, w = t / WAVE;
-  for (int x = t; x < SF_TILE; x += BLOCK) starts[x] = 0;
+  for (int x = t; x < SF_TILE / 4; x += BLOCK) reinterpret_cast<v4u *>(starts)[x] = v4u{0u, 0u, 0u, 0u};
   if (first) {
     if (t < 2) sr[t] = first[blockIdx.x + t];
   } else {
@@ -210,22 +221,25 @@ __device__ inline int32_t tile_rows(const Graph &g, int64_t e0, int64_t e1, uint
   }
   __syncthreads();
   // inclusive prefix sum of the counts: thread t owns positions SF_ITEMS*t ..
-  uint32_t v[SF_ITEMS], run = 0;
-#pragma unroll
-  for (int q = 0; q < SF_ITEMS; ++q) {
-    v[q] = starts[t * SF_ITEMS + q];
-    run += v[q];
-  }
+  static_assert(SF_ITEMS == 8, "two 128-bit words per thread");
+  v4u *own = reinterpret_cast<v4u *>(starts + t * SF_ITEMS);
+  const v4u a = own[0], b = own[1];
+  const uint32_t run = a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
   const uint32_t incl = wave_inclusive_scan(run);
   if (lane_id() == WAVE - 1) wsum[w] = incl;
   __syncthreads();
   uint32_t acc = incl - run;
   for (int q = 0; q < w; ++q) acc += wsum[q];
-#pragma unroll
-  for (int q = 0; q < SF_ITEMS; ++q) {
-    acc += v[q];
-    starts[t * SF_ITEMS + q] = acc;
-  }
+  v4u x = {acc + a.x, 0u, 0u, 0u};
+  x.y = x.x + a.y;
+  x.z = x.y + a.z;
+  x.w = x.z + a.w;
+  own[0] = x;
+  x.x = x.w + b.x;
+  x.y = x.x + b.y;
+  x.z = x.y + b.z;
+  x.w = x.z + b.w;
+  own[1] = x;
   __syncthreads();
   return r0;
 }
@@ -233,34 +247,36 @@ __device__ inline int32_t tile_rows(const Graph &g, int64_t e0, int64_t e1, uint
 
 __global__ void __launch_bounds__(BLOCK)
     k_row_weight_sums(Graph g, const int32_t *first, uint32_t *K, unsigned long long *Wpart) {
-  __shared__ uint32_t ex[DG_TILE + 1];
+  __shared__ __attribute__((aligned(16))) uint32_t ex[DG_TILE + 4];
   __shared__ uint32_t wsum[BLOCK / WAVE];
   __shared__ unsigned long long wtot[BLOCK / WAVE];
   __shared__ int32_t sr[2];
   const int t = threadIdx.x, w = t / WAVE;
   const int64_t e0 = (int64_t)blockIdx.x * DG_TILE;
   const int64_t e1 = e0 + DG_TILE < g.nnz ? e0 + DG_TILE : g.nnz;
-  static_assert(DG_TILE == SF_TILE, "one tile table");
-  if (first) {  // rows meeting the tile lie in sr[0] .. sr[1]
-    if (t < 2) sr[t] = first[blockIdx.x + t];
+  static_assert(DG_TILE == SF_TILE && DG_ITEMS == 8, "one tile table; two 128-bit loads per thread");
+  // thread t owns positions 8 t ..; its first row's bounds are read with the weights
+  const int64_t p = e0 + t * DG_ITEMS;
+  const v4u wa = load4(g.w, p, g.nnz, p < g.nnz), wb = load4(g.w, p + 4, g.nnz, p + 4 < g.nnz);
+  int32_t r0 = 0, r1 = -1;
+  int64_t lo0 = 0, hi0 = 0;
+  if (first) {  // rows meeting the tile lie in r0 .. r1
+    r0 = first[blockIdx.x];
+    r1 = first[blockIdx.x + 1];
+    if ((int64_t)r0 + t <= r1) {
+      lo0 = g.off[r0 + t];
+      hi0 = g.off[r0 + t + 1];
+    }
   } else {
     if (t == 0) sr[0] = row_of_entry(g.off, 0, g.n - 1, e0);
     if (t == 1) sr[1] = row_of_entry(g.off, 0, g.n - 1, e1 - 1);
   }
+  const uint32_t v[DG_ITEMS] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
   unsigned long long tsum = 0;
+  uint32_t run = 0;
 #pragma unroll
   for (int q = 0; q < DG_ITEMS; ++q) {
-    const int x = q * BLOCK + t;
-    const uint32_t v = e0 + x < e1 ? __builtin_nontemporal_load(g.w + e0 + x) : 0u;
-    ex[x] = v;
-    tsum += v;
-  }
-  __syncthreads();
-  // exclusive prefix sums in place: thread t owns positions DG_ITEMS*t ..
-  uint32_t v[DG_ITEMS], run = 0;
-#pragma unroll
-  for (int q = 0; q < DG_ITEMS; ++q) {
-    v[q] = ex[t * DG_ITEMS + q];
+    tsum += v[q];
     run += v[q];
   }
   const uint32_t incl = wave_inclusive_scan(run);
@@ -268,13 +284,18 @@ __global__ void __launch_bounds__(BLOCK)
   if (lane_id() == WAVE - 1) wsum[w] = incl;
   if (lane_id() == 0) wtot[w] = tsum;
   __syncthreads();
+  // exclusive prefix sums of the tile
   uint32_t acc = incl - run;
   for (int q = 0; q < w; ++q) acc += wsum[q];
+  uint32_t x[DG_ITEMS];
 #pragma unroll
   for (int q = 0; q < DG_ITEMS; ++q) {
-    ex[t * DG_ITEMS + q] = acc;
+    x[q] = acc;
     acc += v[q];
   }
+  v4u *ex4 = reinterpret_cast<v4u *>(ex + t * DG_ITEMS);
+  ex4[0] = v4u{x[0], x[1], x[2], x[3]};
+  ex4[1] = v4u{x[4], x[5], x[6], x[7]};
   if (t == BLOCK - 1) ex[DG_TILE] = acc;
   __syncthreads();
   if (t == 0) {
@@ -282,9 +303,13 @@ __global__ void __launch_bounds__(BLOCK)
     for (int q = 0; q < BLOCK / WAVE; ++q) total += wtot[q];
     if (total) atomicAdd(&Wpart[spread_copy()], total);
   }
-  const int32_t r0 = sr[0], r1 = sr[1];
+  if (!first) {
+    r0 = sr[0];
+    r1 = sr[1];
+  }
   for (int64_t r = (int64_t)r0 + t; r <= r1; r += BLOCK) {
-    const int64_t lo = g.off[r], hi = g.off[r + 1];
+    const bool read = first && r == (int64_t)r0 + t;
+    const int64_t lo = read ? lo0 : g.off[r], hi = read ? hi0 : g.off[r + 1];
     const int64_t a = lo > e0 ? lo : e0, b = hi < e1 ? hi : e1;
     if (b <= a) continue;  // empty row
     const uint32_t part = ex[b - e0] - ex[a - e0];
@@ -309,10 +334,7 @@ void launch_degrees(const Graph &g, uint32_t *K, unsigned long long *W, Arena &a
   launch_zero_u64(part, SPREAD, st);
   if (g.n > 0) zero_u32(K, g.n, st);
   if (g.nnz > 0) {
-    // the tile table when the workspace holds it (a fixed scratch may not): else each
-    // workgroup finds its rows by binary search
-    const size_t tb = (size_t)(ceil_div(g.nnz, SF_TILE) + 1) * 4;
-    const int32_t *first = ((a.used + 255) & ~(size_t)255) + tb <= a.cap ? tile_first_rows(g, a, st) : nullptr;
+    const int32_t *first = tile_table_fits(g, a) ? tile_first_rows(g, a, st) : nullptr;
     k_row_weight_sums<<<(unsigned)ceil_div(g.nnz, DG_TILE), BLOCK, 0, st>>>(g, first, K, part);
     MGCD_LAUNCHED();
   }
@@ -369,15 +391,17 @@ int32_t canonical(const int32_t *C, int32_t n, int32_t *out, Arena &a, hipStream
 // Weight of the intra-community entries (sigma of Eq. 1 summed over communities):
 // SF_TILE consecutive entries per workgroup with their rows from tile_rows, every
 // entry's C[row] and C[j] gathered together; the workgroup total goes to one of SPREAD
-// copies of terms[0].
+// copies of terms[0].  Bound by the gathers of C[j] (147 us for R-MAT 2^20's 31 M from 4 MB
+// at the rate that such gathers reach): 214 us with a binary search for every tile's rows,
+// 185 with the tile table.
 __global__ void __launch_bounds__(BLOCK)
-    k_intra(Graph g, const int32_t *C, unsigned long long *terms) {
-  __shared__ uint32_t starts[SF_TILE];
+    k_intra(Graph g, const int32_t *first, const int32_t *C, unsigned long long *terms) {
+  __shared__ __attribute__((aligned(16))) uint32_t starts[SF_TILE];
   __shared__ unsigned long long lw[BLOCK / WAVE];
   const int t = threadIdx.x;
   const int64_t e0 = (int64_t)blockIdx.x * SF_TILE;
   const int64_t e1 = e0 + SF_TILE < g.nnz ? e0 + SF_TILE : g.nnz;
-  const int32_t r0 = tile_rows(g, e0, e1, starts, nullptr);
+  const int32_t r0 = tile_rows(g, e0, e1, starts, first);
   unsigned long long tot = 0;
 #pragma unroll
   for (int q = 0; q < SF_ITEMS; ++q) {
@@ -422,7 +446,8 @@ void modularity_terms(const Graph &g, const int32_t *C, const uint32_t *K, unsig
   uint32_t *tot = a.take<uint32_t>(g.n);
   zero_u32(tot, g.n, st);
   if (g.nnz > 0) {
-    k_intra<<<(unsigned)ceil_div(g.nnz, SF_TILE), BLOCK, 0, st>>>(g, C, terms);
+    const int32_t *first = tile_table_fits(g, a) ? tile_first_rows(g, a, st) : nullptr;
+    k_intra<<<(unsigned)ceil_div(g.nnz, SF_TILE), BLOCK, 0, st>>>(g, first, C, terms);
     MGCD_LAUNCHED();
   }
   k_comm_tot<<<grid_for(g.n), BLOCK, 0, st>>>(C, K, g.n, tot);
@@ -612,7 +637,7 @@ __global__ void k_row_pos(const uint32_t *mem, const int64_t *P, const int32_t *
 __global__ void __launch_bounds__(BLOCK)
     k_agg_streamify(Graph g, const int32_t *first, const int32_t *D, const int64_t *rowpos, uint32_t *skey,
                     uint32_t *sw) {
-  __shared__ uint32_t starts[SF_TILE];
+  __shared__ __attribute__((aligned(16))) uint32_t starts[SF_TILE];
   const int t = threadIdx.x;
   const int64_t e0 = (int64_t)blockIdx.x * SF_TILE;
   const int64_t e1 = e0 + SF_TILE < g.nnz ? e0 + SF_TILE : g.nnz;
@@ -1005,7 +1030,7 @@ __device__ inline void count_heads(bool head, uint32_t row, uint32_t *rowcnt) {
 __global__ void __launch_bounds__(BLOCK)
     k_exact_keys(Graph g, const int32_t *first, const int32_t *D, int b, uint64_t *key, uint32_t *val,
                  unsigned long long *kept) {
-  __shared__ uint32_t starts[SF_TILE];
+  __shared__ __attribute__((aligned(16))) uint32_t starts[SF_TILE];
   __shared__ unsigned long long bk[BLOCK / WAVE];
   const int t = threadIdx.x;
   const int64_t e0 = (int64_t)blockIdx.x * SF_TILE;

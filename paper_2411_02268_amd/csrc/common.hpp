@@ -223,6 +223,24 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Entries e .. e + 3 of p (nnz entries; 0 past the end); nothing when off.
+__device__ inline v4u load4(const uint32_t *p, int64_t e, int64_t nnz, bool on) {
+  typedef uint32_t v4a __attribute__((ext_vector_type(4), aligned(4)));
+  v4u x = {0u, 0u, 0u, 0u};
+  if (on) {
+    if (e + 4 <= nnz) {
+      x = *reinterpret_cast<const v4a *>(p + e);
+    } else {
+      x.x = p[e];
+      x.y = e + 1 < nnz ? p[e + 1] : 0u;
+      x.z = e + 2 < nnz ? p[e + 2] : 0u;
+    }
+  }
+  return x;
+}
+
 // A value that is the same in every lane, moved to a scalar register so that the
 // compiler treats what depends on it as wave-uniform (scalar branches and loops).
 __device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -534,24 +534,6 @@ struct RowShare {
   int64_t item;                              // persistent: next work item
 };
 
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
-// Entries e .. e + 3 of p (nnz entries; 0 past the end); nothing when off.
-__device__ inline v4u load4(const uint32_t *p, int64_t e, int64_t nnz, bool on) {
-  typedef uint32_t v4a __attribute__((ext_vector_type(4), aligned(4)));
-  v4u x = {0u, 0u, 0u, 0u};
-  if (on) {
-    if (e + 4 <= nnz) {
-      x = *reinterpret_cast<const v4a *>(p + e);
-    } else {
-      x.x = p[e];
-      x.y = e + 1 < nnz ? p[e + 1] : 0u;
-      x.z = e + 2 < nnz ? p[e + 2] : 0u;
-    }
-  }
-  return x;
-}
-
 // A window: positions s0 .. s0 + CAP - 1 of this wave's 16 chunks, LPC lanes (four
 // entries each) per chunk, CPR chunks per round of loads.
 constexpr int LPC = CAP / 4, CPR = WAVE / LPC, ROUNDS = WCH / 4 / CPR;
