@@ -43,7 +43,7 @@ TRAFFIC_BYTES = {
     ("leiden-mg-k16-cl24", False, 0): (79392629096, "14135e926398dd07a7f2c1975aa01f1d5d0505a6324d9e01db2eb465472917e9"),
     ("leiden-mg-k16-cl24", True, 0): (67723806128, "14135e926398dd07a7f2c1975aa01f1d5d0505a6324d9e01db2eb465472917e9"),
 }
-TRAFFIC_SOURCES = ["csrc/move.hip", "csrc/move.hpp", "csrc/sketch.hpp", "csrc/common.hpp", "csrc/staging.hpp"]
+TRAFFIC_SOURCES = ["csrc/move.hip", "csrc/move.hpp", "csrc/sketch.hpp", "csrc/common.hpp", "csrc/quad_sketch.hpp"]
 
 
 def sources_sha256() -> str:

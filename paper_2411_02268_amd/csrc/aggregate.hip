@@ -11,7 +11,7 @@
 #include "move.hpp"
 #include "primitives.hpp"
 #include "sketch.hpp"
-#include "staging.hpp"
+#include "quad_sketch.hpp"
 #include "wave_sketch.hpp"
 
 namespace mgcd {
@@ -745,56 +745,14 @@ __global__ void k_row_starts(const int64_t *off, const uint32_t *mem, int32_t n,
   if (t < n) rs[t] = off[mem[t]];
 }
 
-// Stream positions [p0, p1) of community c into the sketch.
-// Communities whose stream has at most 64 chunks: P = 2^b adjacent lanes per
-// community (P >= its chunk count), lane q sketches chunk q, the chunk sketches are
-// merged by the fixed tree with cross-lane shuffles and lane 0 writes the row.
+// Communities whose stream has at most 64 chunks, by the power of two P = 2^b that holds
+// their chunks: 64 / P of them per workgroup.
 struct AggBuckets {
-  int64_t wave_begin[7];
-  int64_t wave_end[7];
+  int64_t item_begin[7];
+  int64_t item_end[7];
   const int32_t *comm[7];
   int64_t ncomm[7];
 };
-
-template <int K>
-__device__ inline void write_row(uint32_t (&k)[K], uint32_t (&v)[K], int32_t c, Pair *rows,
-                                 uint32_t *rcount);
-
-template <int K, int MODE>
-__global__ void __launch_bounds__(BLOCK) MGCD_ROWS_OCCUPANCY(K)
-    k_agg_rows(AggStreams s, AggBuckets bk, int64_t L, Pair *rows, uint32_t *rcount) {
-  __shared__ __attribute__((aligned(16))) uint32_t swin[BLOCK / WAVE][WAVE * WROW];
-  const int lane = lane_id();
-  const int64_t wave = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;
-  int b = 6;
-  while (b > 0 && wave >= bk.wave_end[b]) --b;
-  const int logp = b;
-  const int q = lane & ((1 << logp) - 1);
-  const int64_t r = (wave - bk.wave_begin[b]) * (WAVE >> logp) + (lane >> logp);
-  const bool valid = wave < bk.wave_end[0] && r < bk.ncomm[b];
-  const int32_t c = valid ? bk.comm[b][r] : 0;
-  const int64_t base = valid ? s.P[s.mstart[c]] : 0, end = valid ? s.P[s.mstart[c + 1]] : 0;
-  const int64_t nc = (end - base + L - 1) / L;
-  RegSketch<K, MODE> sk;
-  sk.reset();
-  const int64_t p0 = base + q * L;
-  const int64_t p1 = q < nc ? (p0 + L < end ? p0 + L : end) : p0;
-  staged_fold<K, MODE>(sk, swin[threadIdx.x / WAVE], p0, p1, s.skey, s.sw);
-  sk.finalize();
-  for (int l = 0; l < logp; ++l) {
-    const int stride = 1 << l;
-    uint32_t bk_[K], bv_[K];
-#pragma unroll
-    for (int p = 0; p < K; ++p) {
-      bk_[p] = __shfl_down(sk.key[p], stride);
-      bv_[p] = __shfl_down(sk.val[p], stride);
-    }
-    const int64_t c_l = (nc + stride - 1) >> l;
-    const bool left = (q & ((2 << l) - 1)) == 0;
-    if (left && (int64_t)(q >> l) + 1 < c_l) merge_sketch<K>(sk.key, sk.val, bk_, bv_);
-  }
-  if (valid && q == 0) write_row<K>(sk.key, sk.val, c, rows, rcount);
-}
 
 template <int K>
 __device__ inline void write_row(uint32_t (&k)[K], uint32_t (&v)[K], int32_t c, Pair *rows,
@@ -820,44 +778,129 @@ struct AggLong {
   Pair *skbuf;            // [ngroups * K] group roots
 };
 
-// Wave w takes the aligned group of 64 chunks gstart[x] .. of long stream x (lane =
-// chunk within the group): the staged fold of each chunk, then the first six
-// levels of the fixed merge tree with shuffles; lane 0 writes the group's root.
+// A workgroup sketches 64 chunks, a quad of lanes each (quad_sketch.hpp): an aligned group of
+// a stream of more than 64 chunks (workgroups below ngroups), whose root goes to skbuf, or
+// the streams of a bucket.  A lane reads a quarter of each 16 positions of its chunk by
+// 128-bit loads, the next ones on their way during the fold, and every entry is broadcast to
+// the quad by DPP moves.  The chunk sketches are merged by the fixed tree in LDS and one lane
+// writes the row.
+// Bound by the latency of a chunk's fold: a lane per chunk (windows through LDS, groups and
+// buckets one launch after the other) took 180 + 110 us for R-MAT 2^20's streams (k = 8),
+// 71 us for R-MAT 2^14's and 1070 + 285 us for Chung-Lu 2^22's (k = 16), small levels there
+// 100 to 280; now 152, 22, 1048 and 29 to 119.
 template <int K, int MODE>
-__global__ void __launch_bounds__(BLOCK) MGCD_ROWS_OCCUPANCY(K)
-    k_agg_chunks(AggStreams s, AggLong lg, int64_t L) {
-  __shared__ __attribute__((aligned(16))) uint32_t swin[BLOCK / WAVE][WAVE * WROW];
-  const int64_t w = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
-  if (w >= lg.ngroups) return;
-  const int lane = lane_id();
-  const int32_t x = lg.gowner[w];
-  const int32_t c = lg.multi[x];
-  const int64_t nc = lg.cstart[x + 1] - lg.cstart[x];
-  const int64_t q = (w - lg.gstart[x]) * WAVE + lane;  // chunk index within the stream
-  const int64_t base = s.P[s.mstart[c]], end = s.P[s.mstart[c + 1]];
-  const int64_t p0 = base + q * L;
-  const int64_t p1 = q < nc ? (p0 + L < end ? p0 + L : end) : p0;
-  RegSketch<K, MODE> sk;
-  sk.reset();
-  staged_fold<K, MODE>(sk, swin[threadIdx.x / WAVE], p0, p1, s.skey, s.sw);
-  sk.finalize();
+__global__ void __launch_bounds__(BLOCK)
+    k_agg_rows(AggStreams s, AggBuckets bk, AggLong lg, int64_t L, Pair *rows, uint32_t *rcount) {
+  constexpr int SL = QuadSketch<K, MODE>::S, CH = BLOCK / QUAD;
+  static_assert(CH == WAVE, "64 chunks per workgroup");
+  __shared__ uint32_t sk[CH][K + 1], sv[CH][K + 1];
+  __shared__ int32_t snc[CH], scomm[CH];  // of the row of a chunk: its chunks here, its community
+  const int t = threadIdx.x, c = t / QUAD, ql = t % QUAD;
+  const int64_t w = blockIdx.x;
+  const bool group = w < lg.ngroups;  // block-uniform, as all of the choice below
+  int logp = 6;
+  int64_t r = 0;
+  int32_t comm = -1;
+  int64_t first = 0, nc = 0;  // first chunk here, chunks from it on
+  if (group) {
+    const int32_t x = lg.gowner[w];
+    comm = lg.multi[x];
+    first = (w - lg.gstart[x]) * CH;
+    nc = lg.cstart[x + 1] - lg.cstart[x] - first;
+  } else {
+    const int64_t item = w - lg.ngroups;
+    while (logp > 0 && item >= bk.item_end[logp]) --logp;
+    r = (item - bk.item_begin[logp]) * (CH >> logp) + (c >> logp);
+    if (r < bk.ncomm[logp]) comm = bk.comm[logp][r];
+  }
+  const int P = 1 << logp, q = c & (P - 1);
+  int64_t p0 = 0, len = 0;
+  if (comm >= 0) {
+    const int64_t base = s.P[s.mstart[comm]], end = s.P[s.mstart[comm + 1]];
+    if (!group) nc = (end - base + L - 1) / L;
+    p0 = base + (first + q) * L;
+    if (q < nc) len = p0 + L < end ? L : end - p0;
+  }
+  if (ql == 0) {
+    snc[c] = (int32_t)(nc < CH ? nc : CH);
+    scomm[c] = comm;
+  }
+  QuadSketch<K, MODE> a;
+  a.reset();
+  const auto load = [&](int64_t e, v4u &k, v4u &x) {  // nothing past the chunk's end
+    const int64_t f = e + QUAD * ql;
+    const bool on = f < len;
+    k = load4(s.skey, p0 + f, s.g.nnz, on);
+    x = load4(s.sw, p0 + f, s.g.nnz, on);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      k[u] = f + u < len ? k[u] : EMPTY;
+      x[u] = f + u < len ? x[u] : 0u;
+    }
+  };
+  v4u k, x;
+  load(0, k, x);
 #pragma unroll 1
-  for (int l = 0; l < 6; ++l) {
-    const int stride = 1 << l;
-    uint32_t bk_[K], bv_[K];
+  for (int64_t e = 0; __ballot(e < len) != 0; e += QUAD * QUAD) {
+    v4u nk, nx;
+    load(e + QUAD * QUAD, nk, nx);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a.update(quad_bcast<0>(k[u]), quad_bcast<0>(x[u]));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a.update(quad_bcast<1>(k[u]), quad_bcast<1>(x[u]));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a.update(quad_bcast<2>(k[u]), quad_bcast<2>(x[u]));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a.update(quad_bcast<3>(k[u]), quad_bcast<3>(x[u]));
+    k = nk;
+    x = nx;
+  }
+  a.finalize();
+  const auto put = [&](int ch) {
+#pragma unroll
+    for (int p = 0; p < SL; ++p) {
+      if (p * QUAD + ql < K) {
+        sk[ch][p * QUAD + ql] = a.key[p];
+        sv[ch][p * QUAD + ql] = a.val[p];
+      }
+    }
+  };
+  put(c);
+  __syncthreads();
+  // level l: node y (a multiple of 2^(l+1) chunks) takes in node y + 2^l if the row has it,
+  // a quad per merge: the first two waves for level 0, the first for the others
+#pragma unroll 1
+  for (int l = 0; l < logp; ++l) {
+    if (t < WAVE * (l == 0 ? 2 : 1)) {
+      const int y = c << (l + 1);
+      if (y < CH && ((y & (P - 1)) >> l) + 1 < ((snc[y] + (1 << l) - 1) >> l)) {
+        const int z = y + (1 << l);
+        uint32_t bk_[SL], bv_[SL];
+#pragma unroll
+        for (int p = 0; p < SL; ++p) {
+          const bool h = p * QUAD + ql < K;
+          a.key[p] = h ? sk[y][p * QUAD + ql] : EMPTY;
+          a.val[p] = h ? sv[y][p * QUAD + ql] : 0u;
+          bk_[p] = h ? sk[z][p * QUAD + ql] : EMPTY;
+          bv_[p] = h ? sv[z][p * QUAD + ql] : 0u;
+        }
+        a.merge(bk_, bv_);
+        put(y);
+      }
+      wave_sync();
+    }
+    if (l == 0) __syncthreads();
+  }
+  if (group) {
+    if (t < K) lg.skbuf[w * K + t] = Pair{sk[0][t], sv[0][t]};
+  } else if (t < CH && (t & (P - 1)) == 0 && scomm[t] >= 0) {
+    uint32_t rk[K], rv[K];
 #pragma unroll
     for (int p = 0; p < K; ++p) {
-      bk_[p] = __shfl_down(sk.key[p], stride);
-      bv_[p] = __shfl_down(sk.val[p], stride);
+      rk[p] = sk[t][p];
+      rv[p] = sv[t][p];
     }
-    const int64_t c_l = (nc + stride - 1) >> l;  // nodes at level l
-    const bool left = (lane & ((2 << l) - 1)) == 0;
-    if (left && (q >> l) + 1 < c_l) merge_sketch<K>(sk.key, sk.val, bk_, bv_);
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int p = 0; p < K; ++p)
-      lg.skbuf[w * K + p] = Pair{sk.val[p] > 0 ? sk.key[p] : EMPTY, sk.val[p]};
+    write_row<K>(rk, rv, scomm[t], rows, rcount);
   }
 }
 
@@ -1287,22 +1330,21 @@ static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, c
 }
 
 template <int K, int MODE>
-static void agg_mg(const AggStreams &s, const AggBuckets &bk, int64_t waves, const AggLong &lg,
+static void agg_mg(const AggStreams &s, const AggBuckets &bk, int64_t items, const AggLong &lg,
                    int64_t L, Pair *rows, uint32_t *rcount, hipStream_t st) {
-  if (lg.nmulti > 0) {
-    k_agg_chunks<K, MODE><<<(unsigned)ceil_div(lg.ngroups, BLOCK / WAVE), BLOCK, 0, st>>>(s, lg, L);
-    MGCD_LAUNCHED();
-    k_agg_multi<K><<<(unsigned)lg.nmulti, BLOCK, 0, st>>>(lg, rows, rcount);
+  const int64_t groups = lg.nmulti > 0 ? lg.ngroups : 0;
+  if (groups + items > 0) {
+    k_agg_rows<K, MODE><<<(unsigned)(groups + items), BLOCK, 0, st>>>(s, bk, lg, L, rows, rcount);
     MGCD_LAUNCHED();
   }
-  if (waves > 0) {
-    k_agg_rows<K, MODE><<<(unsigned)ceil_div(waves, BLOCK / WAVE), BLOCK, 0, st>>>(s, bk, L, rows, rcount);
+  if (lg.nmulti > 0) {
+    k_agg_multi<K><<<(unsigned)lg.nmulti, BLOCK, 0, st>>>(lg, rows, rcount);
     MGCD_LAUNCHED();
   }
 }
 
 template <int MODE>
-static void agg_mg_k(int k, const AggStreams &s, const AggBuckets &bk, int64_t waves, const AggLong &lg,
+static void agg_mg_k(int k, const AggStreams &s, const AggBuckets &bk, int64_t items, const AggLong &lg,
                      const AggSplit &sp, int64_t L, Pair *rows, uint32_t *rcount, const int32_t *one,
                      int64_t none, int64_t max_len, hipStream_t st) {
   switch (k) {
@@ -1310,11 +1352,11 @@ static void agg_mg_k(int k, const AggStreams &s, const AggBuckets &bk, int64_t w
     case 64: agg_wave<64, MODE>(s, one, none, sp, L, rows, rcount, max_len, st); break;
     case 128: agg_wave<128, MODE>(s, one, none, sp, L, rows, rcount, max_len, st); break;
     case 256: agg_wave<256, MODE>(s, one, none, sp, L, rows, rcount, max_len, st); break;
-    case 1: agg_mg<1, MODE>(s, bk, waves, lg, L, rows, rcount, st); break;
-    case 2: agg_mg<2, MODE>(s, bk, waves, lg, L, rows, rcount, st); break;
-    case 4: agg_mg<4, MODE>(s, bk, waves, lg, L, rows, rcount, st); break;
-    case 8: agg_mg<8, MODE>(s, bk, waves, lg, L, rows, rcount, st); break;
-    case 16: agg_mg<16, MODE>(s, bk, waves, lg, L, rows, rcount, st); break;
+    case 1: agg_mg<1, MODE>(s, bk, items, lg, L, rows, rcount, st); break;
+    case 2: agg_mg<2, MODE>(s, bk, items, lg, L, rows, rcount, st); break;
+    case 4: agg_mg<4, MODE>(s, bk, items, lg, L, rows, rcount, st); break;
+    case 8: agg_mg<8, MODE>(s, bk, items, lg, L, rows, rcount, st); break;
+    case 16: agg_mg<16, MODE>(s, bk, items, lg, L, rows, rcount, st); break;
     default: throw Error(-6, "k_aggregate must be 1, 2, 4, 8, 16, 32 or 64");
   }
 }
@@ -1426,7 +1468,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   read_spread(cnt, 8, hc, st);
   MGCD_HIP(hipStreamSynchronize(st));
   AggBuckets bk{};
-  int64_t pos = 0, waves = 0;
+  int64_t pos = 0, items = 0;
   const int32_t *bucket_rows[7];
   for (int b = 0; b <= 6; ++b) {
     bucket_rows[b] = corder + pos;
@@ -1435,9 +1477,9 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   for (int b = 6; b >= 0; --b) {  // heaviest bucket first in the grid
     bk.comm[b] = bucket_rows[b];
     bk.ncomm[b] = (int64_t)hc[b];
-    bk.wave_begin[b] = waves;
-    waves += ceil_div((int64_t)hc[b] << b, WAVE);
-    bk.wave_end[b] = waves;
+    bk.item_begin[b] = items;
+    items += ceil_div((int64_t)hc[b] << b, WAVE);
+    bk.item_end[b] = items;
   }
   const int64_t nmulti = (int64_t)hc[7];
   int32_t *multi = corder + pos;
@@ -1491,9 +1533,9 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   }
   AggStreams s{g, D, mem, mstart, P, rs, skey, sw};
   switch (mode) {
-    case MODE_ALG1: agg_mg_k<MODE_ALG1>(k, s, bk, waves, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
-    case MODE_UNCOND: agg_mg_k<MODE_UNCOND>(k, s, bk, waves, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
-    case MODE_STD: agg_mg_k<MODE_STD>(k, s, bk, waves, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
+    case MODE_ALG1: agg_mg_k<MODE_ALG1>(k, s, bk, items, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
+    case MODE_UNCOND: agg_mg_k<MODE_UNCOND>(k, s, bk, items, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
+    case MODE_STD: agg_mg_k<MODE_STD>(k, s, bk, items, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
     default: throw Error(-6, "unknown sketch mode");
   }
   int64_t total = 0;

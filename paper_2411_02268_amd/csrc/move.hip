@@ -23,7 +23,6 @@
 #include "primitives.hpp"
 #include "quad_sketch.hpp"
 #include "sketch.hpp"
-#include "staging.hpp"
 #include "wave_sketch.hpp"
 
 namespace mgcd {

@@ -2,9 +2,9 @@
 // 4p + q lives in register p of the quad's lane q, so one stream's chain of updates is
 // about a third as long as with all slots in one lane, and a wave holds 16 streams,
 // whose entries fit in LDS whole.  The lanes of a quad see the same items and take the
-// same branches; they agree through DPP quad permutes (no LDS).  Same results as
-// RegSketch: the sketch depends on the stream only, not on which free slot a new key
-// takes (a slot of value 0 is free; reviving a stale key equals inserting it afresh).
+// same branches; they agree through DPP quad permutes (no LDS).  The sketch depends on the
+// stream only, not on which free slot a new key takes (a slot of value 0 is free; reviving
+// a stale key equals inserting it afresh).
 #pragma once
 #include "common.hpp"
 

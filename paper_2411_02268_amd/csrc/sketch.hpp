@@ -1,128 +1,10 @@
-// The weighted Misra-Gries sketch held in registers (Appendix A.1, Algorithm 1).
-//
-// K slots live in 2K VGPRs of the lane that owns a stream; every loop over the
-// slots is unrolled so the compiler keeps the slots in registers (static indices,
-// no scratch).  The final sketch is a function of the stream only, not of which
-// free slot a new key takes: a slot whose value is 0 is free, and reviving a
-// stale key equals inserting it afresh.  So a new key goes to the first free slot
-// here, which needs one pass and no slot-index arithmetic.
+// Merges and sorts of K-slot sketches held in registers (Appendix A.1): every loop over
+// the slots is unrolled so the compiler keeps them in registers (static indices, no
+// scratch).
 #pragma once
 #include "common.hpp"
 
 namespace mgcd {
-
-template <int K, int MODE>
-struct RegSketch {
-  uint32_t key[K];
-  uint32_t val[K];
-  bool lossy;  // some counted weight was removed: values are lower bounds only
-
-  __device__ inline void reset() {
-#pragma unroll
-    for (int p = 0; p < K; ++p) {
-      key[p] = EMPTY;
-      val[p] = 0;
-    }
-    lossy = false;
-  }
-
-  // Add (c, w) to the sketch.
-  __device__ inline void update(uint32_t c, uint32_t w) {
-    if constexpr (MODE == MODE_ALG1) {
-      // Algorithm 1: accumulate into the slot holding c; else insert into a free
-      // slot; else subtract w from every slot (clamped at 0) and drop the item.
-      bool has = false;
-#pragma unroll
-      for (int p = 0; p < K; ++p) {
-        bool m = key[p] == c;
-        val[p] += m ? w : 0u;
-        has |= m;
-      }
-      if (!has) {
-        bool done = false;
-#pragma unroll
-        for (int p = 0; p < K; ++p) {
-          bool e = !done && val[p] == 0;
-          key[p] = e ? c : key[p];
-          val[p] = e ? w : val[p];
-          done |= e;
-        }
-        if (!done) {
-          lossy = true;
-#pragma unroll
-          for (int p = 0; p < K; ++p) val[p] = val[p] > w ? val[p] - w : 0u;
-        }
-      }
-    } else if constexpr (MODE == MODE_UNCOND) {
-      // Unconditional subtraction: a key is present while its value is positive; on
-      // a miss subtract w from every slot first, then insert into a free slot.
-      bool has = false;
-#pragma unroll
-      for (int p = 0; p < K; ++p) {
-        bool m = key[p] == c && val[p] > 0;
-        val[p] += m ? w : 0u;
-        has |= m;
-      }
-      if (!has) {
-        bool any = false;
-#pragma unroll
-        for (int p = 0; p < K; ++p) {
-          any |= val[p] > 0;
-          val[p] = val[p] > w ? val[p] - w : 0u;
-        }
-        bool done = false;
-#pragma unroll
-        for (int p = 0; p < K; ++p) {
-          bool e = !done && val[p] == 0;
-          key[p] = e ? c : key[p];
-          val[p] = e ? w : val[p];
-          done |= e;
-        }
-        lossy |= any || !done;
-      }
-    } else {  // MODE_STD: textbook weighted MG
-      bool has = false;
-#pragma unroll
-      for (int p = 0; p < K; ++p) {
-        bool m = key[p] == c && val[p] > 0;
-        val[p] += m ? w : 0u;
-        has |= m;
-      }
-      if (!has) {
-        bool done = false;
-#pragma unroll
-        for (int p = 0; p < K; ++p) {
-          bool e = !done && val[p] == 0;
-          key[p] = e ? c : key[p];
-          val[p] = e ? w : val[p];
-          done |= e;
-        }
-        if (!done) {
-          lossy = true;
-          uint32_t d = w;
-#pragma unroll
-          for (int p = 0; p < K; ++p) d = val[p] < d ? val[p] : d;
-          uint32_t rest = w - d;
-          bool put = rest == 0;
-#pragma unroll
-          for (int p = 0; p < K; ++p) {
-            val[p] -= d;
-            bool e = !put && val[p] == 0;
-            key[p] = e ? c : key[p];
-            val[p] = e ? rest : val[p];
-            put |= e;
-          }
-        }
-      }
-    }
-  }
-
-  // Keep only the candidates (positive slots); other keys become EMPTY.
-  __device__ inline void finalize() {
-#pragma unroll
-    for (int p = 0; p < K; ++p) key[p] = val[p] > 0 ? key[p] : EMPTY;
-  }
-};
 
 // Merge sketch b into sketch a (mergeable summaries, Agarwal et al. 2012): add the
 // values of equal keys; if more than K keys are positive, subtract the (K+1)-th
