@@ -34,14 +34,12 @@ PEAK_HBM_GBS = 8000.0  # MI355X HBM3E, GB/s
 # HBM bytes of one level-0 launch of the main sweep kernel, per (workload, level 0 on
 # the storage copy, short_rows), from FETCH_SIZE and WRITE_SIZE (rocprofv3 --pmc, one
 # counter per run) scaled by what the counters read for a 512 MiB device copy (FETCH
-# x 2.0, WRITE x 1.0); commands and figures in profiles/k_move_rows_rmat20_counters.md
-# and profiles/k_move_rows_cl24_leiden_counters.md.  Each figure is valid only for the
-# kernel sources it was taken on (the SHA-256 of TRAFFIC_SOURCES beside it, checked at
-# run time); traffic is reported as null when the sources differ.
+# x 2.0, WRITE x 1.0); commands and figures in profiles/k_move_rows_rmat20_counters.md.
+# Each figure is valid only for the kernel sources it was taken on (the SHA-256 of
+# TRAFFIC_SOURCES beside it, checked at run time); traffic is reported as null when the
+# sources differ.
 TRAFFIC_BYTES = {
-    ("louvain-mg-k8-rmat20", False, 0): (2223564784, "14135e926398dd07a7f2c1975aa01f1d5d0505a6324d9e01db2eb465472917e9"),
-    ("leiden-mg-k16-cl24", False, 0): (79392629096, "14135e926398dd07a7f2c1975aa01f1d5d0505a6324d9e01db2eb465472917e9"),
-    ("leiden-mg-k16-cl24", True, 0): (67723806128, "14135e926398dd07a7f2c1975aa01f1d5d0505a6324d9e01db2eb465472917e9"),
+    ("louvain-mg-k8-rmat20", False, 0): (1858319464, "4e5ef8bbc5c729028b26b9f3ccb505f016fe3f12f4404adfc647d8162ee923fc"),
 }
 TRAFFIC_SOURCES = ["csrc/move.hip", "csrc/move.hpp", "csrc/sketch.hpp", "csrc/common.hpp", "csrc/quad_sketch.hpp"]
 
@@ -69,7 +67,7 @@ def class_bytes(g, L: int, k: int, cands: float = 0.0, short: int = 0, label: in
       keys and weights (8 B) and writes and reads 4 (k + 1) B of counts per chunk.
     Class 0: the main sweep kernel (k_move_rows).  Class 1: long-row merge, second
     pass and decision (k_long_merge, k_long_count, k_long_decide).  Class 2: rows of
-    1..short entries on the exact one-lane kernel (12 B per entry, 28 B per vertex;
+    1..short entries on the short rows' kernel (12 B per entry, 28 B per vertex;
     their candidates' totals are not counted)."""
     deg = np.diff(g.offsets)
     nch = (deg + L - 1) // L
@@ -351,7 +349,7 @@ def main():
                     help="level-0 storage copy in degree order: 0 by size (default), 1 off, 2 on "
                          "(schedule only: results are the same)")
     ap.add_argument("--short-rows", type=int, default=0, choices=(0, 1, 2),
-                    help="MG rows of at most k entries on the exact one-lane kernel: 0 (default) "
+                    help="MG rows of at most k entries on the short rows' kernel: 0 (default) "
                          "when the average row has at most k entries, 1 never, 2 always "
                          "(schedule only: results are the same)")
     ap.add_argument("--no-quality-split", dest="quality_split", action="store_false",
@@ -431,7 +429,7 @@ def main():
     names = ["k_move_rows (every row of more than k entries: staged sketch, merge tree, second "
              "pass, decision; chunk sketches of rows longer than 64 chunks)",
              "k_long_merge + k_long_count + k_long_decide (rows longer than 64 chunks)",
-             "k_exact_small (rows of at most k entries: their sketch is their exact table)"]
+             "k_exact_short (rows of at most k entries: their sketch is their exact table)"]
     per_launch_ms = ms[dom] / max(sweeps, 1)
     achieved = cb[dom] / (per_launch_ms * 1e-3) / 1e9 if per_launch_ms > 0 else 0.0
     sweep_ms = ms.sum() / max(sweeps, 1)

@@ -143,7 +143,7 @@ typedef struct {
   float ms_aggregate;     /* device time in renumbering and aggregation               */
   float ms_total;         /* device time of the whole call                            */
   /* Level-0 local-moving sweeps, device time per kernel class (HIP events on the
-     call's stream).  MG: [0] the main sweep kernel (every row the sketch takes:
+     call's stream, or the device clock where a sweep is one class).  MG: [0] the main sweep kernel (every row the sketch takes:
      all rows but those that short_rows sends to the exact kernel, plus the chunk
      sketches of rows longer than 64 chunks), [1] the merge, second pass and
      decision of those long rows, [2] rows of at most k entries on the exact

@@ -139,11 +139,10 @@ void launch_scatter_labels(const int32_t *map, const int32_t *val, int32_t *out,
 
 
 // K_i = sum of row i's weights (Section 3), W = their total.  A workgroup takes
-// DG_TILE consecutive entries: their weights are staged in LDS (coalesced loads) and
-// scanned there; every row meeting the tile takes the difference of the scan at its
-// bounds within the tile, stored when the row lies inside the tile and added
-// atomically (to a zeroed K) when it crosses a tile boundary.  Tile totals go to
-// SPREAD copies of W, folded by k_fold_total.
+// DG_TILE consecutive entries and keeps the scan of their weights in LDS; every row
+// meeting the tile takes the difference of the scan at its bounds within the tile,
+// stored when the row lies inside the tile and added atomically (to a zeroed K) when it
+// crosses a tile boundary.  Tile totals go to SPREAD copies of W, folded by k_fold_total.
 // Bound by a tile's chain of loads: the weights come as two 128-bit loads per thread straight
 // into the scan, and the bounds of a thread's first row with them.  R-MAT 2^20 (31 M
 // weights): 72 us with weights through LDS, then the bounds; now 57.
@@ -1450,7 +1449,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   k_member_deg<<<grid_for(n), BLOCK, 0, st>>>(g.off, mem, n, mdeg);
   MGCD_LAUNCHED();
   scan_u32_i64(mdeg, P, n, P + n, a, st);
-  // communities: short streams (one lane each) vs long ones (chunks + merge tree)
+  // communities: short streams (one chunk) vs long ones (chunks + merge tree)
   unsigned long long *cnt = a.take<unsigned long long>(SPREAD * 9);
   launch_zero_u64(cnt, SPREAD * 9, st);
   uint64_t *ck0 = a.take<uint64_t>(m), *ck1 = a.take<uint64_t>(m);

@@ -188,7 +188,7 @@ struct Schedule {
 // changes which kernel and mapping takes a row (results never change):
 //   row_lanes_log2: rows of more than 2^row_lanes_log2 chunks (at most 64) take the
 //                   long-row path;
-//   exact_t0/t1/t2: exact mode, rows of at most t0 entries use one lane each, at most
+//   exact_t0/t1/t2: exact mode, rows of at most t0 entries take the short rows' kernel, at most
 //                   t1 (<= 512; EXACT_WAVE_MAX) a wave with an LDS table, at most t2
 //                   (<= 4096) a workgroup with an LDS table, longer rows a global table.
 struct SchedParams {
