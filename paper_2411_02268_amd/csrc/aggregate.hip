@@ -789,13 +789,13 @@ struct AggLong {
 // 100 to 280; now 152, 22, 1048 and 29 to 119.
 template <int K, int MODE>
 __global__ void __launch_bounds__(BLOCK)
-    k_agg_rows(AggStreams s, AggBuckets bk, AggLong lg, int64_t L, Pair *rows, uint32_t *rcount) {
+    k_agg_rows(AggStreams s, AggBuckets bk, AggLong lg, int64_t L, int64_t block0, Pair *rows, uint32_t *rcount) {
   constexpr int SL = QuadSketch<K, MODE>::S, CH = BLOCK / QUAD;
   static_assert(CH == WAVE, "64 chunks per workgroup");
   __shared__ uint32_t sk[CH][K + 1], sv[CH][K + 1];
   __shared__ int32_t snc[CH], scomm[CH];  // of the row of a chunk: its chunks here, its community
   const int t = threadIdx.x, c = t / QUAD, ql = t % QUAD;
-  const int64_t w = blockIdx.x;
+  const int64_t w = block0 + blockIdx.x;
   const bool group = w < lg.ngroups;  // block-uniform, as all of the choice below
   int logp = 6;
   int64_t r = 0;
@@ -923,8 +923,8 @@ __global__ void __launch_bounds__(BLOCK) MGCD_SKETCH_OCCUPANCY(K)
 
 // rows (k slots per community, rcount used) -> CSR, a thread per slot
 __global__ void k_compact_rows(const Pair *rows, const uint32_t *rcount, const int64_t *off, int32_t m,
-                               int k, int32_t *idx, uint32_t *w) {
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+                               int k, int64_t block0, int32_t *idx, uint32_t *w) {
+  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
   const int64_t c = i / k;
   const uint32_t x = (uint32_t)(i - c * k);
   if (c >= m || x >= rcount[c]) return;
@@ -966,8 +966,8 @@ __global__ void k_rev_counts(const Pair *rows, const uint32_t *rcount, int32_t m
 }
 
 __global__ void k_emit_reverse(const Pair *rows, const uint32_t *rcount, const uint32_t *ec, const int64_t *epos,
-                               int32_t m, int k, int b, uint64_t *key, uint32_t *val) {
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+                               int32_t m, int k, int b, int64_t block0, uint64_t *key, uint32_t *val) {
+  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
   const int64_t c = i / k;
   const uint32_t x = (uint32_t)(i - c * k);
   if (c >= m || x >= rcount[c]) return;
@@ -1018,10 +1018,10 @@ __global__ void k_sym_reverse(const uint64_t *ks, const uint32_t *vs, int64_t n,
   w[o] = vs[e];
 }
 
-__global__ void k_sym_forward(const Pair *rows, const uint32_t *rcount, int32_t m, int k, int b,
+__global__ void k_sym_forward(const Pair *rows, const uint32_t *rcount, int32_t m, int k, int b, int64_t block0,
                               const uint64_t *ks, const uint32_t *vs, const int64_t *rstart, const int64_t *kept,
                               const int64_t *off, int32_t *idx, uint32_t *w) {
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
   const int64_t r = i / k;
   const uint32_t x = (uint32_t)(i - r * k);
   if (r >= m || x >= rcount[r]) return;
@@ -1199,11 +1199,12 @@ struct AggSplit {
 // One wave per chunk of a split stream: its sketch, finalised; the workgroup's chunks (eight
 // neighbouring ones of a stream, K = 128 / 256: each alone) become one node.
 template <int K, int MODE>
-__global__ void __launch_bounds__(wave_group_block(K)) k_aggw_chunks(AggStreams s, AggSplit sp, int64_t L) {
+__global__ void __launch_bounds__(wave_group_block(K))
+    k_aggw_chunks(AggStreams s, AggSplit sp, int64_t L, int64_t block0) {
   constexpr int S = WaveSlots<K>::S, G = wave_group(K), WAVES = wave_group_waves(K);
   __shared__ uint32_t smap[WAVES][WaveMap<K>::WORDS];
   const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
-  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
+  const int64_t q = G > 1 ? block0 + blockIdx.x : uniform((block0 + blockIdx.x) * WAVES + wave);
   if (q >= sp.nchunks) return;
   const int32_t x = uniform(sp.owner[q]);
   const int32_t c = uniform(sp.multi[x]);
@@ -1244,9 +1245,10 @@ __global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level) {
 
 // Levels from `level` on of every split stream, one workgroup each, as in the sweeps.
 template <int K>
-__global__ void __launch_bounds__(TREE_BLOCK) k_aggw_tree(AggSplit sp, int level) {
+__global__ void __launch_bounds__(TREE_BLOCK) k_aggw_tree(AggSplit sp, int level, int64_t block0) {
   __shared__ uint32_t smap[TREE_BLOCK / WAVE][WaveMap<K>::WORDS];
-  const int64_t q0 = sp.cstart[blockIdx.x], n = sp.cstart[blockIdx.x + 1] - q0;
+  const int64_t x0 = block0 + blockIdx.x;
+  const int64_t q0 = sp.cstart[x0], n = sp.cstart[x0 + 1] - q0;
   const int wave = uniform((int32_t)(threadIdx.x / WAVE));
   for (int64_t half = (int64_t)1 << level; half < n; half *= 2) {  // block-uniform
     for (int64_t x = wave * 2 * half; x + half < n; x += TREE_BLOCK / WAVE * 2 * half)
@@ -1300,8 +1302,10 @@ template <int K, int MODE>
 static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, const AggSplit &sp,
                      int64_t L, Pair *rows, uint32_t *rcount, int64_t max_len, hipStream_t st) {
   if (sp.nmulti > 0) {
-    k_aggw_chunks<K, MODE><<<wave_group_grid(K, sp.nchunks), wave_group_block(K), 0, st>>>(s, sp, L);
-    MGCD_LAUNCHED();
+    launch_slices(wave_group_blocks(K, sp.nchunks), wave_group_block(K), [&](int64_t first, unsigned blocks) {
+      k_aggw_chunks<K, MODE><<<blocks, wave_group_block(K), 0, st>>>(s, sp, L, first);
+      MGCD_LAUNCHED();
+    });
     const int64_t G = wave_group(K), maxch = (max_len + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
@@ -1309,8 +1313,10 @@ static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, c
       MGCD_LAUNCHED();
     }
     if (((int64_t)1 << l) < maxch) {
-      k_aggw_tree<K><<<(unsigned)sp.nmulti, TREE_BLOCK, 0, st>>>(sp, l);
-      MGCD_LAUNCHED();
+      launch_slices(sp.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
+        k_aggw_tree<K><<<blocks, TREE_BLOCK, 0, st>>>(sp, l, first);
+        MGCD_LAUNCHED();
+      });
     }
     k_aggw_rows<K><<<(unsigned)ceil_div(sp.nmulti, BLOCK / WAVE), BLOCK, 0, st>>>(sp, rows, rcount);
     MGCD_LAUNCHED();
@@ -1332,10 +1338,10 @@ template <int K, int MODE>
 static void agg_mg(const AggStreams &s, const AggBuckets &bk, int64_t items, const AggLong &lg,
                    int64_t L, Pair *rows, uint32_t *rcount, hipStream_t st) {
   const int64_t groups = lg.nmulti > 0 ? lg.ngroups : 0;
-  if (groups + items > 0) {
-    k_agg_rows<K, MODE><<<(unsigned)(groups + items), BLOCK, 0, st>>>(s, bk, lg, L, rows, rcount);
+  launch_slices(groups + items, BLOCK, [&](int64_t first, unsigned blocks) {
+    k_agg_rows<K, MODE><<<blocks, BLOCK, 0, st>>>(s, bk, lg, L, first, rows, rcount);
     MGCD_LAUNCHED();
-  }
+  });
   if (lg.nmulti > 0) {
     k_agg_multi<K><<<(unsigned)lg.nmulti, BLOCK, 0, st>>>(lg, rows, rcount);
     MGCD_LAUNCHED();
@@ -1538,10 +1544,13 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     default: throw Error(-6, "unknown sketch mode");
   }
   int64_t total = 0;
+  const int64_t slot_blocks = ceil_div((int64_t)m * k, BLOCK);
   if (!symmetric) {
     offsets_from_counts(rcount, m, out_off, a, st);
-    k_compact_rows<<<grid_for((int64_t)m * k), BLOCK, 0, st>>>(rows, rcount, out_off, m, k, out_idx, out_w);
-    MGCD_LAUNCHED();
+    launch_slices(slot_blocks, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_compact_rows<<<blocks, BLOCK, 0, st>>>(rows, rcount, out_off, m, k, first, out_idx, out_w);
+      MGCD_LAUNCHED();
+    });
     total = read_i64(out_off + m, st);
   } else {
     uint32_t *ec = a.take<uint32_t>(m);
@@ -1553,8 +1562,10 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     const int b = bits_for((uint64_t)(m > 1 ? m - 1 : 1));
     uint64_t *e0 = a.take<uint64_t>(E), *e1 = a.take<uint64_t>(E);
     uint32_t *w0 = a.take<uint32_t>(E), *w1 = a.take<uint32_t>(E);
-    k_emit_reverse<<<grid_for((int64_t)m * k), BLOCK, 0, st>>>(rows, rcount, ec, epos, m, k, b, e0, w0);
-    MGCD_LAUNCHED();
+    launch_slices(slot_blocks, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_emit_reverse<<<blocks, BLOCK, 0, st>>>(rows, rcount, ec, epos, m, k, b, first, e0, w0);
+      MGCD_LAUNCHED();
+    });
     const bool ef = radix_sort_pairs(e0, w0, e1, w1, E, 2 * b, a, st, b);  // by row; columns are in order
     const uint64_t *sk = ef ? e1 : e0;
     const uint32_t *sv = ef ? w1 : w0;
@@ -1572,9 +1583,11 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     k_sym_counts<<<grid_for(m), BLOCK, 0, st>>>(rcount, rstart, kept, m, rowcnt);
     MGCD_LAUNCHED();
     offsets_from_counts(rowcnt, m, out_off, a, st);
-    k_sym_forward<<<grid_for((int64_t)m * k), BLOCK, 0, st>>>(rows, rcount, m, k, b, sk, sv, rstart, kept, out_off,
-                                                             out_idx, out_w);
-    MGCD_LAUNCHED();
+    launch_slices(slot_blocks, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_sym_forward<<<blocks, BLOCK, 0, st>>>(rows, rcount, m, k, b, first, sk, sv, rstart, kept, out_off, out_idx,
+                                              out_w);
+      MGCD_LAUNCHED();
+    });
     if (E > 0) {
       k_sym_reverse<<<grid_for(E), BLOCK, 0, st>>>(sk, sv, E, b, rows, rcount, k, rstart, kept, out_off, out_idx, out_w);
       MGCD_LAUNCHED();

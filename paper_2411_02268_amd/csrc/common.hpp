@@ -9,6 +9,8 @@
 #include <string>
 #include <vector>
 
+#include "launch.hpp"
+
 namespace mgcd {
 
 constexpr uint32_t EMPTY = 0xFFFFFFFFu;  // key of a fresh sketch slot; never a community id

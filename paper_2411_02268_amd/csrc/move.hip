@@ -272,8 +272,8 @@ __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
 }
 
 // The device clock at the start of a sweep of one kernel class (SweepArgs::stamp).
-__device__ inline void stamp_start(const SweepArgs &a) {
-  if (a.stamp && blockIdx.x == 0 && threadIdx.x == 0) *a.stamp = wall_clock64();
+__device__ inline void stamp_start(const SweepArgs &a, int64_t first = 0) {
+  if (a.stamp && first == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.stamp = wall_clock64();
 }
 
 // Key of entry (i -> j) in the stream of vertex i, or EMPTY when Algorithm 1's
@@ -1086,16 +1086,17 @@ constexpr int light_waves_per_simd() {  // what registers leave room for
 template <int K, int ALGO, int MODE, bool PERSIST>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_waves_per_simd<K>())))
     k_move_rows(SweepArgs a, const Buckets bk, int64_t L, uint32_t *keybuf, int64_t total, const int32_t *light,
-                int64_t nlight, unsigned long long *queue) {
+                int64_t nlight, int64_t first, unsigned long long *queue) {
   __shared__ RowShare<K> S;
   Counters ct;
-  stamp_start(a);
+  stamp_start(a, first);
   if constexpr (!PERSIST) {
-    if (blockIdx.x < total) {
-      row_item<K, ALGO, MODE>(a, bk, L, keybuf, S, blockIdx.x, ct);
+    const int64_t block = first + blockIdx.x;
+    if (block < total) {
+      row_item<K, ALGO, MODE>(a, bk, L, keybuf, S, block, ct);
       if (threadIdx.x < WAVE) flush_wave_counters(a, ct);
     } else {
-      const int64_t w = (blockIdx.x - total) * (BLOCK / WAVE) + threadIdx.x / WAVE;
+      const int64_t w = (block - total) * (BLOCK / WAVE) + threadIdx.x / WAVE;
       light_item<K, ALGO, MODE>(a, light, nlight, uniform(w), ct);
       flush_counters(a, ct);
     }
@@ -1127,10 +1128,11 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_
 // k_move_rows).  PERSIST as in k_move_rows, a wave taking the items.
 template <int K, int ALGO, int MODE, bool PERSIST>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(light_waves_per_simd<K>())))
-    k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, unsigned long long *queue) {
-  const int64_t wave = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+    k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t first,
+                 unsigned long long *queue) {
+  const int64_t wave = uniform(((first + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
-  stamp_start(a);
+  stamp_start(a, first);
   if constexpr (!PERSIST) {
     light_item<K, ALGO, MODE>(a, rows, nrows, wave, ct);
     flush_counters(a, ct);
@@ -1301,12 +1303,12 @@ template <int K, int ALGO, int MODE>
 __global__ void __launch_bounds__(wave_group_block(K))
     k_wave_chunks(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
                   const int32_t *__restrict__ owner, int64_t nnodes, int64_t L, uint32_t *keybuf,
-                  Pair *node, uint32_t *nflag, uint32_t *count) {
+                  int64_t block0, Pair *node, uint32_t *nflag, uint32_t *count) {
   if (level_over(a)) return;  // batched: every graph has stopped
   constexpr int S = WaveSlots<K>::S, G = wave_group(K), WAVES = wave_group_waves(K);
   __shared__ uint32_t smap[WAVES][WaveMap<K>::WORDS];
   const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
-  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
+  const int64_t q = G > 1 ? block0 + blockIdx.x : uniform((block0 + blockIdx.x) * WAVES + wave);
   if (q >= nnodes) return;
   const int32_t m = uniform(owner[q]);
   const int32_t i = uniform(rows[m]);
@@ -1360,10 +1362,10 @@ __global__ void __launch_bounds__(BLOCK)
 template <int K>
 __global__ void __launch_bounds__(TREE_BLOCK)
     k_wave_tree(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart, int level,
-                Pair *node, uint32_t *nflag) {
+                int64_t block0, Pair *node, uint32_t *nflag) {
   if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ uint32_t smap[TREE_BLOCK / WAVE][WaveMap<K>::WORDS];
-  const int64_t m = blockIdx.x;
+  const int64_t m = block0 + blockIdx.x;
   if (frozen(a, rows[m])) return;
   const int64_t q0 = cstart[m], n = cstart[m + 1] - q0;
   const int wave = uniform((int32_t)(threadIdx.x / WAVE));
@@ -1397,7 +1399,7 @@ __device__ inline void wave_root(const Pair *node, const int64_t *cstart, int32_
 template <int K, int ALGO>
 __global__ void __launch_bounds__(wave_group_block(K))
     k_wave_count(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
-                 const int32_t *__restrict__ owner, int64_t nnodes, int64_t L,
+                 const int32_t *__restrict__ owner, int64_t nnodes, int64_t L, int64_t block0,
                  const uint32_t *__restrict__ keybuf, const Pair *__restrict__ node,
                  const uint32_t *__restrict__ nflag, uint32_t *count) {
   if (level_over(a)) return;  // batched: every graph has stopped
@@ -1405,7 +1407,7 @@ __global__ void __launch_bounds__(wave_group_block(K))
   __shared__ uint32_t smap[G > 1 ? 1 : WAVES][WaveMap<K>::WORDS];
   __shared__ uint32_t skd;
   const int lane = lane_id(), wave = uniform((int32_t)(threadIdx.x / WAVE));
-  const int64_t q = G > 1 ? (int64_t)blockIdx.x : uniform((int64_t)blockIdx.x * WAVES + wave);
+  const int64_t q = G > 1 ? block0 + blockIdx.x : uniform((block0 + blockIdx.x) * WAVES + wave);
   if (q >= nnodes) return;
   const int32_t m = uniform(owner[q]);
   const int32_t i = uniform(rows[m]);
@@ -2582,22 +2584,28 @@ static void launch_rows(const SweepArgs &a, const Schedule &s, int64_t L, hipStr
     if (a.queue) {
       const int64_t grid = std::min<int64_t>(items, compute_units() * row_waves_per_simd<K>());
       k_move_rows<K, ALGO, MODE, true><<<(unsigned)grid, BLOCK, 0, st>>>(a, s.buckets, L, s.keybuf, items, nullptr, 0,
-                                                                        a.queue);
+                                                                        0, a.queue);
+      MGCD_LAUNCHED();
     } else {
-      k_move_rows<K, ALGO, MODE, false><<<(unsigned)(items + lblocks), BLOCK, 0, st>>>(
-          a, s.buckets, L, s.keybuf, items, s.light, s.nlight, nullptr);
+      launch_slices(items + lblocks, BLOCK, [&](int64_t first, unsigned blocks) {
+        k_move_rows<K, ALGO, MODE, false><<<blocks, BLOCK, 0, st>>>(a, s.buckets, L, s.keybuf, items, s.light,
+                                                                    s.nlight, first, nullptr);
+        MGCD_LAUNCHED();
+      });
     }
-    MGCD_LAUNCHED();
   }
   if (own && lblocks > 0) {
     if (a.queue) {
       const int64_t grid = std::min<int64_t>(lblocks, compute_units() * light_waves_per_simd<K>());
-      k_move_light<K, ALGO, MODE, true><<<(unsigned)grid, BLOCK, 0, st>>>(a, s.light, s.nlight,
+      k_move_light<K, ALGO, MODE, true><<<(unsigned)grid, BLOCK, 0, st>>>(a, s.light, s.nlight, 0,
                                                                          a.queue + QLANES * QSTRIDE);
+      MGCD_LAUNCHED();
     } else {
-      k_move_light<K, ALGO, MODE, false><<<(unsigned)lblocks, BLOCK, 0, st>>>(a, s.light, s.nlight, nullptr);
+      launch_slices(lblocks, BLOCK, [&](int64_t first, unsigned blocks) {
+        k_move_light<K, ALGO, MODE, false><<<blocks, BLOCK, 0, st>>>(a, s.light, s.nlight, first, nullptr);
+        MGCD_LAUNCHED();
+      });
     }
-    MGCD_LAUNCHED();
   }
 }
 
@@ -2692,10 +2700,12 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
   }
   mark(s, ev, 2, st);
   if (s.nmulti > 0) {  // split rows
-    const unsigned cgrid = wave_group_grid(K, s.nchunks);
-    k_wave_chunks<K, ALGO, MODE><<<cgrid, wave_group_block(K), 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L,
-                                                          s.keybuf, s.wnode, s.wflag, s.wcount);
-    MGCD_LAUNCHED();
+    const int64_t groups = wave_group_blocks(K, s.nchunks);
+    launch_slices(groups, wave_group_block(K), [&](int64_t first, unsigned blocks) {
+      k_wave_chunks<K, ALGO, MODE><<<blocks, wave_group_block(K), 0, st>>>(
+          a, s.multi, s.cstart, s.owner, s.nchunks, L, s.keybuf, first, s.wnode, s.wflag, s.wcount);
+      MGCD_LAUNCHED();
+    });
     const int64_t G = wave_group(K), maxch = (s.maxdeg + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
@@ -2704,13 +2714,17 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
       MGCD_LAUNCHED();
     }
     if (((int64_t)1 << l) < maxch) {
-      k_wave_tree<K><<<(unsigned)s.nmulti, TREE_BLOCK, 0, st>>>(a, s.multi, s.cstart, l, s.wnode, s.wflag);
-      MGCD_LAUNCHED();
+      launch_slices(s.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
+        k_wave_tree<K><<<blocks, TREE_BLOCK, 0, st>>>(a, s.multi, s.cstart, l, first, s.wnode, s.wflag);
+        MGCD_LAUNCHED();
+      });
     }
     if (second_pass(a, ALGO)) {
-      k_wave_count<K, ALGO><<<cgrid, wave_group_block(K), 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, L, s.keybuf,
-                                                     s.wnode, s.wflag, s.wcount);
-      MGCD_LAUNCHED();
+      launch_slices(groups, wave_group_block(K), [&](int64_t first, unsigned blocks) {
+        k_wave_count<K, ALGO><<<blocks, wave_group_block(K), 0, st>>>(
+            a, s.multi, s.cstart, s.owner, s.nchunks, L, first, s.keybuf, s.wnode, s.wflag, s.wcount);
+        MGCD_LAUNCHED();
+      });
     }
     k_wave_decide<K, ALGO><<<(unsigned)ceil_div(s.nmulti, BLOCK / WAVE), BLOCK, 0, st>>>(
         a, s.multi, s.cstart, s.nmulti, s.wnode, s.wflag, s.wcount);

@@ -466,8 +466,8 @@ struct WaveTree {
 constexpr int wave_group(int k) { return k <= WAVE ? 8 : 1; }
 constexpr int wave_group_waves(int k) { return k <= WAVE ? 8 : BLOCK / WAVE; }
 constexpr int wave_group_block(int k) { return wave_group_waves(k) * WAVE; }
-inline unsigned wave_group_grid(int k, int64_t nodes) {
-  return (unsigned)(wave_group(k) > 1 ? nodes : ceil_div(nodes, wave_group_waves(k)));
+inline int64_t wave_group_blocks(int k, int64_t nodes) {
+  return wave_group(k) > 1 ? nodes : ceil_div(nodes, wave_group_waves(k));
 }
 
 // The levels of the fixed merge tree within a workgroup's `n` chunk sketches (K <= 64, wave
