@@ -599,10 +599,16 @@ __global__ void k_comm_groups(const int64_t *cstart, int64_t nmulti, int64_t *ng
   if (x < nmulti) ng[x] = (cstart[x + 1] - cstart[x] + WAVE - 1) / WAVE;
 }
 
-__global__ void k_comm_owner(const int64_t *cstart, int64_t nmulti, int32_t *owner) {
-  int64_t x = blockIdx.x;
-  if (x >= nmulti) return;
+__global__ void k_comm_owner(const int64_t *cstart, int64_t block0, int32_t *owner) {
+  const int64_t x = block0 + blockIdx.x;
   for (int64_t q = cstart[x] + threadIdx.x; q < cstart[x + 1]; q += BLOCK) owner[q] = (int32_t)x;
+}
+
+static void comm_owners(const int64_t *cstart, int64_t nmulti, int32_t *owner, hipStream_t st) {
+  launch_slices(nmulti, BLOCK, [&](int64_t first, unsigned blocks) {
+    k_comm_owner<<<blocks, BLOCK, 0, st>>>(cstart, first, owner);
+    MGCD_LAUNCHED();
+  });
 }
 
 __global__ void k_u32_to_i32(const uint32_t *v, int32_t *out, int64_t n) {
@@ -905,9 +911,9 @@ __global__ void __launch_bounds__(BLOCK)
 
 template <int K>
 __global__ void __launch_bounds__(BLOCK) MGCD_SKETCH_OCCUPANCY(K)
-    k_agg_multi(AggLong lg, Pair *rows, uint32_t *rcount) {
+    k_agg_multi(AggLong lg, int64_t block0, Pair *rows, uint32_t *rcount) {
   __shared__ Pair lds[BLOCK * K];
-  const int32_t x = blockIdx.x;
+  const int32_t x = (int32_t)(block0 + blockIdx.x);
   const int32_t c = lg.multi[x];
   tree_reduce<K>(lg.skbuf, lg.gstart[x], lg.gstart[x + 1] - lg.gstart[x], lds);  // group roots
   if (threadIdx.x == 0) {
@@ -1156,11 +1162,11 @@ struct StreamLoad {
 template <int K, int MODE>
 __global__ void __launch_bounds__(BLOCK)
     k_agg_wave(AggStreams s, const int32_t *__restrict__ comms, int64_t ncomm, int64_t L, int depth,
-               Pair *rows, uint32_t *rcount) {
+               int64_t block0, Pair *rows, uint32_t *rcount) {
   static_assert(K <= WAVE, "one slot per lane; larger sketches split every stream");
   extern __shared__ uint32_t wave_lds[];
   const int lane = lane_id();
-  const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t r = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   if (r >= ncomm) return;
   const int32_t c = uniform(comms[r]);
   const int wave = uniform((int32_t)(threadIdx.x / WAVE));
@@ -1231,9 +1237,9 @@ __global__ void __launch_bounds__(wave_group_block(K))
 // multiple of 2^(level+1), takes in node x + 2^level if that exists; an odd last node
 // is carried).
 template <int K>
-__global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level) {
+__global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level, int64_t block0) {
   __shared__ uint32_t smap[BLOCK / WAVE][WaveMap<K>::WORDS];
-  const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t q = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   if (q >= sp.nchunks) return;
   const int32_t x = uniform(sp.owner[q]);
   const int64_t half = (int64_t)1 << level;
@@ -1259,9 +1265,9 @@ __global__ void __launch_bounds__(TREE_BLOCK) k_aggw_tree(AggSplit sp, int level
 
 // The row of every split stream: the root's positive slots sorted by key.
 template <int K>
-__global__ void __launch_bounds__(BLOCK) k_aggw_rows(AggSplit sp, Pair *rows, uint32_t *rcount) {
+__global__ void __launch_bounds__(BLOCK) k_aggw_rows(AggSplit sp, int64_t block0, Pair *rows, uint32_t *rcount) {
   const int lane = lane_id();
-  const int64_t x = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t x = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   if (x >= sp.nmulti) return;
   const int32_t c = uniform(sp.multi[x]);
   constexpr int S = WaveSlots<K>::S;
@@ -1309,8 +1315,10 @@ static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, c
     const int64_t G = wave_group(K), maxch = (max_len + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
-      k_aggw_level<K><<<(unsigned)ceil_div(sp.nchunks, BLOCK / WAVE), BLOCK, 0, st>>>(sp, l);
-      MGCD_LAUNCHED();
+      launch_slices(ceil_div(sp.nchunks, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_aggw_level<K><<<blocks, BLOCK, 0, st>>>(sp, l, first);
+        MGCD_LAUNCHED();
+      });
     }
     if (((int64_t)1 << l) < maxch) {
       launch_slices(sp.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
@@ -1318,19 +1326,23 @@ static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, c
         MGCD_LAUNCHED();
       });
     }
-    k_aggw_rows<K><<<(unsigned)ceil_div(sp.nmulti, BLOCK / WAVE), BLOCK, 0, st>>>(sp, rows, rcount);
-    MGCD_LAUNCHED();
+    launch_slices(ceil_div(sp.nmulti, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+      k_aggw_rows<K><<<blocks, BLOCK, 0, st>>>(sp, first, rows, rcount);
+      MGCD_LAUNCHED();
+    });
   }
   if (ncomm > 0) {
     if constexpr (K <= WAVE) {
-      const unsigned grid = (unsigned)ceil_div(ncomm, BLOCK / WAVE);
       const int depth = wave_tree_depth(WAVE_SPLIT, L);  // longer streams are one chunk or split
-      k_agg_wave<K, MODE><<<grid, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(s, comms, ncomm, L, depth,
-                                                                                    rows, rcount);
+      launch_slices(ceil_div(ncomm, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_agg_wave<K, MODE><<<blocks, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(s, comms, ncomm, L, depth,
+                                                                                         first, rows, rcount);
+        MGCD_LAUNCHED();
+      });
     } else {
       k_empty_rows<<<grid_for(ncomm), BLOCK, 0, st>>>(comms, ncomm, rcount);
+      MGCD_LAUNCHED();
     }
-    MGCD_LAUNCHED();
   }
 }
 
@@ -1342,10 +1354,10 @@ static void agg_mg(const AggStreams &s, const AggBuckets &bk, int64_t items, con
     k_agg_rows<K, MODE><<<blocks, BLOCK, 0, st>>>(s, bk, lg, L, first, rows, rcount);
     MGCD_LAUNCHED();
   });
-  if (lg.nmulti > 0) {
-    k_agg_multi<K><<<(unsigned)lg.nmulti, BLOCK, 0, st>>>(lg, rows, rcount);
+  launch_slices(lg.nmulti, BLOCK, [&](int64_t first, unsigned blocks) {
+    k_agg_multi<K><<<blocks, BLOCK, 0, st>>>(lg, first, rows, rcount);
     MGCD_LAUNCHED();
-  }
+  });
 }
 
 template <int MODE>
@@ -1501,8 +1513,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   if (wave && nmulti > 0) {  // chunks of the split streams
     const int64_t nchunks = read_i64(cstart + nmulti, st);
     int32_t *owner = a.take<int32_t>(nchunks);
-    k_comm_owner<<<(unsigned)nmulti, BLOCK, 0, st>>>(cstart, nmulti, owner);
-    MGCD_LAUNCHED();
+    comm_owners(cstart, nmulti, owner, st);
     sp = AggSplit{multi, nmulti, cstart, owner, nchunks, a.take<Pair>(nchunks * k)};
   } else if (nmulti > 0) {
     // groups of 64 chunks per long stream
@@ -1513,8 +1524,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     scan_i64(ng, gstart, nmulti, gstart + nmulti, a, st);
     const int64_t ngroups = read_i64(gstart + nmulti, st);
     int32_t *gowner = a.take<int32_t>(ngroups);
-    k_comm_owner<<<(unsigned)nmulti, BLOCK, 0, st>>>(gstart, nmulti, gowner);
-    MGCD_LAUNCHED();
+    comm_owners(gstart, nmulti, gowner, st);
     lg = AggLong{multi, nmulti, cstart, gstart, gowner, ngroups, a.take<Pair>(ngroups * k)};
   }
   Pair *rows = a.take<Pair>((int64_t)m * k);

@@ -346,12 +346,12 @@ __device__ inline void decide_long(const SweepArgs &a, int32_t i, int32_t d, con
 template <int K, int ALGO>
 __global__ void __launch_bounds__(BLOCK) MGCD_SKETCH_OCCUPANCY(K)
     k_long_merge(SweepArgs a, const int32_t *__restrict__ multi, const int64_t *__restrict__ gstart,
-                 Pair *sk, const uint32_t *__restrict__ skflag, Pair *cand, uint32_t *cflag) {
+                 int64_t block0, Pair *sk, const uint32_t *__restrict__ skflag, Pair *cand, uint32_t *cflag) {
   if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ Pair lds[BLOCK * K];
   __shared__ int flag_any;
   const int t = threadIdx.x;
-  const int32_t m = blockIdx.x;
+  const int32_t m = (int32_t)(block0 + blockIdx.x);
   const int32_t i = multi[m];
   const int64_t cb = gstart[m], nc = gstart[m + 1] - cb;  // group roots of the row
   if (frozen(a, i)) {  // block-uniform
@@ -395,11 +395,11 @@ __global__ void __launch_bounds__(BLOCK) MGCD_SKETCH_OCCUPANCY(K)
 template <int K, int ALGO>
 __global__ void __launch_bounds__(BLOCK)
     k_long_count(SweepArgs a, const int32_t *__restrict__ multi, const int32_t *__restrict__ owner,
-                 const int64_t *__restrict__ cstart, int64_t nchunks, int64_t L,
+                 const int64_t *__restrict__ cstart, int64_t nchunks, int64_t L, int64_t block0,
                  const Pair *__restrict__ cand, const uint32_t *__restrict__ cflag,
                  const uint32_t *__restrict__ keybuf, uint32_t *part) {
   if (level_over(a)) return;  // batched: every graph has stopped
-  const int64_t q = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
+  const int64_t q = ((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
   if (q >= nchunks) return;
   const int32_t m = owner[q];
   if (cflag[m] != 1) return;
@@ -445,11 +445,11 @@ __global__ void __launch_bounds__(BLOCK)
 template <int K, int ALGO>
 __global__ void __launch_bounds__(BLOCK)
     k_long_decide(SweepArgs a, const int32_t *__restrict__ multi, const int64_t *__restrict__ cstart,
-                  const Pair *__restrict__ cand, const uint32_t *__restrict__ cflag,
+                  int64_t block0, const Pair *__restrict__ cand, const uint32_t *__restrict__ cflag,
                   const uint32_t *__restrict__ part) {
   if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ uint32_t red[K + 1][BLOCK / WAVE];
-  const int32_t m = blockIdx.x;
+  const int32_t m = (int32_t)(block0 + blockIdx.x);
   if (cflag[m] != 1) return;  // block-uniform
   const int t = threadIdx.x;
   const int64_t cb = cstart[m], ce = cstart[m + 1];
@@ -1216,12 +1216,12 @@ __device__ inline uint32_t pass2_items(const SweepArgs &a, WaveMap<K> map, int64
 template <int K, int ALGO, int MODE>
 __global__ void __launch_bounds__(BLOCK)
     k_wave_rows(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t L, int depth,
-                uint32_t *keybuf) {
+                int64_t block0, uint32_t *keybuf) {
   static_assert(K <= WAVE, "one slot per lane; larger sketches take the split rows");
   if (level_over(a)) return;  // batched: every graph has stopped
   extern __shared__ uint32_t wave_lds[];
   const int lane = lane_id();
-  const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t r = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
   const bool listed = r < nrows;
   const int32_t i = listed ? uniform(rows[r]) : 0;
@@ -1342,11 +1342,11 @@ __global__ void __launch_bounds__(wave_group_block(K))
 template <int K>
 __global__ void __launch_bounds__(BLOCK)
     k_wave_level(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
-                 const int32_t *__restrict__ owner, int64_t nchunks, int level, Pair *node,
+                 const int32_t *__restrict__ owner, int64_t nchunks, int level, int64_t block0, Pair *node,
                  uint32_t *nflag) {
   if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ uint32_t smap[BLOCK / WAVE][WaveMap<K>::WORDS];
-  const int64_t q = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t q = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   if (q >= nchunks) return;
   const int32_t m = uniform(owner[q]);
   const int64_t x = q - cstart[m], half = (int64_t)1 << level;
@@ -1452,11 +1452,11 @@ __global__ void __launch_bounds__(wave_group_block(K))
 template <int K, int ALGO>
 __global__ void __launch_bounds__(BLOCK)
     k_wave_decide(SweepArgs a, const int32_t *__restrict__ rows, const int64_t *__restrict__ cstart,
-                  int64_t nrows, const Pair *__restrict__ node, const uint32_t *__restrict__ nflag,
-                  const uint32_t *__restrict__ count) {
+                  int64_t nrows, int64_t block0, const Pair *__restrict__ node,
+                  const uint32_t *__restrict__ nflag, const uint32_t *__restrict__ count) {
   if (level_over(a)) return;  // batched: every graph has stopped
   const int lane = lane_id();
-  const int64_t m = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t m = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
   if (m < nrows) {
     const int32_t i = uniform(rows[m]);
@@ -1769,14 +1769,14 @@ __device__ inline uint32_t table_sum(const Pair *tab, uint32_t mask, uint32_t c)
 // the others, with tier 2's, are below.
 template <int ALGO, bool SMALL = false>
 __global__ void __launch_bounds__(BLOCK)
-    k_exact_wave(SweepArgs a, const int32_t *__restrict__ list, int64_t count) {
+    k_exact_wave(SweepArgs a, const int32_t *__restrict__ list, int64_t count, int64_t block0) {
   if (level_over(a)) return;  // batched: every graph has stopped
   constexpr uint32_t CAPW = 2 * EXACT_WAVE_MAX;
   __shared__ __attribute__((aligned(16))) Pair wtab[BLOCK / WAVE][CAPW];
   __shared__ uint32_t wpos[BLOCK / WAVE][SMALL ? CAPW : 1];
   __shared__ uint16_t wcell[BLOCK / WAVE][EXACT_WAVE_MAX];
   const int lane = lane_id(), w = uniform((int32_t)(threadIdx.x / WAVE));
-  const int64_t r = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
+  const int64_t r = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
   if (r < count) {
     const int32_t i = uniform(list[r]);
@@ -1864,7 +1864,8 @@ __global__ void __launch_bounds__(BLOCK)
 // over R-MAT 2^19's rows of 513 to 4096 entries took 136 to 194 us; rows of 257 to 1023 now
 // take 52 to 73 us and those of 1024 to 4096 23 to 31.
 template <int ALGO, int THREADS, bool SMALL = false>
-__global__ void __launch_bounds__(THREADS) k_exact_table(SweepArgs a, const int32_t *__restrict__ list) {
+__global__ void __launch_bounds__(THREADS)
+    k_exact_table(SweepArgs a, const int32_t *__restrict__ list, int64_t block0) {
   if (level_over(a)) return;  // batched: every graph has stopped
   constexpr int U = 4;
   constexpr uint32_t CAP = 2 * U * THREADS;
@@ -1875,7 +1876,7 @@ __global__ void __launch_bounds__(THREADS) k_exact_table(SweepArgs a, const int3
   __shared__ int32_t bc[THREADS / WAVE];
   __shared__ int64_t bg[THREADS / WAVE];
   const int t = threadIdx.x;
-  const int32_t i = uniform(list[blockIdx.x]);
+  const int32_t i = uniform(list[block0 + blockIdx.x]);
   if (frozen(a, i)) {  // block-uniform
     if (t == 0) a.Cnew[i] = community_of_self<ALGO>(a, i);
     return;
@@ -1960,8 +1961,8 @@ __global__ void __launch_bounds__(THREADS) k_exact_table(SweepArgs a, const int3
 template <int ALGO, bool SMALL>
 __global__ void __launch_bounds__(BLOCK)
     k_gtab_insert(SweepArgs a, const int32_t *__restrict__ list, const int64_t *__restrict__ hbase,
-                  const int64_t *__restrict__ sstart, const int32_t *__restrict__ sowner, Pair *htab,
-                  uint32_t *hpos) {
+                  const int64_t *__restrict__ sstart, const int32_t *__restrict__ sowner, int64_t block0,
+                  Pair *htab, uint32_t *hpos) {
   if (level_over(a)) return;  // batched: every graph has stopped
   // Each round's U * BLOCK entries are first combined in an LDS table (at most U * BLOCK
   // keys in 2 * U * BLOCK slots), then every distinct key goes to the global table
@@ -1972,7 +1973,7 @@ __global__ void __launch_bounds__(BLOCK)
   __shared__ uint32_t lk[LCAP], lv[LCAP];
   __shared__ uint32_t lp[SMALL ? LCAP : 1];
   const int t = threadIdx.x;
-  const int64_t sg = blockIdx.x;
+  const int64_t sg = block0 + blockIdx.x;
   const int32_t r = sowner[sg];
   const int32_t i = list[r];
   if (frozen(a, i)) return;  // block-uniform
@@ -2084,13 +2085,13 @@ __global__ void __launch_bounds__(BLOCK)
 template <int ALGO, bool SMALL>
 __global__ void __launch_bounds__(BLOCK)
     k_gtab_scan(SweepArgs a, const int32_t *__restrict__ list, const int64_t *__restrict__ hbase,
-                const int64_t *__restrict__ tstart, const int32_t *__restrict__ towner, Pair *htab,
-                uint32_t *hpos, const uint32_t *__restrict__ kdin, int32_t *pbest, int64_t *pgain) {
+                const int64_t *__restrict__ tstart, const int32_t *__restrict__ towner, int64_t block0,
+                Pair *htab, uint32_t *hpos, const uint32_t *__restrict__ kdin, int32_t *pbest, int64_t *pgain) {
   if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ int32_t bc[BLOCK / WAVE];
   __shared__ int64_t bg[BLOCK / WAVE];
   const int t = threadIdx.x;
-  const int64_t sg = blockIdx.x;
+  const int64_t sg = block0 + blockIdx.x;
   const int32_t r = towner[sg];
   const int32_t i = list[r];
   if (frozen(a, i)) return;  // block-uniform; the table was not filled
@@ -2168,8 +2169,8 @@ __global__ void __launch_bounds__(BLOCK)
   flush_counters(a, ct);
 }
 
-__global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n) {
-  const int64_t x = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+__global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n, int64_t block0) {
+  const int64_t x = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
   if (x < n) {
     htab[x] = Pair{EMPTY, 0u};
     hpos[x] = 0xFFFFFFFFu;
@@ -2290,10 +2291,16 @@ __global__ void k_group_counts(const int64_t *cstart, int64_t nmulti, int64_t *n
   ng[m] = (cstart[m + 1] - cstart[m] + WAVE - 1) / WAVE;
 }
 
-__global__ void k_chunk_owner(const int64_t *cstart, int64_t nmulti, int32_t *owner) {
-  int64_t m = blockIdx.x;
-  if (m >= nmulti) return;
+__global__ void k_chunk_owner(const int64_t *cstart, int64_t block0, int32_t *owner) {
+  const int64_t m = block0 + blockIdx.x;
   for (int64_t q = cstart[m] + threadIdx.x; q < cstart[m + 1]; q += BLOCK) owner[q] = (int32_t)m;
+}
+
+static void chunk_owners(const int64_t *cstart, int64_t nmulti, int32_t *owner, hipStream_t st) {
+  launch_slices(nmulti, BLOCK, [&](int64_t first, unsigned blocks) {
+    k_chunk_owner<<<blocks, BLOCK, 0, st>>>(cstart, first, owner);
+    MGCD_LAUNCHED();
+  });
 }
 
 __global__ void k_table_segs(const int64_t *hbase, int64_t count, int64_t *nt) {
@@ -2405,8 +2412,7 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
       scan_i64(nch, s.cstart, s.nmulti, s.cstart + s.nmulti, a, st);
       read_back(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), st);
       s.owner = a.take<int32_t>(s.nchunks);
-      k_chunk_owner<<<(unsigned)s.nmulti, BLOCK, 0, st>>>(s.cstart, s.nmulti, s.owner);
-      MGCD_LAUNCHED();
+      chunk_owners(s.cstart, s.nmulti, s.owner, st);
       s.wnode = a.take<Pair>(s.nchunks * k);
       s.wflag = a.take<uint32_t>(s.nchunks);
       s.wcount = a.take<uint32_t>(s.nmulti * (k + 1));
@@ -2445,18 +2451,18 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
       rd.add(&s.ntseg, s.tstart + c3, sizeof(int64_t));
       rd.wait();
       s.sowner = a.take<int32_t>(s.nseg);
-      k_chunk_owner<<<(unsigned)c3, BLOCK, 0, st>>>(s.sstart, c3, s.sowner);
-      MGCD_LAUNCHED();
+      chunk_owners(s.sstart, c3, s.sowner, st);
       s.towner = a.take<int32_t>(s.ntseg);
-      k_chunk_owner<<<(unsigned)c3, BLOCK, 0, st>>>(s.tstart, c3, s.towner);
-      MGCD_LAUNCHED();
+      chunk_owners(s.tstart, c3, s.towner, st);
       s.gkd = a.take<uint32_t>(c3);
       s.pbest = a.take<int32_t>(s.ntseg);
       s.pgain = a.take<int64_t>(s.ntseg);
       s.htab = a.take<Pair>(tot);
       s.hpos = a.take<uint32_t>(tot);
-      k_gtab_clear<<<grid_for(tot), BLOCK, 0, st>>>(s.htab, s.hpos, tot);
-      MGCD_LAUNCHED();
+      launch_slices(ceil_div(tot, BLOCK), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_gtab_clear<<<blocks, BLOCK, 0, st>>>(s.htab, s.hpos, tot, first);
+        MGCD_LAUNCHED();
+      });
     }
     return;
   }
@@ -2494,11 +2500,9 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
     rd.add(&s.ngroups, s.gstart + s.nmulti, sizeof(int64_t));
     rd.wait();
     s.owner = a.take<int32_t>(s.nchunks);
-    k_chunk_owner<<<(unsigned)s.nmulti, BLOCK, 0, st>>>(s.cstart, s.nmulti, s.owner);
-    MGCD_LAUNCHED();
+    chunk_owners(s.cstart, s.nmulti, s.owner, st);
     s.gowner = a.take<int32_t>(s.ngroups);
-    k_chunk_owner<<<(unsigned)s.nmulti, BLOCK, 0, st>>>(s.gstart, s.nmulti, s.gowner);
-    MGCD_LAUNCHED();
+    chunk_owners(s.gstart, s.nmulti, s.gowner, st);
     s.sk = a.take<Pair>(s.ngroups * k);
     s.skflag = a.take<uint32_t>(s.ngroups);
     s.part = a.take<uint32_t>(s.nchunks * (k + 1));
@@ -2630,15 +2634,19 @@ static void sweep_mg(const SweepArgs &a, const Schedule &s, int64_t L, hipStream
   mark(s, ev, 1, st);
   // long rows: rest of the merge tree, pass 2, decision
   if (s.nmulti > 0) {
-    k_long_merge<K, ALGO><<<(unsigned)s.nmulti, BLOCK, 0, st>>>(a, s.multi, s.gstart, s.sk,
-                                                                s.skflag, s.cand, s.cflag);
-    MGCD_LAUNCHED();
-    k_long_count<K, ALGO><<<(unsigned)ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, 0, st>>>(
-        a, s.multi, s.owner, s.cstart, s.nchunks, L, s.cand, s.cflag, s.keybuf, s.part);
-    MGCD_LAUNCHED();
-    k_long_decide<K, ALGO><<<(unsigned)s.nmulti, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.cand,
-                                                                 s.cflag, s.part);
-    MGCD_LAUNCHED();
+    launch_slices(s.nmulti, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_long_merge<K, ALGO><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.gstart, first, s.sk, s.skflag, s.cand, s.cflag);
+      MGCD_LAUNCHED();
+    });
+    launch_slices(ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+      k_long_count<K, ALGO><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.owner, s.cstart, s.nchunks, L, first, s.cand,
+                                                      s.cflag, s.keybuf, s.part);
+      MGCD_LAUNCHED();
+    });
+    launch_slices(s.nmulti, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_long_decide<K, ALGO><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.cstart, first, s.cand, s.cflag, s.part);
+      MGCD_LAUNCHED();
+    });
   }
   mark(s, ev, 2, st);
   launch_short<ALGO>(a, s, st);  // rows whose sketch is their exact table
@@ -2651,32 +2659,37 @@ static void sweep_exact(const SweepArgs &a, const Schedule &s, hipStream_t st, h
   launch_short<ALGO, SMALL>(a, s, st);
   mark(s, ev, 1, st);
   if (s.ntier[1] > 0) {
-    k_exact_wave<ALGO, SMALL><<<(unsigned)ceil_div(s.ntier[1], BLOCK / WAVE), BLOCK, 0, st>>>(
-        a, s.tier[1], s.ntier[1]);
-    MGCD_LAUNCHED();
+    launch_slices(ceil_div(s.ntier[1], BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+      k_exact_wave<ALGO, SMALL><<<blocks, BLOCK, 0, st>>>(a, s.tier[1], s.ntier[1], first);
+      MGCD_LAUNCHED();
+    });
   }
   if (s.ntier[2] > 0) {
     const int64_t big = s.ntier[2] - s.nblock;
-    if (big > 0) {
-      k_exact_table<ALGO, EXACT_T2_MAX / 4, SMALL><<<(unsigned)big, EXACT_T2_MAX / 4, 0, st>>>(a, s.tier[2]);
+    launch_slices(big, EXACT_T2_MAX / 4, [&](int64_t first, unsigned blocks) {
+      k_exact_table<ALGO, EXACT_T2_MAX / 4, SMALL><<<blocks, EXACT_T2_MAX / 4, 0, st>>>(a, s.tier[2], first);
       MGCD_LAUNCHED();
-    }
-    if (s.nblock > 0) {
-      k_exact_table<ALGO, EXACT_BLOCK_MAX / 4, SMALL><<<(unsigned)s.nblock, EXACT_BLOCK_MAX / 4, 0, st>>>(
-          a, s.tier[2] + big);
+    });
+    launch_slices(s.nblock, EXACT_BLOCK_MAX / 4, [&](int64_t first, unsigned blocks) {
+      k_exact_table<ALGO, EXACT_BLOCK_MAX / 4, SMALL><<<blocks, EXACT_BLOCK_MAX / 4, 0, st>>>(a, s.tier[2] + big,
+                                                                                            first);
       MGCD_LAUNCHED();
-    }
+    });
   }
   mark(s, ev, 2, st);
   if (s.ntier[3] > 0) {
-    k_gtab_insert<ALGO, SMALL><<<(unsigned)s.nseg, BLOCK, 0, st>>>(a, s.tier[3], s.hbase, s.sstart, s.sowner,
-                                                                  s.htab, s.hpos);
-    MGCD_LAUNCHED();
+    launch_slices(s.nseg, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_gtab_insert<ALGO, SMALL><<<blocks, BLOCK, 0, st>>>(a, s.tier[3], s.hbase, s.sstart, s.sowner, first, s.htab,
+                                                           s.hpos);
+      MGCD_LAUNCHED();
+    });
     k_gtab_kd<ALGO><<<grid_for(s.ntier[3]), BLOCK, 0, st>>>(a, s.tier[3], s.ntier[3], s.hbase, s.htab, s.gkd);
     MGCD_LAUNCHED();
-    k_gtab_scan<ALGO, SMALL><<<(unsigned)s.ntseg, BLOCK, 0, st>>>(a, s.tier[3], s.hbase, s.tstart, s.towner,
-                                                                 s.htab, s.hpos, s.gkd, s.pbest, s.pgain);
-    MGCD_LAUNCHED();
+    launch_slices(s.ntseg, BLOCK, [&](int64_t first, unsigned blocks) {
+      k_gtab_scan<ALGO, SMALL><<<blocks, BLOCK, 0, st>>>(a, s.tier[3], s.hbase, s.tstart, s.towner, first, s.htab,
+                                                         s.hpos, s.gkd, s.pbest, s.pgain);
+      MGCD_LAUNCHED();
+    });
     k_gtab_finish<ALGO><<<grid_for(s.ntier[3]), BLOCK, 0, st>>>(a, s.tier[3], s.ntier[3], s.tstart, s.pbest,
                                                                 s.pgain);
     MGCD_LAUNCHED();
@@ -2691,11 +2704,12 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
   mark(s, ev, 1, st);
   if constexpr (K <= WAVE) {  // K = 128 / 256: every row the sketch takes is a split row
     if (s.ntier[1] > 0) {
-      const unsigned grid = (unsigned)ceil_div(s.ntier[1], BLOCK / WAVE);
       const int depth = wave_tree_depth(WAVE_SPLIT, L);  // longer rows are one chunk or split
-      k_wave_rows<K, ALGO, MODE><<<grid, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(
-          a, s.tier[1], s.ntier[1], L, depth, s.keybuf);
-      MGCD_LAUNCHED();
+      launch_slices(ceil_div(s.ntier[1], BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_wave_rows<K, ALGO, MODE><<<blocks, BLOCK, BLOCK / WAVE * wave_tree_lds<K>(depth), st>>>(
+            a, s.tier[1], s.ntier[1], L, depth, first, s.keybuf);
+        MGCD_LAUNCHED();
+      });
     }
   }
   mark(s, ev, 2, st);
@@ -2709,9 +2723,10 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
     const int64_t G = wave_group(K), maxch = (s.maxdeg + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
-      k_wave_level<K><<<(unsigned)ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, l, s.wnode,
-                                               s.wflag);
-      MGCD_LAUNCHED();
+      launch_slices(ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_wave_level<K><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, l, first, s.wnode, s.wflag);
+        MGCD_LAUNCHED();
+      });
     }
     if (((int64_t)1 << l) < maxch) {
       launch_slices(s.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
@@ -2726,9 +2741,11 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
         MGCD_LAUNCHED();
       });
     }
-    k_wave_decide<K, ALGO><<<(unsigned)ceil_div(s.nmulti, BLOCK / WAVE), BLOCK, 0, st>>>(
-        a, s.multi, s.cstart, s.nmulti, s.wnode, s.wflag, s.wcount);
-    MGCD_LAUNCHED();
+    launch_slices(ceil_div(s.nmulti, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+      k_wave_decide<K, ALGO><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.nmulti, first, s.wnode, s.wflag,
+                                                       s.wcount);
+      MGCD_LAUNCHED();
+    });
   }
   mark(s, ev, 3, st);
 }

@@ -83,3 +83,38 @@ def test_split_rows(mg):
         want, wgain, wctr = mg.move_sweep(g, algo, C, 0, mode=2, k=64, chunk_len=1)
         assert wctr[0] == n and ctr == wctr
         assert torch.equal(got, want) and torch.equal(gain, wgain)
+
+
+@pytest.mark.parametrize("n,k", [((1 << 26) + 1000, 64), ((1 << 24) + 1000, 128)])
+def test_wave_and_workgroup_per_stream(mg, n, k):
+    """A wave per stream at 64 slots; at 128 a workgroup per stream lists its chunks."""
+    import torch
+    g = ring(mg, n, 0)
+    D = torch.arange(n, dtype=torch.int32, device="cuda")
+    off, idx, w = mg.aggregate(g, D, n, mode=1, k=k)
+    assert (off == g.offsets.cpu().numpy()).all()
+    assert (idx == g.indices.cpu().numpy()).all()
+    assert (w == g.weights.cpu().numpy()).all()
+
+
+TABLES = {"mode": 0, "exact_small": 1, "exact_lds": 1}  # rows of two entries to the exact mode's tables
+
+
+@pytest.mark.parametrize("n,kw,other", [
+    ((1 << 26) + 1000, {"mode": 2, "k": 64}, {"mode": 2, "k": 16}),              # a wave per row
+    ((1 << 26) + 1000, {**TABLES, "exact_lds": 2}, {"mode": 0}),                 # a wave per row
+    ((1 << 24) + 1000, {**TABLES, "exact_lds_big": 2}, {"mode": 0}),             # a workgroup per row
+    ((1 << 24) + 1000, {**TABLES, "exact_lds_big": 1}, {"mode": 0}),             # global tables
+    ((1 << 24) + 1000, {"mode": 1, "k": 8, "chunk_len": 1, "row_lanes": 1}, {"mode": 0}),  # long rows
+])
+def test_wave_and_workgroup_per_row(mg, n, kw, other):
+    """Schedules that give each of these many rows a wave or a workgroup, against one that
+    does not; rows of two entries are exact in every mode."""
+    import torch
+    g = ring(mg, n, 0)
+    C = torch.arange(n, dtype=torch.int32, device="cuda")
+    for algo in (mg.ALGO_LPA, mg.ALGO_LOUVAIN):
+        got, gain, ctr = mg.move_sweep(g, algo, C, 0, **kw)
+        want, wgain, wctr = mg.move_sweep(g, algo, C, 0, **other)
+        assert wctr[0] == n and ctr == wctr
+        assert torch.equal(got, want) and torch.equal(gain, wgain)
