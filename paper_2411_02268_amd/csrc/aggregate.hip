@@ -962,10 +962,12 @@ __device__ inline uint32_t row_lower(const Pair *F, uint32_t n, uint32_t key) {
   return lo;
 }
 
-// Reverses of each community's row: all its pairs but the diagonal.
-__global__ void k_rev_counts(const Pair *rows, const uint32_t *rcount, int32_t m, int k, uint32_t *ec) {
+// Reverses of each community's row: all its pairs but the diagonal.  rend is cleared.
+__global__ void k_rev_counts(const Pair *rows, const uint32_t *rcount, int32_t m, int k, uint32_t *ec,
+                             int64_t *rend) {
   const int64_t c = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (c >= m) return;
+  rend[c] = 0;
   const Pair *F = rows + c * k;
   const uint32_t n = rcount[c], f = row_lower(F, n, (uint32_t)c);
   ec[c] = n - (f < n && F[f].key == (uint32_t)c);
@@ -984,56 +986,53 @@ __global__ void k_emit_reverse(const Pair *rows, const uint32_t *rcount, const u
   val[o] = p.val;
 }
 
-// rstart[t] = first sorted reverse of row t (t = 0 .. m).  One thread per reverse and
-// one past the end.
-__global__ void k_rev_starts(const uint64_t *ks, int64_t n, int32_t m, int b, int64_t *rstart) {
-  const int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (e > n) return;
-  const int64_t from = e == 0 ? 0 : (int64_t)(ks[e - 1] >> b) + 1;
-  const int64_t to = e == n ? m : (int64_t)(ks[e] >> b);
-  for (int64_t t = from; t <= to; ++t) rstart[t] = e;
-}
-
-// A reverse is kept unless its row has the pair itself.
+// A reverse is kept unless its row has the pair itself.  Row r's sorted reverses are
+// rbegin[r] .. rend[r], each bound written by the reverse there; a row without any keeps
+// rend 0 and has no rbegin, so that no thread walks over the rows between two reverses (one
+// thread for all of 2^24 rows without reverses took 424 ms of a 428 ms call, now 4.9).
 __global__ void k_rev_keep(const uint64_t *ks, int64_t n, int b, const Pair *rows, const uint32_t *rcount, int k,
-                           uint32_t *keep) {
+                           uint32_t *keep, int64_t *rbegin, int64_t *rend) {
   const int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (e >= n) return;
   const int64_t r = (int64_t)(ks[e] >> b);
+  if (e == 0 || (int64_t)(ks[e - 1] >> b) != r) rbegin[r] = e;
+  if (e == n - 1 || (int64_t)(ks[e + 1] >> b) != r) rend[r] = e + 1;
   const uint32_t s = (uint32_t)(ks[e] & ((1ull << b) - 1)), c = rcount[r];
   const Pair *F = rows + r * k;
   const uint32_t f = row_lower(F, c, s);
   keep[e] = f < c && F[f].key == s ? 0u : 1u;
 }
 
-__global__ void k_sym_counts(const uint32_t *rcount, const int64_t *rstart, const int64_t *kept, int32_t m,
-                             uint32_t *rowcnt) {
+__global__ void k_sym_counts(const uint32_t *rcount, const int64_t *rbegin, const int64_t *rend,
+                             const int64_t *kept, int32_t m, uint32_t *rowcnt) {
   const int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (r < m) rowcnt[r] = rcount[r] + (uint32_t)(kept[rstart[r + 1]] - kept[rstart[r]]);
+  if (r >= m) return;
+  const int64_t r1 = rend[r], r0 = r1 ? rbegin[r] : 0;
+  rowcnt[r] = rcount[r] + (uint32_t)(kept[r1] - kept[r0]);
 }
 
 __global__ void k_sym_reverse(const uint64_t *ks, const uint32_t *vs, int64_t n, int b, const Pair *rows,
-                              const uint32_t *rcount, int k, const int64_t *rstart, const int64_t *kept,
+                              const uint32_t *rcount, int k, const int64_t *rbegin, const int64_t *kept,
                               const int64_t *off, int32_t *idx, uint32_t *w) {
   const int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (e >= n || kept[e + 1] == kept[e]) return;
   const int64_t r = (int64_t)(ks[e] >> b);
   const uint32_t s = (uint32_t)(ks[e] & ((1ull << b) - 1));
-  const int64_t o = off[r] + row_lower(rows + r * k, rcount[r], s) + (kept[e] - kept[rstart[r]]);
+  const int64_t o = off[r] + row_lower(rows + r * k, rcount[r], s) + (kept[e] - kept[rbegin[r]]);
   idx[o] = (int32_t)s;
   w[o] = vs[e];
 }
 
 __global__ void k_sym_forward(const Pair *rows, const uint32_t *rcount, int32_t m, int k, int b, int64_t block0,
-                              const uint64_t *ks, const uint32_t *vs, const int64_t *rstart, const int64_t *kept,
-                              const int64_t *off, int32_t *idx, uint32_t *w) {
+                              const uint64_t *ks, const uint32_t *vs, const int64_t *rbegin, const int64_t *rend,
+                              const int64_t *kept, const int64_t *off, int32_t *idx, uint32_t *w) {
   const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
   const int64_t r = i / k;
   const uint32_t x = (uint32_t)(i - r * k);
   if (r >= m || x >= rcount[r]) return;
   const Pair p = rows[i];
   const uint64_t key = ((uint64_t)r << b) | p.key;
-  const int64_t r0 = rstart[r], r1 = rstart[r + 1];
+  const int64_t r1 = rend[r], r0 = r1 ? rbegin[r] : 0;
   int64_t lo = r0, hi = r1;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
@@ -1564,8 +1563,8 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     total = read_i64(out_off + m, st);
   } else {
     uint32_t *ec = a.take<uint32_t>(m);
-    int64_t *epos = a.take<int64_t>((int64_t)m + 1);
-    k_rev_counts<<<grid_for(m), BLOCK, 0, st>>>(rows, rcount, m, k, ec);
+    int64_t *epos = a.take<int64_t>((int64_t)m + 1), *rend = a.take<int64_t>(m);
+    k_rev_counts<<<grid_for(m), BLOCK, 0, st>>>(rows, rcount, m, k, ec, rend);
     MGCD_LAUNCHED();
     scan_u32_i64(ec, epos, m, epos + m, a, st);
     const int64_t E = read_i64(epos + m, st);
@@ -1579,27 +1578,25 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     const bool ef = radix_sort_pairs(e0, w0, e1, w1, E, 2 * b, a, st, b);  // by row; columns are in order
     const uint64_t *sk = ef ? e1 : e0;
     const uint32_t *sv = ef ? w1 : w0;
-    int64_t *rstart = a.take<int64_t>((int64_t)m + 1), *kept = a.take<int64_t>(E + 1);
+    int64_t *rbegin = epos, *kept = a.take<int64_t>(E + 1);  // epos has been read
     uint32_t *keep = a.take<uint32_t>(E), *rowcnt = a.take<uint32_t>(m);
-    k_rev_starts<<<grid_for(E + 1), BLOCK, 0, st>>>(sk, E, m, b, rstart);
-    MGCD_LAUNCHED();
     if (E > 0) {
-      k_rev_keep<<<grid_for(E), BLOCK, 0, st>>>(sk, E, b, rows, rcount, k, keep);
+      k_rev_keep<<<grid_for(E), BLOCK, 0, st>>>(sk, E, b, rows, rcount, k, keep, rbegin, rend);
       MGCD_LAUNCHED();
       scan_u32_i64(keep, kept, E, kept + E, a, st);
     } else {
       launch_fill_i64(kept, 0, 1, st);
     }
-    k_sym_counts<<<grid_for(m), BLOCK, 0, st>>>(rcount, rstart, kept, m, rowcnt);
+    k_sym_counts<<<grid_for(m), BLOCK, 0, st>>>(rcount, rbegin, rend, kept, m, rowcnt);
     MGCD_LAUNCHED();
     offsets_from_counts(rowcnt, m, out_off, a, st);
     launch_slices(slot_blocks, BLOCK, [&](int64_t first, unsigned blocks) {
-      k_sym_forward<<<blocks, BLOCK, 0, st>>>(rows, rcount, m, k, b, first, sk, sv, rstart, kept, out_off, out_idx,
-                                              out_w);
+      k_sym_forward<<<blocks, BLOCK, 0, st>>>(rows, rcount, m, k, b, first, sk, sv, rbegin, rend, kept, out_off,
+                                              out_idx, out_w);
       MGCD_LAUNCHED();
     });
     if (E > 0) {
-      k_sym_reverse<<<grid_for(E), BLOCK, 0, st>>>(sk, sv, E, b, rows, rcount, k, rstart, kept, out_off, out_idx, out_w);
+      k_sym_reverse<<<grid_for(E), BLOCK, 0, st>>>(sk, sv, E, b, rows, rcount, k, rbegin, kept, out_off, out_idx, out_w);
       MGCD_LAUNCHED();
     }
     total = read_i64(out_off + m, st);
@@ -1636,7 +1633,7 @@ size_t aggregate_ws_bytes(int32_t n, int64_t nnz, int mode, int k, int64_t L, bo
   b += tile_table_bytes(nnz);                                // tile first rows
   if (symmetric) {
     // reverses (rows hold at most their stream: at most min(k n, nnz) entries): sort
-    // buffers, kept flags and their scan; row starts and counts
+    // buffers, kept flags and their scan; row bounds and counts
     int64_t e1 = (int64_t)n * k < nnz ? (int64_t)n * k : nnz;
     b += (size_t)n * (4 + 8 + 8 + 4) + (size_t)e1 * (8 + 8 + 4 + 4 + 4 + 8) + 16384;
     b += radix_sort_ws_bytes(e1) + scan_ws_bytes(e1 > n ? e1 : n);
