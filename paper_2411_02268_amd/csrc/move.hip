@@ -226,30 +226,35 @@ __device__ inline void flush_wave_counters(const SweepArgs &a, Counters &ct) {
   if (l < 4 && x) atomicAdd(&sweep_counters(a)[l], x);
 }
 
+// Batched runs: the last graphs of a workgroup's waves, together.
+__device__ inline void flush_graph_counts(const SweepArgs &a, GraphCounts gc) {
+  __shared__ GraphCounts last[BLOCK / WAVE];
+  if (lane_id() == 0) last[threadIdx.x / WAVE] = gc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < BLOCK / WAVE; ++q) {
+      const GraphCounts x = last[q];
+      if (x.g < 0) continue;
+      if (x.g != gc.g) {
+        commit_graph_counts(a, gc);
+        gc = x;
+      } else {
+        gc.moved += x.moved;
+        gc.prop += x.prop;
+        gc.sumG += x.sumG;
+      }
+    }
+    commit_graph_counts(a, gc);
+  }
+}
+
 // A workgroup's counts of at most one row per lane.
 __device__ inline void flush_counters(const SweepArgs &a, Counters ct) {
   const int w = threadIdx.x / WAVE;
-  if (a.gctr) {  // batched (kernel-uniform): the waves' last graphs together
-    __shared__ GraphCounts last[BLOCK / WAVE];
+  if (a.gctr) {  // batched (kernel-uniform)
     GraphCounts gc{-1, 0, 0, 0};
     gather_graph_counts(a, ct, gc);
-    if (lane_id() == 0) last[w] = gc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int q = 1; q < BLOCK / WAVE; ++q) {
-        const GraphCounts x = last[q];
-        if (x.g < 0) continue;
-        if (x.g != gc.g) {
-          commit_graph_counts(a, gc);
-          gc = x;
-        } else {
-          gc.moved += x.moved;
-          gc.prop += x.prop;
-          gc.sumG += x.sumG;
-        }
-      }
-      commit_graph_counts(a, gc);
-    }
+    flush_graph_counts(a, gc);
     return;
   }
   __shared__ unsigned long long red[4][4];
@@ -530,6 +535,7 @@ struct RowShare {
   uint32_t own[WCH], ki[WCH], sd[WCH];       // its community, K_i, Sigma of its community,
   uint32_t need[WCH], lossy[WCH];            // needs pass 2, lost weight
   uint32_t any;                              // some row needs pass 2
+  uint32_t live;                             // some chunk has entries (of a row that may move)
   int64_t item;                              // persistent: next work item
 };
 
@@ -704,9 +710,14 @@ __device__ MGCD_INLINE void row_item(const SweepArgs &a, const Buckets &bk, int6
     S.own[t] = (uint32_t)d;
     S.need[t] = 0;
     S.lossy[t] = 0;
-    if (t == 0) S.any = 0;
+    const bool live = __ballot(hi > lo) != 0;
+    if (t == 0) {
+      S.any = 0;
+      S.live = live;
+    }
   }
   __syncthreads();
+  if (!S.live) return;  // rows that stay where they are: their labels are copied above
   const int64_t clo = S.lo[c], chi = S.hi[c], len = chi - clo;
   const int ch = S.chunk[c];
   const int64_t maxlen = wave_max_chunk(len);
@@ -986,16 +997,18 @@ __device__ MGCD_INLINE void light_item(const SweepArgs &a, const int32_t *rows, 
   const int64_t r = w * (WAVE / QUAD) + lane / QUAD;
   const bool listed = r < nrows;
   const int32_t i = listed ? rows[r] : 0;
-  // what the row needs is read before it is known whether its graph still moves
+  // the row's bounds are read before it is known whether its graph still moves, the rest
+  // after that: a wave of rows that stay where they are copies their labels and is done
   const int64_t rlo = a.g.off[i], rhi = a.g.off[i + 1];
   const int32_t d = community_of_self<ALGO>(a, i);
-  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
-  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
   const int32_t g = a.gid ? a.gid[i] : 0;
-  const uint32_t Sd = ALGO == ALGO_LPA ? 0u : a.Sig[d];
-  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[g] : (int64_t)a.W;
   const bool valid = listed && !(a.halt && *a.halt) && !(a.gid && !a.active[g]);
   if (listed && !valid && ql == 0) a.Cnew[i] = d;
+  if (!__ballot(valid)) return;
+  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
+  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+  const uint32_t Sd = ALGO == ALGO_LPA ? 0u : a.Sig[d];
+  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[g] : (int64_t)a.W;
   const int64_t lo = valid ? rlo : 0, hi = valid ? rhi : 0;
   // this lane's entries lo + 16 x + 4 ql + u
   uint32_t kk[R][4], ww[R][4];
@@ -1543,15 +1556,16 @@ __device__ MGCD_INLINE void short_item(const SweepArgs &a, const int32_t *list, 
   const int64_t r = w * (WAVE / G) + lane / G;
   const bool listed = r < count;
   const int32_t i = listed ? list[r] : 0;
-  // what the row needs is read before it is known whether its graph still moves
+  // as in light_item: a wave of rows that stay where they are ends here
   const int64_t rlo = a.g.off[i], rhi = a.g.off[i + 1];
   const int32_t d = community_of_self<ALGO>(a, i);
-  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
-  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
   const int32_t gi = a.gid ? a.gid[i] : 0;
-  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[gi] : (int64_t)a.W;
   const bool valid = listed && !(a.halt && *a.halt) && !(a.gid && !a.active[gi]);
   if (listed && !valid && q == 0) a.Cnew[i] = d;
+  if (!__ballot(valid)) return;
+  const uint32_t Ki = ALGO == ALGO_LPA ? 0u : a.K[i];
+  const int32_t b = ALGO == ALGO_REFINE ? a.bound[i] : 0;
+  const int64_t W = ALGO == ALGO_LPA ? 0 : a.gid ? (int64_t)a.Wg[gi] : (int64_t)a.W;
   const int left = valid ? (int)(rhi - rlo) - 4 * q : 0;
   const v4u j = load4(reinterpret_cast<const uint32_t *>(a.g.idx), rlo + 4 * q, a.g.nnz, left > 0);
   const v4u y = load4(a.g.w, rlo + 4 * q, a.g.nnz, left > 0);
@@ -1631,23 +1645,57 @@ __device__ MGCD_INLINE void short_item(const SweepArgs &a, const int32_t *list, 
   if (valid && q == 0) finish<ALGO>(a, i, d, best, bestG, ct);
 }
 
-// The short rows, classes of 17..32, 8..16, 4..7 and 1..3 entries one after another in
-// the list, each from a wave of its own on.
-template <int ALGO, bool SMALL>
+// Many graphs: rows s * 64 .. of list (count of them), one wave, as G items whose counts it
+// keeps together; an item whose rows all stay where they are costs no more than the look at
+// them, one per lane.
+template <int ALGO, bool SMALL, int G>
+__device__ MGCD_INLINE void short_rows64(const SweepArgs &a, const int32_t *list, int64_t count, int64_t s,
+                                         GraphCounts &gc) {
+  const int64_t r = s * WAVE + lane_id();
+  const int32_t i = r < count ? list[r] : 0;
+  const bool moving = r < count && !frozen(a, i);
+  if (r < count && !moving) a.Cnew[i] = community_of_self<ALGO>(a, i);
+  const uint64_t todo = __ballot(moving);
+#pragma unroll 1
+  for (int t = 0; t < G; ++t) {
+    if ((todo >> (t * (WAVE / G)) & (~0ull >> (WAVE - WAVE / G))) == 0) continue;
+    Counters ct;
+    short_item<ALGO, SMALL, G>(a, list, count, s * G + t, ct);
+    gather_graph_counts(a, ct, gc);
+  }
+}
+
+// The short rows, classes of 16..32, 8..15, 4..7 and 1..3 entries one after another in
+// the list, each from a wave of its own on (sr.wave).  WIDE (many graphs): the first two
+// classes go 64 rows to a wave.
+template <int ALGO, bool SMALL, bool WIDE>
 __global__ void __launch_bounds__(BLOCK) k_exact_short(SweepArgs a, const int32_t *__restrict__ list, ShortRows sr) {
   if (level_over(a)) return;  // batched: every graph has stopped
   Counters ct;
+  GraphCounts gc{-1, 0, 0, 0};
   stamp_start(a);
   const int64_t w = uniform(((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE);
-  if (w < sr.wave[1])
-    short_item<ALGO, SMALL, 8>(a, list, sr.row[1], w, ct);
-  else if (w < sr.wave[2])
-    short_item<ALGO, SMALL, 4>(a, list + sr.row[1], sr.row[2] - sr.row[1], w - sr.wave[1], ct);
-  else if (w < sr.wave[3])
+  if (w < sr.wave[1]) {
+    if constexpr (WIDE)
+      short_rows64<ALGO, SMALL, 8>(a, list, sr.row[1], w, gc);
+    else
+      short_item<ALGO, SMALL, 8>(a, list, sr.row[1], w, ct);
+  } else if (w < sr.wave[2]) {
+    if constexpr (WIDE)
+      short_rows64<ALGO, SMALL, 4>(a, list + sr.row[1], sr.row[2] - sr.row[1], w - sr.wave[1], gc);
+    else
+      short_item<ALGO, SMALL, 4>(a, list + sr.row[1], sr.row[2] - sr.row[1], w - sr.wave[1], ct);
+  } else if (w < sr.wave[3]) {
     short_item<ALGO, SMALL, 2>(a, list + sr.row[2], sr.row[3] - sr.row[2], w - sr.wave[2], ct);
-  else if (w < sr.wave[4])
+  } else if (w < sr.wave[4]) {
     short_item<ALGO, SMALL, 1>(a, list + sr.row[3], sr.row[4] - sr.row[3], w - sr.wave[3], ct);
-  flush_counters(a, ct);
+  }
+  if constexpr (WIDE) {
+    gather_graph_counts(a, ct, gc);
+    flush_graph_counts(a, gc);
+  } else {
+    flush_counters(a, ct);
+  }
 }
 
 // Tier-0 rows of more than 32 entries (a raised exact_small): one lane per row, which
@@ -2613,6 +2661,15 @@ static void launch_rows(const SweepArgs &a, const Schedule &s, int64_t L, hipStr
   }
 }
 
+// Many graphs: from so many waves on the short rows of 8 and more entries go 64 to a wave,
+// which then adds to a graph's counters once for 64 rows and passes over the rows of a graph
+// that has stopped at one look.  63 graphs of equal rows, the first sweep with its set-up and
+// a sweep in which all but one graph stand: 2.56 M rows of 23 entries 759 and 37 us, with 8
+// rows to a wave 1317 and 99; of 11 entries 550 and 37, with 16 rows to a wave 874 and 63.
+// At 160,000 rows (2500 waves) 194 us against 217, at 80,000 187 against 179, at 20,000 179
+// against 156: a wave's items then take their turns on an idle chip.
+constexpr int64_t SHORT_WIDE = 2048;
+
 // Tier 0: the list's longer rows (a raised exact_small), then the short rows.
 template <int ALGO, bool SMALL = false>
 static void launch_short(const SweepArgs &a, const Schedule &s, hipStream_t st) {
@@ -2620,11 +2677,18 @@ static void launch_short(const SweepArgs &a, const Schedule &s, hipStream_t st) 
     k_exact_small<ALGO><<<grid_for(s.ntail), BLOCK, 0, st>>>(a, s.tier[0], s.ntail);
     MGCD_LAUNCHED();
   }
-  if (s.shorts.wave[4] > 0) {
-    k_exact_short<ALGO, SMALL><<<(unsigned)ceil_div(s.shorts.wave[4], BLOCK / WAVE), BLOCK, 0, st>>>(
-        a, s.tier[0] + s.ntail, s.shorts);
+  const auto launch = [&](auto kernel, const ShortRows &sr) {
+    kernel<<<(unsigned)ceil_div(sr.wave[4], BLOCK / WAVE), BLOCK, 0, st>>>(a, s.tier[0] + s.ntail, sr);
     MGCD_LAUNCHED();
-  }
+  };
+  ShortRows wide = s.shorts;  // 64 rows per wave in the first two classes
+  for (int q = 0; q < 4; ++q)
+    wide.wave[q + 1] = wide.wave[q] + (q < 2 ? ceil_div(wide.row[q + 1] - wide.row[q], WAVE)
+                                             : s.shorts.wave[q + 1] - s.shorts.wave[q]);
+  if (a.gctr && wide.wave[2] >= SHORT_WIDE)
+    launch(k_exact_short<ALGO, SMALL, true>, wide);
+  else if (s.shorts.wave[4] > 0)
+    launch(k_exact_short<ALGO, SMALL, false>, s.shorts);
 }
 
 template <int K, int ALGO, int MODE>
