@@ -1100,6 +1100,7 @@ template <int K, int ALGO, int MODE, bool PERSIST>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_waves_per_simd<K>())))
     k_move_rows(SweepArgs a, const Buckets bk, int64_t L, uint32_t *keybuf, int64_t total, const int32_t *light,
                 int64_t nlight, int64_t first, unsigned long long *queue) {
+  if (level_over(a)) return;  // batched: every graph has stopped
   __shared__ RowShare<K> S;
   Counters ct;
   stamp_start(a, first);
@@ -1114,7 +1115,6 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_
       flush_counters(a, ct);
     }
   } else {
-    if (level_over(a)) return;
     GraphCounts gc{-1, 0, 0, 0};
     const int64_t c = blockIdx.x % QLANES;
     unsigned long long *qc = queue + c * QSTRIDE;
@@ -1143,6 +1143,7 @@ template <int K, int ALGO, int MODE, bool PERSIST>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(light_waves_per_simd<K>())))
     k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t first,
                  unsigned long long *queue) {
+  if (level_over(a)) return;  // batched: every graph has stopped
   const int64_t wave = uniform(((first + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
   Counters ct;
   stamp_start(a, first);
@@ -1150,7 +1151,6 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ligh
     light_item<K, ALGO, MODE>(a, rows, nrows, wave, ct);
     flush_counters(a, ct);
   } else {
-    if (level_over(a)) return;
     GraphCounts gc{-1, 0, 0, 0};
     const int64_t total = (nrows + WAVE / QUAD - 1) / (WAVE / QUAD);
     const int64_t c = wave % QLANES;
