@@ -572,7 +572,11 @@ static void *scratch_of_stream(hipStream_t st) {
 
 // MGCD_MODE_BM is Algorithm 1 with one slot for local moving and refinement and four
 // for aggregation (the weighted Boyer-Moore variant of Section 4.1); every entry
-// point works on the resolved copy.
+// point works on the resolved copy.  A chunk_len beyond any stream means one chunk; it is
+// cut to CHUNK_LEN_MAX, so that position + chunk_len and eight times it stay in 64 bits
+// (near 2^63 every row of more than 32 entries came out empty, and a stream of one entry
+// as endless).
+constexpr int64_t CHUNK_LEN_MAX = (int64_t)1 << 40;
 static mgcd_params resolved(const mgcd_params *p) {
   mgcd_params q{};
   if (!p) return q;
@@ -582,6 +586,7 @@ static mgcd_params resolved(const mgcd_params *p) {
     q.k = 1;
     q.k_aggregate = 4;
   }
+  if (q.chunk_len > CHUNK_LEN_MAX) q.chunk_len = CHUNK_LEN_MAX;
   return q;
 }
 mgcd_params mgcd::checked_params(const mgcd_params *p) {
