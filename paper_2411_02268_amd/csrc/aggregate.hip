@@ -166,13 +166,25 @@ constexpr int SF_ITEMS = 8, SF_TILE = BLOCK * SF_ITEMS;
 // entry are recognised by their offsets).  One thread per row marks the tile starts
 // inside its row; each entry lies in exactly one row, so each slot has one writer.
 // This replaces two binary searches over the offsets per workgroup, whose chains of
-// dependent loads set the time of the tiled kernels.
+// dependent loads set the time of the tiled kernels.  A row of more than LONG tiles is
+// marked by its whole wave: one thread writes a tile in 26 ns, longer than the tile's own
+// work takes.
 __global__ void k_tile_first_rows(const int64_t *off, int32_t n, int64_t ntiles, int32_t *first) {
+  constexpr int64_t LONG = 8;
   const int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (r == 0) first[ntiles] = n - 1;
-  if (r >= n) return;
-  const int64_t lo = off[r], hi = off[r + 1];
-  for (int64_t b = (lo + SF_TILE - 1) / SF_TILE; b * SF_TILE < hi; ++b) first[b] = (int32_t)r;
+  int64_t lo = 0, hi = 0;  // the tiles that start inside the row
+  if (r < n) {
+    lo = (off[r] + SF_TILE - 1) / SF_TILE;
+    hi = (off[r + 1] + SF_TILE - 1) / SF_TILE;
+  }
+  const bool wide = hi - lo > LONG;
+  for (int64_t b = lo; b < hi && !wide; ++b) first[b] = (int32_t)r;
+  for (uint64_t rows = __ballot(wide); rows; rows &= rows - 1) {
+    const int src = __builtin_ctzll(rows);
+    const int64_t b0 = __shfl(lo, src), b1 = __shfl(hi, src);
+    for (int64_t b = b0 + lane_id(); b < b1; b += WAVE) first[b] = (int32_t)(r - lane_id() + src);
+  }
 }
 
 size_t tile_table_bytes(int64_t nnz) { return (size_t)(ceil_div(nnz > 0 ? nnz : 0, SF_TILE) + 1) * 4 + 256; }
