@@ -37,16 +37,13 @@ constexpr int SEG = 4;
 // ---- pinned blocks of HostRead --------------------------------------------------------
 constexpr size_t POOL_BLOCKS = 32;
 static std::mutex g_pinned_mu;
-static std::vector<void *> g_pinned;  // free blocks
+static void *g_pinned[POOL_BLOCKS];  // the free ones; plain storage: returning a block cannot
+static size_t g_pinned_free = 0;     // fail, also from a thread that outlives static objects
 
 void *pinned_lease() {
   {
     std::lock_guard<std::mutex> lock(g_pinned_mu);
-    if (!g_pinned.empty()) {
-      void *p = g_pinned.back();
-      g_pinned.pop_back();
-      return p;
-    }
+    if (g_pinned_free > 0) return g_pinned[--g_pinned_free];
   }
   void *p = nullptr;
   if (hipHostMalloc(&p, PINNED_BYTES, hipHostMallocPortable) != hipSuccess) {
@@ -59,8 +56,8 @@ void *pinned_lease() {
 void pinned_return(void *block) {
   {
     std::lock_guard<std::mutex> lock(g_pinned_mu);
-    if (g_pinned.size() < POOL_BLOCKS) {
-      g_pinned.push_back(block);
+    if (g_pinned_free < POOL_BLOCKS) {
+      g_pinned[g_pinned_free++] = block;
       return;
     }
   }
