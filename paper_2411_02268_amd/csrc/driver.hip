@@ -65,11 +65,17 @@ void pinned_return(void *block) {
 }
 
 // Device time of the level-0 sweeps by kernel class: by the device clock where a sweep is
-// one class (LevelState::ticks), else by events around the classes that have kernels.
+// one class (LevelState::ticks), else by events around the classes that have kernels: those
+// of the schedule that it was made with (Leiden rebuilds its schedule before the refinement).
 struct ClassTimer {
   hipEvent_t ev[SEG][4] = {};
-  const Schedule *sch = nullptr;
-  explicit ClassTimer(const Schedule *s) : sch(s) {
+  unsigned classes = 0;
+  bool clock = false;
+  explicit ClassTimer(const Schedule *s) {  // null: nothing is timed
+    if (s) {
+      classes = s->classes;
+      clock = s->clock;
+    }
     if (!timed()) return;
     for (auto &row : ev)
       for (auto &e : row) MGCD_HIP(hipEventCreate(&e));
@@ -79,11 +85,11 @@ struct ClassTimer {
       for (auto &e : row)
         if (e) (void)hipEventDestroy(e);
   }
-  bool timed() const { return sch && !sch->clock; }
+  bool timed() const { return classes != 0 && !clock; }
   hipEvent_t *events(int j) { return timed() ? ev[j] : nullptr; }
   void add(mgcd_stats &s, int j) {  // after sweep j of the segment has completed
     for (int q = 0; q < 3 && timed(); ++q) {
-      if (!(sch->classes >> q & 1u)) continue;
+      if (!(classes >> q & 1u)) continue;
       float ms = 0;
       MGCD_HIP(hipEventElapsedTime(&ms, ev[j][q], ev[j][q + 1]));
       s.ms_l0_kernel[q] += ms;
@@ -91,11 +97,11 @@ struct ClassTimer {
     s.l0_sweeps += 1;
   }
   void finish(mgcd_stats &s, const LevelState &h) {  // the level's ticks, to its only class
-    if (!sch || !sch->clock) return;
+    if (!clock) return;
     int dev = 0, khz = 0;
     MGCD_HIP(hipGetDevice(&dev));
     MGCD_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
-    const int q = sch->classes == 4u ? 2 : 0;
+    const int q = classes == 4u ? 2 : 0;
     if (khz > 0) s.ms_l0_kernel[q] += (float)((double)h.ticks / khz);
   }
 };
