@@ -629,12 +629,9 @@ __global__ void k_u32_to_i32(const uint32_t *v, int32_t *out, int64_t n) {
 }
 
 struct AggStreams {
-  Graph g;
-  const int32_t *D;
-  const uint32_t *mem;    // members sorted by community, ascending id within one
-  const int32_t *mstart;  // [m+1]
+  int64_t size;           // entries that skey and sw have room for
+  const int32_t *mstart;  // [m+1] first member of each community in the order of communities
   const int64_t *P;       // [n+1] stream position of each member's row
-  const int64_t *rs;      // [n] CSR offset of each member's row (off[mem[t]])
   const uint32_t *skey;   // [positions] the streams laid out contiguously: key D[j]
   const uint32_t *sw;     //             and weight of every position
 };
@@ -757,11 +754,6 @@ StorageCopy storage_copy(const Graph &g, const uint32_t *K, Arena &a, hipStream_
   return s;
 }
 
-__global__ void k_row_starts(const int64_t *off, const uint32_t *mem, int32_t n, int64_t *rs) {
-  int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (t < n) rs[t] = off[mem[t]];
-}
-
 // Communities whose stream has at most 64 chunks, by the power of two P = 2^b that holds
 // their chunks: 64 / P of them per workgroup.
 struct AggBuckets {
@@ -847,8 +839,8 @@ __global__ void __launch_bounds__(BLOCK)
   const auto load = [&](int64_t e, v4u &k, v4u &x) {  // nothing past the chunk's end
     const int64_t f = e + QUAD * ql;
     const bool on = f < len;
-    k = load4(s.skey, p0 + f, s.g.nnz, on);
-    x = load4(s.sw, p0 + f, s.g.nnz, on);
+    k = load4(s.skey, p0 + f, s.size, on);
+    x = load4(s.sw, p0 + f, s.size, on);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       k[u] = f + u < len ? k[u] : EMPTY;
@@ -1494,7 +1486,6 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   MGCD_LAUNCHED();
   unsigned long long hc[9];
   read_spread(cnt, 8, hc, st);
-  MGCD_HIP(hipStreamSynchronize(st));
   AggBuckets bk{};
   int64_t pos = 0, items = 0;
   const int32_t *bucket_rows[7];
@@ -1540,9 +1531,6 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   }
   Pair *rows = a.take<Pair>((int64_t)m * k);
   uint32_t *rcount = a.take<uint32_t>(m);
-  int64_t *rs = a.take<int64_t>(n);
-  k_row_starts<<<grid_for(n), BLOCK, 0, st>>>(g.off, mem, n, rs);
-  MGCD_LAUNCHED();
   int64_t *rowpos = a.take<int64_t>(n);
   launch_fill_i64(rowpos, -1, n, st);
   if (n > 0) {
@@ -1557,7 +1545,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     k_agg_streamify<<<(unsigned)ceil_div(g.nnz, SF_TILE), BLOCK, 0, st>>>(g, first, D, rowpos, skey, sw);
     MGCD_LAUNCHED();
   }
-  AggStreams s{g, D, mem, mstart, P, rs, skey, sw};
+  AggStreams s{g.nnz, mstart, P, skey, sw};
   switch (mode) {
     case MODE_ALG1: agg_mg_k<MODE_ALG1>(k, s, bk, items, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
     case MODE_UNCOND: agg_mg_k<MODE_UNCOND>(k, s, bk, items, lg, sp, L, rows, rcount, corder, (int64_t)hc[0], (int64_t)hc[8], st); break;
@@ -1628,7 +1616,7 @@ size_t aggregate_ws_bytes(int32_t n, int64_t nnz, int mode, int k, int64_t L, bo
   b += radix_sort_ws_bytes(n) + 4096;
   b += (size_t)(n + 1) * (4 + 4 + 8) + 4096;        // mstart, mdeg, P
   b += scan_ws_bytes(n + 1) + 4096;
-  b += (size_t)n * (8 + 8 + 4 + 4 + 4 + 8) + 4096;  // community sort, order, row starts
+  b += (size_t)n * (8 + 8 + 4 + 4 + 4) + 4096;      // community sort, order
   // streams of more than 64 chunks: at most nnz / (64 L) of them, at most
   // nnz / L + that many chunks
   const int64_t Lc = L > 0 ? L : 1;

@@ -140,12 +140,6 @@ struct Batch {
   uint8_t *sel_d;
 };
 
-static unsigned long long read_u64(const unsigned long long *p, hipStream_t st) {
-  unsigned long long h = 0;
-  read_back(&h, p, sizeof(h), st);
-  return h;
-}
-
 static void copy_h2d(void *dst, const void *src, size_t bytes, hipStream_t st) {
   MGCD_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
   MGCD_HIP(hipStreamSynchronize(st));  // the host buffer may go away
