@@ -161,22 +161,23 @@ __device__ inline int32_t row_of_entry(const int64_t *off, int32_t lo, int32_t h
 constexpr int SF_ITEMS = 8, SF_TILE = BLOCK * SF_ITEMS;
 
 // The first row of every tile of SF_TILE consecutive CSR entries: first[t] = the row
-// holding entry t * SF_TILE (t < ntiles) and first[ntiles] = n - 1, so that a tile's
-// rows lie in first[t] .. first[t + 1] (an upper bound: rows after the tile's last
-// entry are recognised by their offsets).  One thread per row marks the tile starts
+// holding entry t * SF_TILE (t < ntiles) and first[ntiles] = the row holding the last entry,
+// so that a tile's rows lie in first[t] .. first[t + 1] (an upper bound: rows after the
+// tile's last entry are recognised by their offsets; empty rows at the end are in no tile).  One thread per row marks the tile starts
 // inside its row; each entry lies in exactly one row, so each slot has one writer.
 // This replaces two binary searches over the offsets per workgroup, whose chains of
 // dependent loads set the time of the tiled kernels.  A row of more than LONG tiles is
 // marked by its whole wave: one thread writes a tile in 26 ns, longer than the tile's own
 // work takes.
-__global__ void k_tile_first_rows(const int64_t *off, int32_t n, int64_t ntiles, int32_t *first) {
+__global__ void k_tile_first_rows(const int64_t *off, int32_t n, int64_t nnz, int64_t ntiles, int32_t *first) {
   constexpr int64_t LONG = 8;
   const int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (r == 0) first[ntiles] = n - 1;
   int64_t lo = 0, hi = 0;  // the tiles that start inside the row
   if (r < n) {
-    lo = (off[r] + SF_TILE - 1) / SF_TILE;
-    hi = (off[r + 1] + SF_TILE - 1) / SF_TILE;
+    const int64_t a = off[r], b = off[r + 1];
+    if (a < nnz && (b >= nnz || r == n - 1)) first[ntiles] = (int32_t)r;
+    lo = (a + SF_TILE - 1) / SF_TILE;
+    hi = (b + SF_TILE - 1) / SF_TILE;
   }
   const bool wide = hi - lo > LONG;
   for (int64_t b = lo; b < hi && !wide; ++b) first[b] = (int32_t)r;
@@ -193,7 +194,7 @@ size_t tile_table_bytes(int64_t nnz) { return (size_t)(ceil_div(nnz > 0 ? nnz : 
 static int32_t *tile_first_rows(const Graph &g, Arena &a, hipStream_t st) {
   const int64_t nt = ceil_div(g.nnz, SF_TILE);
   int32_t *first = a.take<int32_t>(nt + 1);
-  k_tile_first_rows<<<(unsigned)ceil_div(g.n > 0 ? g.n : 1, BLOCK), BLOCK, 0, st>>>(g.off, g.n, nt, first);
+  k_tile_first_rows<<<(unsigned)ceil_div(g.n > 0 ? g.n : 1, BLOCK), BLOCK, 0, st>>>(g.off, g.n, g.nnz, nt, first);
   MGCD_LAUNCHED();
   return first;
 }
