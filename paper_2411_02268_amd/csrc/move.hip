@@ -1600,15 +1600,20 @@ __device__ MGCD_INLINE void short_item(const SweepArgs &a, const int32_t *list, 
   for (int u = 0; u < 4; ++u) stands[u] = key[u] != EMPTY;
 #pragma unroll
   for (int v = 0; v < G; ++v) {
-    const uint32_t qo = group_perm<G>((uint32_t)q, v);
+    bool same[4] = {};  // SMALL: the other lane has the slot (this lane, v = 0: at an earlier place)
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const uint32_t so = group_perm<G>(sl[x], v), wo = group_perm<G>(wt[x], v);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         kc[u] += so == sl[u] ? wo : 0u;
-        if (SMALL) stands[u] &= !(so == sl[u] && (qo < (uint32_t)q || (qo == (uint32_t)q && x < u)));
+        if (SMALL && (v > 0 || x < u)) same[u] |= so == sl[u];
       }
+    }
+    if (SMALL) {
+      const bool earlier = v == 0 || group_perm<G>((uint32_t)q, v) < (uint32_t)q;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) stands[u] &= !(same[u] && earlier);
     }
   }
   int32_t best = -1;
