@@ -932,17 +932,33 @@ __global__ void __launch_bounds__(BLOCK) MGCD_SKETCH_OCCUPANCY(K)
   }
 }
 
-// rows (k slots per community, rcount used) -> CSR, a thread per slot
+// The threads that go over a row's used slots: one each up to 16 slots, 16 for more, whose
+// rows are mostly empty (2 M rows of one entry at k = 256: 780 us with a thread per slot,
+// now 90).
+struct RowSlots {
+  int64_t c;      // the row
+  uint32_t x, by;  // its first slot here, then every by-th
+  __device__ inline RowSlots(int64_t block0, int k) {
+    const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
+    by = k < 16 ? k : 16;
+    c = i / by;
+    x = (uint32_t)(i - c * by);
+  }
+};
+static int64_t row_slot_blocks(int32_t m, int k) { return ceil_div((int64_t)m * (k < 16 ? k : 16), BLOCK); }
+
+// rows (k slots per community, rcount used) -> CSR
 __global__ void k_compact_rows(const Pair *rows, const uint32_t *rcount, const int64_t *off, int32_t m,
                                int k, int64_t block0, int32_t *idx, uint32_t *w) {
-  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
-  const int64_t c = i / k;
-  const uint32_t x = (uint32_t)(i - c * k);
-  if (c >= m || x >= rcount[c]) return;
-  const Pair p = rows[i];
-  const int64_t o = off[c] + x;
-  idx[o] = (int32_t)p.key;
-  w[o] = p.val;
+  const RowSlots s(block0, k);
+  if (s.c >= m) return;
+  const uint32_t n = rcount[s.c];
+  for (uint32_t x = s.x; x < n; x += s.by) {
+    const Pair p = rows[s.c * k + x];
+    const int64_t o = off[s.c] + x;
+    idx[o] = (int32_t)p.key;
+    w[o] = p.val;
+  }
 }
 
 // ---- Leiden: the union of the kept pairs and their reverses, the larger value where both
@@ -980,15 +996,17 @@ __global__ void k_rev_counts(const Pair *rows, const uint32_t *rcount, int32_t m
 
 __global__ void k_emit_reverse(const Pair *rows, const uint32_t *rcount, const uint32_t *ec, const int64_t *epos,
                                int32_t m, int k, int b, int64_t block0, uint64_t *key, uint32_t *val) {
-  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
-  const int64_t c = i / k;
-  const uint32_t x = (uint32_t)(i - c * k);
-  if (c >= m || x >= rcount[c]) return;
-  const Pair p = rows[i];
-  if (p.key == (uint32_t)c) return;
-  const int64_t o = epos[c] + x - (ec[c] != rcount[c] && p.key > (uint32_t)c);  // past the diagonal
-  key[o] = ((uint64_t)p.key << b) | (uint64_t)c;
-  val[o] = p.val;
+  const RowSlots s(block0, k);
+  const int64_t c = s.c;
+  if (c >= m) return;
+  const uint32_t n = rcount[c];
+  for (uint32_t x = s.x; x < n; x += s.by) {
+    const Pair p = rows[c * k + x];
+    if (p.key == (uint32_t)c) continue;
+    const int64_t o = epos[c] + x - (ec[c] != n && p.key > (uint32_t)c);  // past the diagonal
+    key[o] = ((uint64_t)p.key << b) | (uint64_t)c;
+    val[o] = p.val;
+  }
 }
 
 // A reverse is kept unless its row has the pair itself.  Row r's sorted reverses are
@@ -1031,25 +1049,27 @@ __global__ void k_sym_reverse(const uint64_t *ks, const uint32_t *vs, int64_t n,
 __global__ void k_sym_forward(const Pair *rows, const uint32_t *rcount, int32_t m, int k, int b, int64_t block0,
                               const uint64_t *ks, const uint32_t *vs, const int64_t *rbegin, const int64_t *rend,
                               const int64_t *kept, const int64_t *off, int32_t *idx, uint32_t *w) {
-  const int64_t i = (block0 + blockIdx.x) * BLOCK + threadIdx.x;
-  const int64_t r = i / k;
-  const uint32_t x = (uint32_t)(i - r * k);
-  if (r >= m || x >= rcount[r]) return;
-  const Pair p = rows[i];
-  const uint64_t key = ((uint64_t)r << b) | p.key;
-  const int64_t r1 = rend[r], r0 = r1 ? rbegin[r] : 0;
-  int64_t lo = r0, hi = r1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (ks[mid] < key)
-      lo = mid + 1;
-    else
-      hi = mid;
+  const RowSlots s(block0, k);
+  const int64_t r = s.c;
+  if (r >= m) return;
+  const uint32_t n = rcount[r];
+  for (uint32_t x = s.x; x < n; x += s.by) {
+    const Pair p = rows[r * k + x];
+    const uint64_t key = ((uint64_t)r << b) | p.key;
+    const int64_t r1 = rend[r], r0 = r1 ? rbegin[r] : 0;
+    int64_t lo = r0, hi = r1;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (ks[mid] < key)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    const uint32_t v = lo < r1 && ks[lo] == key ? vs[lo] : 0u;
+    const int64_t o = off[r] + x + (kept[lo] - kept[r0]);
+    idx[o] = (int32_t)p.key;
+    w[o] = v > p.val ? v : p.val;
   }
-  const uint32_t v = lo < r1 && ks[lo] == key ? vs[lo] : 0u;
-  const int64_t o = off[r] + x + (kept[lo] - kept[r0]);
-  idx[o] = (int32_t)p.key;
-  w[o] = v > p.val ? v : p.val;
 }
 
 // Sorted (row, col) keys: run heads (first entry of each distinct key).
@@ -1554,7 +1574,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     default: throw Error(-6, "unknown sketch mode");
   }
   int64_t total = 0;
-  const int64_t slot_blocks = ceil_div((int64_t)m * k, BLOCK);
+  const int64_t slot_blocks = row_slot_blocks(m, k);
   if (!symmetric) {
     offsets_from_counts(rcount, m, out_off, a, st);
     launch_slices(slot_blocks, BLOCK, [&](int64_t first, unsigned blocks) {

@@ -10,7 +10,7 @@ constexpr int64_t GRID_THREADS = (int64_t)1 << 32;
 
 // Calls launch(first, count) for consecutive slices of `blocks` workgroups of `threads`
 // threads, each small enough for one launch.  Kernels with several threads per row, chunk
-// or slot go through it: there are up to 2^31 rows and entries, and m k slots.
+// or community go through it: there are up to 2^31 of each.
 template <typename F>
 inline void launch_slices(int64_t blocks, int threads, F &&launch, int64_t limit = GRID_THREADS) {
   const int64_t most = (limit - 1) / threads;

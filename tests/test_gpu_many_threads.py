@@ -33,11 +33,11 @@ def csr(mg, n, u, v):
 
 
 @pytest.mark.parametrize("symmetric", [False, True])
-def test_slots(mg, symmetric):
-    """2^24 communities of 256 slots: nearly all without entries, so that no other kernel
-    of the call has as many threads; the last rows are beyond the first launch."""
+@pytest.mark.parametrize("n,k", [(1 << 24, 256), ((1 << 28) + 1000, 16)])
+def test_slots(mg, symmetric, n, k):
+    """2^24 communities of 256 slots and 2^28 of 16: nearly all without entries, so that no
+    other kernel of the call has as many threads; the last rows are beyond the first launch."""
     import torch
-    n, k = 1 << 24, 256
     gen = torch.Generator(device="cuda")
     gen.manual_seed(3)
     u = torch.randint(0, n, (4000,), generator=gen, device="cuda")
