@@ -542,15 +542,17 @@ __global__ void k_member_deg(const int64_t *off, const uint32_t *mem, int32_t n,
 
 // Category of every community stream: b = log2 of the lanes it needs (0..6, at
 // most 64 chunks; sort key heavy first within b = 0) or 7 = longer.  With split > 0
-// (the 32/64-slot sketch): 0 = one wave, 7 = more than max(L, split) positions.
+// (the 32/64-slot sketch): 0 = one wave, 7 = more than max(L, split) positions, heavy
+// first; 1 counts those of the latter that may have more than one node of `node` positions.
 __global__ void __launch_bounds__(BLOCK)
-    k_comm_keys(const int32_t *mstart, const int64_t *P, int32_t m, int64_t L, int64_t split,
+    k_comm_keys(const int32_t *mstart, const int64_t *P, int32_t m, int64_t L, int64_t split, int64_t node,
                 uint64_t *key, uint32_t *val, unsigned long long *cnt) {
   __shared__ unsigned long long bc[8];
   if (threadIdx.x < 8) bc[threadIdx.x] = 0;
   __syncthreads();
   int64_t c = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   int cat = -1;
+  bool tree = false;
   int64_t lmax = 0;
   if (c < m) {
     int64_t len = P[mstart[c + 1]] - P[mstart[c]];
@@ -559,7 +561,8 @@ __global__ void __launch_bounds__(BLOCK)
       cat = (split < 0 ? len > 0 : (len > L && len > split)) ? 7 : 0;
       int b = 0;
       while (b < 63 && (len >> b) != 0) ++b;
-      key[c] = cat == 7 ? 207ull : (uint64_t)(64 - b);
+      key[c] = (uint64_t)((cat == 7 ? 128 : 0) + 64 - b);
+      tree = cat == 7 && ((node + 1) >> b) == 0;  // as many bits as node + 1, or more
     } else if (len <= L) {
       int b = 0;
       while (b < 63 && (len >> b) != 0) ++b;
@@ -575,7 +578,7 @@ __global__ void __launch_bounds__(BLOCK)
     val[c] = (uint32_t)c;
   }
   for (int q = 0; q < 8; ++q) {
-    uint64_t mk = __ballot(cat == q);
+    uint64_t mk = __ballot(cat == q || (q == 1 && tree));
     if (lane_id() == 0 && mk) atomicAdd(&bc[q], (unsigned long long)__popcll(mk));
   }
   __syncthreads();
@@ -1220,6 +1223,8 @@ __global__ void __launch_bounds__(BLOCK)
 struct AggSplit {
   const int32_t *multi;   // [nmulti] split communities
   int64_t nmulti;
+  int64_t ntree;          // of these, the first: those that may have more than one node,
+  int64_t tree_nodes;     // with the first nodes
   const int64_t *cstart;  // [nmulti+1] first node (wave_group(K) chunks) of each
   const int32_t *owner;   // [nchunks] index into multi of each node
   int64_t nchunks;        // nodes
@@ -1264,7 +1269,7 @@ template <int K>
 __global__ void __launch_bounds__(BLOCK) k_aggw_level(AggSplit sp, int level, int64_t block0) {
   __shared__ uint32_t smap[BLOCK / WAVE][WaveMap<K>::WORDS];
   const int64_t q = uniform(((block0 + blockIdx.x) * BLOCK + threadIdx.x) / WAVE);
-  if (q >= sp.nchunks) return;
+  if (q >= sp.tree_nodes) return;
   const int32_t x = uniform(sp.owner[q]);
   const int64_t half = (int64_t)1 << level;
   if (((q - sp.cstart[x]) & (2 * half - 1)) != 0) return;
@@ -1339,13 +1344,13 @@ static void agg_wave(const AggStreams &s, const int32_t *comms, int64_t ncomm, c
     const int64_t G = wave_group(K), maxch = (max_len + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
-      launch_slices(ceil_div(sp.nchunks, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+      launch_slices(ceil_div(sp.tree_nodes, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
         k_aggw_level<K><<<blocks, BLOCK, 0, st>>>(sp, l, first);
         MGCD_LAUNCHED();
       });
     }
     if (((int64_t)1 << l) < maxch) {
-      launch_slices(sp.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
+      launch_slices(sp.ntree, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
         k_aggw_tree<K><<<blocks, TREE_BLOCK, 0, st>>>(sp, l, first);
         MGCD_LAUNCHED();
       });
@@ -1498,8 +1503,8 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   uint32_t *cv0 = a.take<uint32_t>(m), *cv1 = a.take<uint32_t>(m);
   const bool wave = k > 16;  // the 32/64-slot sketch: one wave per stream, long ones split;
                             // 128/256 slots: every non-empty stream split
-  k_comm_keys<<<grid_for(m), BLOCK, 0, st>>>(mstart, P, m, L, !wave ? 0 : k > WAVE ? -1 : WAVE_SPLIT, ck0,
-                                             cv0, cnt);
+  k_comm_keys<<<grid_for(m), BLOCK, 0, st>>>(mstart, P, m, L, !wave ? 0 : k > WAVE ? -1 : WAVE_SPLIT,
+                                             wave ? wave_group(k) * L : 0, ck0, cv0, cnt);
   MGCD_LAUNCHED();
   bool cf = radix_sort_pairs(ck0, cv0, ck1, cv1, m, 8, a, st);
   int32_t *corder = a.take<int32_t>(m);
@@ -1507,6 +1512,8 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   MGCD_LAUNCHED();
   unsigned long long hc[9];
   read_spread(cnt, 8, hc, st);
+  const int64_t ntree = wave ? (int64_t)hc[1] : 0;
+  if (wave) hc[1] = 0;  // no category of its own
   AggBuckets bk{};
   int64_t pos = 0, items = 0;
   const int32_t *bucket_rows[7];
@@ -1525,7 +1532,7 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
   int32_t *multi = corder + pos;
   int64_t *cstart = nullptr;
   AggLong lg{multi, nmulti, nullptr, nullptr, nullptr, 0, nullptr};
-  AggSplit sp{multi, 0, nullptr, nullptr, 0, nullptr};
+  AggSplit sp{};
   if (nmulti > 0) {
     int64_t *nch = a.take<int64_t>(nmulti);
     cstart = a.take<int64_t>(nmulti + 1);
@@ -1534,10 +1541,14 @@ int64_t aggregate(const Graph &g, const int32_t *D, int32_t m, int mode, int k, 
     scan_i64(nch, cstart, nmulti, cstart + nmulti, a, st);
   }
   if (wave && nmulti > 0) {  // chunks of the split streams
-    const int64_t nchunks = read_i64(cstart + nmulti, st);
+    int64_t nchunks = 0, tree_nodes = 0;
+    HostRead rd(st);
+    rd.add(&nchunks, cstart + nmulti, sizeof(int64_t));
+    rd.add(&tree_nodes, cstart + ntree, sizeof(int64_t));
+    rd.wait();
     int32_t *owner = a.take<int32_t>(nchunks);
     comm_owners(cstart, nmulti, owner, st);
-    sp = AggSplit{multi, nmulti, cstart, owner, nchunks, a.take<Pair>(nchunks * k)};
+    sp = AggSplit{multi, nmulti, ntree, tree_nodes, cstart, owner, nchunks, a.take<Pair>(nchunks * k)};
   } else if (nmulti > 0) {
     // groups of 64 chunks per long stream
     int64_t *ng = a.take<int64_t>(nmulti);

@@ -1304,7 +1304,9 @@ __global__ void __launch_bounds__(BLOCK)
 //                  an odd last node is carried; after ceil(log2(nodes)) levels node 0
 //                  is the root, the same tree as WaveTree;
 //   k_wave_tree:   the levels at which every row has at most TREE_NODES nodes left, in one
-//                  launch: one workgroup per row, a barrier between levels;
+//                  launch: one workgroup per row, a barrier between levels (both over the
+//                  rows that may have more than one node; over all 4 M rows of a star at
+//                  K = 256, all split, they took 9.2 ms of a sweep);
 //   k_wave_count:  pass 2 of lossy rows, one workgroup per node's chunks (K = 128 / 256: one
 //                  wave), integer sums added into the row's counts (order-independent);
 //   k_wave_decide: one wave per row: scores and the decision, as in k_wave_rows.
@@ -2238,6 +2240,8 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n, int64_t bloc
 //          most 2^b <= 64 chunks (b = 1..6), 7 = longer rows;
 //   MG with K = 32 / 64: 0 = at most exact_t0 entries, 1 = one wave per row, 2 = split
 //          rows (more than max(L, WAVE_SPLIT) entries);
+//          (4 counts those of the split rows that may have more than one node: the first
+//          ones, heavy rows being first)
 //   exact: tiers 0..3 by degree; 4 counts the tier-2 rows for the smaller workgroup.
 //   every mode: rows without entries (category 8) are sorted last and listed in no
 //          kernel's work: their label can never change, so no sweep writes it, and
@@ -2248,10 +2252,19 @@ __global__ void k_gtab_clear(Pair *htab, uint32_t *hpos, int64_t n, int64_t bloc
 //          by class: 1..3, 4..7, 8..15, 16..32 entries, and longer ones.
 constexpr int NCAT = 16;
 constexpr int CAT_BLOCK = 4;  // exact: tier-2 rows of fewer than EXACT_BLOCK_MAX entries
+constexpr int CAT_TREE = 4;   // K >= 32: split rows of SchedParams::tree_class and up
 constexpr int CAT_EMPTY = 8;
 constexpr int CAT_LIGHT = 10;
 constexpr int CAT_CLASS = 11;
 constexpr int CAT_SHORT = 9;  // MG: rows whose sketch cannot lose weight (short rows' kernel)
+
+// The class of rows of deg entries that lists are ordered by: the bits of deg, 32 with 16..31
+// (the longest of their class of short rows).
+__host__ __device__ inline int row_class(int64_t deg) {
+  int b = 0;
+  while (b < 63 && (deg >> b) != 0) ++b;
+  return deg == 32 ? 5 : b;
+}
 
 __global__ void __launch_bounds__(BLOCK)
     k_schedule_keys(const int64_t *off, int32_t n, SchedParams sp, uint64_t *key, uint32_t *val,
@@ -2267,9 +2280,7 @@ __global__ void __launch_bounds__(BLOCK)
   if (i < n) {
     int64_t deg = off[i + 1] - off[i];
     dmax = deg;
-    int b = 0;
-    while (b < 63 && (deg >> b) != 0) ++b;  // bits of deg
-    if (deg == 32) b = 5;                   // with 16..31: the longest of their class
+    const int b = row_class(deg);
     uint64_t k;
     bool shortrow = false;
     if (deg == 0) {
@@ -2287,6 +2298,7 @@ __global__ void __launch_bounds__(BLOCK)
       cat = deg <= sp.exact_t0 ? 0 : (sp.k > WAVE || (deg > L && deg > WAVE_SPLIT)) ? 2 : 1;
       k = (uint64_t)(cat * 64 + 64 - b);  // heavy rows first in each tier
       shortrow = cat == 0;
+      if (cat == 2 && b >= sp.tree_class) cls = CAT_TREE;
     } else if (deg <= sp.mg_short) {  // after the single-chunk rows, heavy rows first
       cat = CAT_SHORT;
       shortrow = true;
@@ -2423,6 +2435,7 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
   const int mode = sp.mode, k = sp.k;
   const int64_t L = sp.L;
   const int32_t n = g.n;
+  if (sp.wave) sp.tree_class = row_class(wave_group(k) * L + 1);
   s = Schedule{};
   if (n == 0) return;
   unsigned long long *cnt = a.take<unsigned long long>(SPREAD * (NCAT + 1));
@@ -2463,7 +2476,11 @@ static void build_lists(const Graph &g, const SchedParams &sp_in, Schedule &s, A
       k_chunk_counts<<<grid_for(s.nmulti), BLOCK, 0, st>>>(g.off, s.multi, s.nmulti, wave_group(k) * L, nch);
       MGCD_LAUNCHED();
       scan_i64(nch, s.cstart, s.nmulti, s.cstart + s.nmulti, a, st);
-      read_back(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t), st);
+      s.ntree = (int64_t)h[CAT_TREE];
+      HostRead rd(st);
+      rd.add(&s.nchunks, s.cstart + s.nmulti, sizeof(int64_t));
+      rd.add(&s.tree_nodes, s.cstart + s.ntree, sizeof(int64_t));
+      rd.wait();
       s.owner = a.take<int32_t>(s.nchunks);
       chunk_owners(s.cstart, s.nmulti, s.owner, st);
       s.wnode = a.take<Pair>(s.nchunks * k);
@@ -2792,13 +2809,14 @@ static void sweep_wave(const SweepArgs &a, const Schedule &s, int64_t L, hipStre
     const int64_t G = wave_group(K), maxch = (s.maxdeg + G * L - 1) / (G * L);
     int l = 0;
     for (; (maxch >> l) > TREE_NODES; ++l) {
-      launch_slices(ceil_div(s.nchunks, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
-        k_wave_level<K><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.nchunks, l, first, s.wnode, s.wflag);
+      launch_slices(ceil_div(s.tree_nodes, BLOCK / WAVE), BLOCK, [&](int64_t first, unsigned blocks) {
+        k_wave_level<K><<<blocks, BLOCK, 0, st>>>(a, s.multi, s.cstart, s.owner, s.tree_nodes, l, first, s.wnode,
+                                                  s.wflag);
         MGCD_LAUNCHED();
       });
     }
     if (((int64_t)1 << l) < maxch) {
-      launch_slices(s.nmulti, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
+      launch_slices(s.ntree, TREE_BLOCK, [&](int64_t first, unsigned blocks) {
         k_wave_tree<K><<<blocks, TREE_BLOCK, 0, st>>>(a, s.multi, s.cstart, l, first, s.wnode, s.wflag);
         MGCD_LAUNCHED();
       });

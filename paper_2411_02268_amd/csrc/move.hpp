@@ -159,6 +159,8 @@ struct Schedule {
   uint32_t *cflag = nullptr;  // [nmulti] 0 decided, 1 lossy, 2 frozen
   // MG with K >= 32: multi, cstart and owner list the split rows and their nodes
   // (wave_group(k) chunks each; nchunks of them)
+  int64_t ntree = 0;          // split rows that may have more than one node: the first of multi,
+  int64_t tree_nodes = 0;     // with the first nodes
   Pair *wnode = nullptr;      // [nchunks * k] sketches of the nodes, merged in place
   uint32_t *wflag = nullptr;  // [nchunks] the node's sketches or merges lost weight
   uint32_t *wcount = nullptr; // [nmulti * (k+1)] pass-2 counts per candidate slot, then K_{i->d}
@@ -199,6 +201,8 @@ struct SchedParams {
   int64_t exact_t0 = 32, exact_t1 = 512, exact_t2 = 4096;
   bool wave = false;  // K = 32 / 64: rows of at most exact_t0 entries exact, the rest one
                       // wave each
+  int tree_class = 64;  // wave: split rows of this class and up may have more than one node
+                        // (set by build_schedule)
   // K <= 16, Algorithm 1 or the textbook rule: rows of at most mg_short entries hold at
   // most K distinct keys, so no update or merge ever removes weight and the sketch is
   // the row's exact table; they take the short rows' kernel (0: none).  short_auto:
