@@ -199,11 +199,13 @@ static int32_t *tile_first_rows(const Graph &g, Arena &a, hipStream_t st) {
   return first;
 }
 
-// Whether the workspace holds the table (a fixed scratch may not: then each workgroup finds
-// its rows by binary search).
-static bool tile_table_fits(const Graph &g, const Arena &a) {
+// The table, or null for a graph without entries or where the workspace does not hold it and
+// `more` bytes behind it (a fixed scratch may not: then each workgroup finds its rows by
+// binary search).
+const int32_t *tile_table(const Graph &g, size_t more, Arena &a, hipStream_t st) {
   const size_t tb = (size_t)(ceil_div(g.nnz, SF_TILE) + 1) * 4;
-  return ((a.used + 255) & ~(size_t)255) + tb <= a.cap;
+  const bool fits = ((a.used + 255) & ~(size_t)255) + tb + more <= a.cap;
+  return g.nnz > 0 && fits ? tile_first_rows(g, a, st) : nullptr;
 }
 
 // Rows of a tile of consecutive CSR entries [e0, e1) (non-empty): the rows meeting it
@@ -339,14 +341,15 @@ __global__ void k_fold_total(const unsigned long long *part, unsigned long long 
 
 size_t degrees_ws_bytes(int64_t nnz) { return (size_t)SPREAD * 8 + 4096 + tile_table_bytes(nnz); }
 
-void launch_degrees(const Graph &g, uint32_t *K, unsigned long long *W, Arena &a, hipStream_t st) {
+void launch_degrees(const Graph &g, uint32_t *K, unsigned long long *W, Arena &a, hipStream_t st,
+                    const int32_t *table) {
   static_assert(SPREAD == WAVE, "k_fold_total folds one copy per lane");
   size_t mk = a.mark();
   unsigned long long *part = a.take<unsigned long long>(SPREAD);
   launch_zero_u64(part, SPREAD, st);
   if (g.n > 0) zero_u32(K, g.n, st);
   if (g.nnz > 0) {
-    const int32_t *first = tile_table_fits(g, a) ? tile_first_rows(g, a, st) : nullptr;
+    const int32_t *first = table ? table : tile_table(g, 0, a, st);
     k_row_weight_sums<<<(unsigned)ceil_div(g.nnz, DG_TILE), BLOCK, 0, st>>>(g, first, K, part);
     MGCD_LAUNCHED();
   }
@@ -451,15 +454,14 @@ __global__ void __launch_bounds__(BLOCK)
 }
 
 void modularity_terms(const Graph &g, const int32_t *C, const uint32_t *K, unsigned long long *terms,
-                      Arena &a, hipStream_t st) {
+                      Arena &a, hipStream_t st, const int32_t *table) {
   launch_zero_u64(terms, 2 * SPREAD, st);
   if (g.n == 0) return;
   size_t mk = a.mark();
   uint32_t *tot = a.take<uint32_t>(g.n);
   zero_u32(tot, g.n, st);
   if (g.nnz > 0) {
-    const int32_t *first = tile_table_fits(g, a) ? tile_first_rows(g, a, st) : nullptr;
-    k_intra<<<(unsigned)ceil_div(g.nnz, SF_TILE), BLOCK, 0, st>>>(g, first, C, terms);
+    k_intra<<<(unsigned)ceil_div(g.nnz, SF_TILE), BLOCK, 0, st>>>(g, table, C, terms);
     MGCD_LAUNCHED();
   }
   k_comm_tot<<<grid_for(g.n), BLOCK, 0, st>>>(C, K, g.n, tot);

@@ -32,9 +32,13 @@ void launch_compose(const int32_t *in, const int32_t *map, int32_t *out, int32_t
 void launch_scatter_labels(const int32_t *map, const int32_t *val, int32_t *out, int32_t n,
                            hipStream_t st);
 
-// K[i] = row sums (uint32) and *W = their total (device uint64).  Uses nnz + 1
-// int64 of transient workspace.
-void launch_degrees(const Graph &g, uint32_t *K, unsigned long long *W, Arena &a, hipStream_t st);
+// The first row of every tile of 2,048 entries, for launch_degrees and modularity_terms; null
+// where the workspace does not hold it and `more` bytes.
+const int32_t *tile_table(const Graph &g, size_t more, Arena &a, hipStream_t st);
+// K[i] = row sums (uint32) and *W = their total (device uint64); degrees_ws_bytes of
+// transient workspace.  table: tile_table's, or null.
+void launch_degrees(const Graph &g, uint32_t *K, unsigned long long *W, Arena &a, hipStream_t st,
+                    const int32_t *table = nullptr);
 size_t degrees_ws_bytes(int64_t nnz);
 
 // Storage copy of a graph for local moving: vertices laid out in descending degree
@@ -56,7 +60,8 @@ int32_t canonical(const int32_t *C, int32_t n, int32_t *out, Arena &a, hipStream
 // Integers of Eq. 1: I = weight of intra-community entries, S2 = sum of Sigma_c^2,
 // accumulated in SPREAD copies: terms[2c] (parts of I) and terms[2c + 1] (parts of S2).
 void modularity_terms(const Graph &g, const int32_t *C, const uint32_t *K,
-                      unsigned long long *terms /* device [2 * SPREAD] */, Arena &a, hipStream_t st);
+                      unsigned long long *terms /* device [2 * SPREAD] */, Arena &a, hipStream_t st,
+                      const int32_t *table);
 
 // *flag = 1 when some C[i] (i < n) lies outside [0, limit).
 void launch_check_labels(const int32_t *C, int64_t n, int64_t limit, unsigned long long *flag,

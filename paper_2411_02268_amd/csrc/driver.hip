@@ -515,8 +515,10 @@ static void modularity_in(const Graph &g, const int32_t *C, double *q, void *ws,
   uint32_t *K = a.take<uint32_t>(g.n);
   unsigned long long *Wd = a.take<unsigned long long>(1);
   unsigned long long *terms = a.take<unsigned long long>(2 * SPREAD);
-  launch_degrees(g, K, Wd, a, st);
-  modularity_terms(g, C, K, terms, a, st);
+  // one table for both; the community totals come behind it
+  const int32_t *table = tile_table(g, (size_t)g.n * sizeof(uint32_t) + 4096, a, st);
+  launch_degrees(g, K, Wd, a, st, table);
+  modularity_terms(g, C, K, terms, a, st, table);
   unsigned long long ht[2 * SPREAD], h[2] = {0, 0};
   unsigned long long W = 0;
   HostRead rd(st);
