@@ -8,8 +8,10 @@ namespace mgcd {
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = BLOCK * SCAN_ITEMS;  // 2048 items per workgroup
 // Scans of at most so many tiles are one launch: the last of eight workgroups reads the
-// seven tiles before its own in 14 loads per thread, all on their way at once, and the scan
-// of 16,384 counts takes 9 us instead of 12 in three launches with two gaps between them.
+// seven tiles before its own in 14 loads per thread, all on their way at once.  32-bit
+// counts of 2, 4 and 8 tiles take 5.5, 5.9 and 7.0 us, in three launches 11.2 to 11.4 (one
+// tile 4.7).  With a limit of 16, scans of 9 and 16 tiles take 8.0 and 9.7 us instead of 11.4,
+// but those of 2 to 8 tiles 0.7 more, for the loads of the largest; most scans are small.
 constexpr int SCAN_ALONE = 8;
 
 template <typename Tin>
@@ -39,11 +41,13 @@ __global__ void __launch_bounds__(BLOCK)
     const int64_t before = (int64_t)blockIdx.x * SCAN_TILE;
     int64_t acc = 0;
     if constexpr (sizeof(Tin) == 4) {  // whole tiles: 128-bit loads, all on their way at once
+      if (before > 0) {  // block-uniform
 #pragma unroll
-      for (int r = 0; r < (SCAN_ALONE - 1) * SCAN_ITEMS / 4; ++r) {
-        const int64_t i = ((int64_t)r * BLOCK + threadIdx.x) * 4;
-        const v4u x = load4(reinterpret_cast<const uint32_t *>(in), i, n, i < before);
-        acc += (int64_t)x.x + x.y + x.z + x.w;
+        for (int r = 0; r < (SCAN_ALONE - 1) * SCAN_ITEMS / 4; ++r) {
+          const int64_t i = ((int64_t)r * BLOCK + threadIdx.x) * 4;
+          const v4u x = load4(reinterpret_cast<const uint32_t *>(in), i, n, i < before);
+          acc += (int64_t)x.x + x.y + x.z + x.w;
+        }
       }
     } else {
 #pragma unroll 8
