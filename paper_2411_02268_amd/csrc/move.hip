@@ -1137,8 +1137,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(row_
   }
 }
 
-// A level of light rows alone (its own kernel has a third more waves per SIMD than
-// k_move_rows).  PERSIST as in k_move_rows, a wave taking the items.
+// The light rows of a level that has no others, and of every level of a batch (its own kernel
+// has a third more waves per SIMD than k_move_rows).  PERSIST as in k_move_rows, a wave
+// taking the items.
 template <int K, int ALGO, int MODE, bool PERSIST>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(light_waves_per_simd<K>())))
     k_move_light(SweepArgs a, const int32_t *__restrict__ rows, int64_t nrows, int64_t first,
