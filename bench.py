@@ -34,12 +34,14 @@ PEAK_HBM_GBS = 8000.0  # MI355X HBM3E, GB/s
 # HBM bytes of one level-0 launch of the main sweep kernel, per (workload, level 0 on
 # the storage copy, short_rows), from FETCH_SIZE and WRITE_SIZE (rocprofv3 --pmc, one
 # counter per run) scaled by what the counters read for a 512 MiB device copy (FETCH
-# x 2.0, WRITE x 1.0); commands and figures in profiles/k_move_rows_rmat20_counters.md.
-# Each figure is valid only for the kernel sources it was taken on (the SHA-256 of
-# TRAFFIC_SOURCES beside it, checked at run time); traffic is reported as null when the
-# sources differ.
+# x 2.0, WRITE x 1.0); commands and figures in profiles/k_move_rows_rmat20_counters.md
+# and profiles/k_move_rows_cl24_leiden_counters.md.  Each figure is valid only for the
+# kernel sources it was taken on (the SHA-256 of TRAFFIC_SOURCES beside it, checked at
+# run time); traffic is reported as null when the sources differ.
 TRAFFIC_BYTES = {
-    ("louvain-mg-k8-rmat20", False, 0): (1858319464, "4e5ef8bbc5c729028b26b9f3ccb505f016fe3f12f4404adfc647d8162ee923fc"),
+    ("louvain-mg-k8-rmat20", False, 0): (1856726938, "191b993ad9a40f4cf961a4bd19d69350079d36f4d543fd7391f4a446f254072c"),
+    ("leiden-mg-k16-cl24", False, 0): (72407291904, "191b993ad9a40f4cf961a4bd19d69350079d36f4d543fd7391f4a446f254072c"),
+    ("leiden-mg-k16-cl24", True, 0): (62824325120, "191b993ad9a40f4cf961a4bd19d69350079d36f4d543fd7391f4a446f254072c"),
 }
 TRAFFIC_SOURCES = ["csrc/move.hip", "csrc/move.hpp", "csrc/sketch.hpp", "csrc/common.hpp", "csrc/quad_sketch.hpp"]
 
