@@ -27,11 +27,12 @@ def step_ms(mg, g, **kw):  # noqa: F811
 
 def test_rest_of_a_step(mg):  # noqa: F811
     """2.5 M rows of 7 entries on the short rows' kernel, on the light rows', and half as many
-    entries again on the main kernel: their rest differs by no more than the few sweeps do."""
+    entries again on the main kernel.  The light rows' launch has twice the short rows'
+    workgroups, which only end; with the rows gone over it takes six times as long."""
     small = cliques(2500000 // 8, 8)
     short, a = step_ms(mg, small, k=8, short_rows=2)
     light, b = step_ms(mg, small, k=8, short_rows=1)
     heavy, c = step_ms(mg, cliques(400000 // 40, 40), k=8)
     print(f"a step of {SWEEPS} sweeps: short rows {short:.2f} ms, light rows {light:.2f}, heavy rows {heavy:.2f}")
     assert np.array_equal(a, np.arange(a.size) // 8) and np.array_equal(a, b) and np.array_equal(c, np.arange(c.size) // 40)
-    assert light < 2 * short and heavy < 2 * short
+    assert light < 3 * short and heavy < 1.5 * short
